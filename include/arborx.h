@@ -107,7 +107,9 @@ const char *arborx_last_error(void);
  * Device memory hook.  The library takes all of its device memory (tree and
  * forest storage, per-call temporaries, CSR plans) from alloc_fn and returns it
  * to free_fn, for example to share a framework's caching allocator; by
- * default it uses stream-ordered allocations from the device's pool.
+ * default it uses stream-ordered allocations from the device's pool and keeps
+ * freed blocks for its later calls (at most a quarter of the device's memory;
+ * given back when an allocation fails or a hook is installed).
  *   alloc_fn(bytes, stream, ctx) returns device memory for work queued on
  *     `stream`, or NULL (the call then fails with ARBORX_E_NOMEM).
  *   free_fn(ptr, stream, ctx) hands a block back.  `stream` is the stream the

@@ -1294,24 +1294,18 @@ arborx_status build_tree(const float *values, int64_t n, int dim, int kind, Tree
 
 void forest_release(ForestDev &f, hipStream_t s)
 {
-    dfree(f.nodes, s);
-    dfree(f.qnodes, s);
-    f.qnodes = nullptr;
-    dfree(f.wnodes, s);
-    f.wnodes = nullptr;
-    dfree(f.leaves, s);
-    dfree(f.hdrs, s);
-    dfree(f.seg, s);
-    dfree(f.ws, s);
-    dfree(f.bws, s);
-    f.bws = nullptr;
-    f.bws_bytes = 0;
+    void *const blocks[] = {f.nodes, f.qnodes, f.wnodes, f.leaves, f.hdrs, f.seg, f.ws, f.bws};
+    dfree_many(blocks, (int)(sizeof(blocks) / sizeof(blocks[0])), s);
     f.nodes = nullptr;
+    f.qnodes = nullptr;
+    f.wnodes = nullptr;
     f.leaves = nullptr;
     f.hdrs = nullptr;
     f.seg = nullptr;
     f.ws = nullptr;
     f.ws_bytes = 0;
+    f.bws = nullptr;
+    f.bws_bytes = 0;
 }
 
 arborx_status forest_alloc(int64_t n, int T, int dim, int kind, ForestDev &f, hipStream_t s)

@@ -92,6 +92,16 @@ arborx_status hip_fail(hipError_t e, const char *what);
 // Stream-ordered device allocation; returns ARBORX_E_NOMEM on failure.
 arborx_status dalloc(void **p, size_t bytes, hipStream_t s);
 void dfree(void *p, hipStream_t s);
+// The same for several blocks at once (NULL entries are skipped): one event
+// covers them all.
+void dfree_many(void *const *p, int n, hipStream_t s);
+
+struct QueryHeader;
+// A header in pinned host memory that kernels write directly: the total of a
+// CSR count reaches the host with the synchronisation alone, without a copy
+// behind it.  NULL when pinned memory runs out.
+QueryHeader *host_header_get();
+void host_header_put(QueryHeader *h);
 
 // Scoped set of stream-ordered temporaries, freed on destruction.
 struct Temps {
@@ -101,8 +111,7 @@ struct Temps {
     explicit Temps(hipStream_t st) : s(st) {}
     ~Temps()
     {
-        for (int i = 0; i < n; ++i)
-            dfree(ptrs[i], s);
+        dfree_many(ptrs, n, s);
     }
     template <typename T>
     arborx_status get(T **p, size_t count)
