@@ -750,18 +750,38 @@ struct KnnEntry {
     float d2;
 };
 
+// Minimum and maximum of two top-k keys held as doubles.  The bit pattern of
+// a float32 distance >= 0 (up to +inf, and NaN) in the high word makes a
+// positive finite double (its exponent field is at most 0x7ff - 1), so the
+// double order is the order of the 64-bit words, and one instruction each
+// replaces a 64-bit compare and two selects.  A denormal (distance 0) keeps
+// its bits: double denormals are always on.  Written as instructions because
+// the library calls would canonicalise their operands first.
+__device__ __forceinline__ double key_min(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double key_max(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // The K best (distance, index) pairs of one query in ascending order, each
-// packed as one 64-bit key: the float32 bits of a distance >= 0 order like the
-// distance itself, so comparing keys compares distances first and breaks ties
-// by the smaller index, with no mask arithmetic.  An empty slot holds index
-// INT32_MAX.
+// packed as one 64-bit key, distance bits above index: the float32 bits of a
+// distance >= 0 order like the distance itself, so comparing keys compares
+// distances first and breaks ties by the smaller index.  The word is kept as a
+// double (key_min).  An empty slot holds index INT32_MAX.
 template <int K>
 struct TopK {
-    uint64_t key[K];
+    double key[K];
 
-    __device__ static __forceinline__ uint64_t pack(float d, int id)
+    __device__ static __forceinline__ double pack(float d, int id)
     {
-        return ((uint64_t)__float_as_uint(d) << 32) | (uint32_t)id;
+        return __hiloint2double((int)__float_as_uint(d), id);
     }
     __device__ __forceinline__ void reset(float bound)
     {
@@ -770,27 +790,26 @@ struct TopK {
             key[s] = pack(bound, INT32_MAX);
     }
     // distance of the K-th best: a box farther than this cannot contribute
-    __device__ __forceinline__ float bound() const { return __uint_as_float((uint32_t)(key[K - 1] >> 32)); }
-    // Insertion from the back: the new key displaces the last slot and moves
-    // left past larger keys.  A candidate that gets in usually ranks near the
-    // end, so the walk stops as soon as no lane of the wavefront still moves.
+    __device__ __forceinline__ float bound() const { return __int_as_float(__double2hiint(key[K - 1])); }
+    // Insertion: slot s becomes the middle one of its key, its left neighbour's
+    // and the new one, so a key above all of them changes nothing and no lane
+    // needs a branch of its own.  In a wavefront some lane nearly always
+    // inserts, and a candidate that gets in usually ranks near the end: the
+    // slots are done in groups of eight from the back, until no lane goes on.
+    // (Against 64-bit compares and selects slot by slot: 1000 queries of k = 10
+    // in 2*10^4 points 111 -> 77 us, k = 16 at 10^7 points 8.6 -> 8.0 ms.)
     __device__ __forceinline__ void offer(float d, int id)
     {
-        const uint64_t v = pack(d, id);
-        bool moving = v < key[K - 1];
-        if (!moving)
+        const double v = pack(d, id);
+        if (!(v < key[K - 1]))
             return;
 #pragma unroll
         for (int s = K - 1; s > 0; --s) {
-            const uint64_t prev = key[s - 1];
-            const bool shift = moving && v < prev;
-            key[s] = shift ? prev : (moving ? v : key[s]);
-            moving = shift;
-            if (__ballot(moving) == 0)
+            key[s] = key_min(key[s], key_max(key[s - 1], v));
+            if (s % 8 == 0 && __ballot(v < key[s - 1]) == 0)
                 return;
         }
-        if (moving)
-            key[0] = v;
+        key[0] = key_min(key[0], v);
     }
     // Write the first k_out, indices relative to `base`; empty slots become (+inf, -1).
     __device__ __forceinline__ void store(int k_out, float *d2, int32_t *idx, int base) const
@@ -798,9 +817,9 @@ struct TopK {
 #pragma unroll
         for (int s = 0; s < K; ++s) {
             if (s < k_out) {
-                const int id = (int)(uint32_t)key[s];
+                const int id = __double2loint(key[s]);
                 const bool empty = id == INT32_MAX;
-                d2[s] = empty ? INFINITY : __uint_as_float((uint32_t)(key[s] >> 32));
+                d2[s] = empty ? INFINITY : __int_as_float(__double2hiint(key[s]));
                 idx[s] = empty ? -1 : id - base;
             }
         }
