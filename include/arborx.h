@@ -83,7 +83,7 @@ typedef struct arborx_tuning {
                              per fetch).  Every format gives identical results.  Formats 1 and 2 are built only
                              while some operation asks for them when the tree is built; asking later is
                              ARBORX_E_INVALID.  The defaults (arborx_set_tuning(NULL)): 1 for ARBORX_OP_SPATIAL
-                             and ARBORX_OP_REDUCE, 0 for ARBORX_OP_KNN, over trees of points; under them a 6D
+                             and ARBORX_OP_REDUCE, 0 for ARBORX_OP_KNN, over trees of points; under them a
                              kNN over points also walks format 1, while trees of boxes, forests and a tree built
                              without format 1 are walked on format 0 */
     int32_t queries_per_thread; /* radius searches (CSR count pass of sphere queries, fused reductions) with

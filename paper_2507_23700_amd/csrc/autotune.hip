@@ -323,7 +323,9 @@ extern "C" arborx_status arborx_autotune(arborx_tree tree, int32_t op, const flo
         return st != ARBORX_OK ? st : fail(ARBORX_E_DEVICE, "no candidate ran");
     }
     besti = keep_unless_faster(cands, besti);
-    const Tuning &b = cands[besti].t;
+    Tuning &b = cands[besti].t;
+    if (op == OP_KNN)  // the defaults choose kNN's format themselves: record the one that ran
+        b.nodes = node_format_of(b, op, dim, kind, false);
     set_tuning_op(op, b);
     cache_store(key, b, cands[besti].ms);
     if (best) {

@@ -49,6 +49,28 @@ __device__ __forceinline__ float quant_scale(float lo, float hi)
     return s;
 }
 
+// The frame of a tree: one step for every dimension, the largest of them, so
+// that walks measure distances in codes (CodeBall), unless some extent is
+// below 1/256 of the largest; that keeps at least 256 codes across every
+// extent, and the largest extent has no finer codes either way.
+template <int D>
+__device__ void quant_frame(const float *lo, const float *hi, float *qscale, double *qinv)
+{
+    float most = 0.0f, least = INFINITY;
+    for (int d = 0; d < D; ++d) {
+        qscale[d] = quant_scale(lo[d], hi[d]);
+        most = fmaxf(most, qscale[d]);
+        if (qscale[d] > 0.0f)
+            least = fminf(least, qscale[d]);
+    }
+    *qinv = 0.0;
+    if (most > 0.0f && most < INFINITY && most * (1.0f / 256.0f) <= least) {
+        *qinv = 1.0 / (double)most;
+        for (int d = 0; d < D; ++d)
+            qscale[d] = most;
+    }
+}
+
 // Largest code whose decoded value is <= x, and smallest whose decoded value
 // is >= x.  The estimate from the reciprocal step `inv` is corrected both ways
 // against the decode itself, so the result does not depend on its rounding.
@@ -172,9 +194,12 @@ __global__ __launch_bounds__(kBuildBlock) void bounds_final(const float *__restr
         }
         hdr->lo[d] = lo;
         hdr->hi[d] = hi;
-        hdr->qscale[d] = quant_scale(lo, hi);
+        s_lo[0][d] = lo;
+        s_hi[0][d] = hi;
     }
+    __syncthreads();
     if (d == 0) {
+        quant_frame<D>(s_lo[0], s_hi[0], hdr->qscale, &hdr->qinv);
         hdr->n = (int32_t)n;
         hdr->root = n > 0 ? 0 : -1;
         hdr->height = 0;
@@ -396,29 +421,23 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
         const int32_t ref = nd.child[c];
         if (ref == kEmptyRef) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                qn.q[c][0][d] = (uint16_t)kQMax;
-                qn.q[c][1][d] = 0;
-            }
+            for (int d = 0; d < D; ++d)
+                qn.w[c][d] = 0xffffffffu;
             qn.child[c] = kEmptyRef;
             continue;
         }
         if (ref < 0 && kind != ARBORX_BOXES) {
-            uint16_t *qc = &qn.q[c][0][0];
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const uint32_t bits = __float_as_uint(nd.lo[c][d]);
-                qc[2 * d] = (uint16_t)(bits & 0xffffu);
-                qc[2 * d + 1] = (uint16_t)(bits >> 16);
-            }
+            for (int d = 0; d < D; ++d)
+                qn.w[c][d] = __float_as_uint(nd.lo[c][d]);
             qn.child[c] = ref;
             continue;
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const float inv = h.qscale[d] > 0.0f ? 1.0f / h.qscale[d] : 0.0f;
-            qn.q[c][0][d] = (uint16_t)qcode_down(nd.lo[c][d], h.lo[d], h.qscale[d], inv);
-            qn.q[c][1][d] = (uint16_t)qcode_up(nd.hi[c][d], h.lo[d], h.qscale[d], inv);
+            qn.w[c][d] = qcode_down(nd.lo[c][d], h.lo[d], h.qscale[d], inv) |
+                         (((uint32_t)kQMax - qcode_up(nd.hi[c][d], h.lo[d], h.qscale[d], inv)) << 16);
         }
         qn.child[c] = ref >= 0 ? ref : ~(p + c);
     }
@@ -764,6 +783,7 @@ __global__ void empty_header(TreeHeader *hdr, int dim)
 {
     for (int d = 0; d < kMaxDim; ++d)
         hdr->qscale[d] = 0.0f;
+    hdr->qinv = 0.0;
     hdr->root = -1;
     hdr->height = 0;
     hdr->n = 0;
@@ -980,8 +1000,11 @@ __global__ void forest_headers(const int64_t *__restrict__ seg, int T, const uin
     for (int d = 0; d < kMaxDim; ++d) {
         h.lo[d] = (d < D && n > 0) ? order_float(tmin[t * D + d]) : INFINITY;
         h.hi[d] = (d < D && n > 0) ? order_float(tmax[t * D + d]) : -INFINITY;
-        h.qscale[d] = (d < D && n > 0) ? quant_scale(h.lo[d], h.hi[d]) : 0.0f;
+        h.qscale[d] = 0.0f;
     }
+    h.qinv = 0.0;
+    if (n > 0)
+        quant_frame<D>(h.lo, h.hi, h.qscale, &h.qinv);
 }
 
 template <int D>

@@ -140,10 +140,9 @@ static thread_local std::string g_error;
 // Defaults measured on MI355X at 10^7 points: 256-thread blocks for the radius
 // walks; 64-thread blocks and an 8-entry LDS ring for kNN (its 8-byte stack
 // entries and larger register set).  Over trees of points the radius walks
-// run over quantized nodes (half the node loads; a point's leaf is exact in
-// its parent), the CSR count one query per thread; kNN over float nodes up to
-// 3D, where its top-k insertions rather than node loads bound it
-// (node_format_of below).
+// and kNN run over quantized nodes (half the node loads; a point's leaf is
+// exact in its parent; node_format_of below), the CSR count one query per
+// thread.
 static Tuning default_tuning(int op)
 {
     Tuning t;
@@ -183,7 +182,9 @@ int node_format_of(const Tuning &t, int op, int dim, int kind, bool forest)
         return t.nodes;
     if (forest || kind == ARBORX_BOXES)  // a box leaf is not exact in the node: its record is fetched again
         return 0;
-    return op == OP_KNN && dim >= 6 ? 1 : t.nodes;
+    if (op == OP_KNN)  // four-wide nodes only where a saved choice of the autotuner names them
+        return t.nodes == 2 && dim < 6 ? 2 : 1;
+    return t.nodes;
 }
 
 int node_format(int op, int dim, int kind, bool forest) { return node_format_of(tuning(op), op, dim, kind, forest); }

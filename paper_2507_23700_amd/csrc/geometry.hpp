@@ -73,16 +73,20 @@ __device__ __forceinline__ void store_leaf(float *leaves, int64_t pos, int kind,
 // The same node with each child box stored as 16-bit codes in the tree's
 // frame (lo + code * qscale per dimension), rounded outward so that the
 // decoded box always contains the true one: tests on it are conservative.
-// In a tree of points a leaf child is stored exactly instead: the point's D
-// float32 words take the 4*D bytes of that child's codes, and the reference
-// is ~value index as in the float node, so leaf tests need no second fetch
-// and give the float node's results bit for bit.  In a tree of boxes a leaf
-// child refers to its sorted leaf record (~position), whose exact box decides
-// the match.  32 bytes in 3D, half the float node; 64 bytes in 6D.
+// Word d of a child is lo code | (65535 - hi code) << 16: both halves grow as
+// the box shrinks away from a query, so one saturating 16-bit pair subtraction
+// gives both gaps of the dimension (CodeBall below).  In a tree of points a
+// leaf child is stored exactly instead: word d is the point's float32
+// coordinate, and the reference is ~value index as in the float node, so leaf
+// tests need no second fetch and give the float node's results bit for bit.
+// In a tree of boxes a leaf child refers to its sorted leaf record
+// (~position), whose exact box decides the match.  The empty slot's words are
+// all ones: no box contains it, and as floats they are NaN, at no distance
+// from anything.  32 bytes in 3D, half the float node; 64 bytes in 6D.
 template <int D>
 struct alignas(16) QNode {
-    uint16_t q[2][2][D];  // [child][lo, hi][dim]
-    int32_t child[2];     // >= 0 node, < 0 leaf record ~ref, kEmptyRef empty
+    uint32_t w[2][D];  // [child][dim]
+    int32_t child[2];  // >= 0 node, < 0 leaf record ~ref, kEmptyRef empty
     int32_t pad[(16 - (8 * D + 8) % 16) % 16 / 4];
 };
 static_assert(sizeof(QNode<3>) == 32, "3D quantized node is 32 bytes");
@@ -132,15 +136,68 @@ template <int D>
 __device__ __forceinline__ void qchild(const QNode<D> &nd, int c, bool exact, const float *flo, const float *fsc,
                                        float (&lo)[D], float (&hi)[D])
 {
-    const uint16_t *qc = &nd.q[c][0][0];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        const float p = __uint_as_float((uint32_t)qc[2 * d] | ((uint32_t)qc[2 * d + 1] << 16));
-        const float l = qdecode(qc[d], flo[d], fsc[d]);
-        const float h = qdecode(qc[D + d], flo[d], fsc[d]);
+        const uint32_t w = nd.w[c][d];
+        const float p = __uint_as_float(w);
+        const float l = qdecode(w & 0xffffu, flo[d], fsc[d]);
+        const float h = qdecode((uint32_t)kQMax - (w >> 16), flo[d], fsc[d]);
         lo[d] = exact ? p : l;
         hi[d] = exact ? p : h;
     }
+}
+
+// A ball around a query in the codes of a frame with one step s for every
+// dimension.  q[d] = (smallest code at or above the query) | (65535 - largest
+// code at or below it) << 16, both moved outward by the error of decoding, so
+// that for a box [lo, hi] with word w the halves of w - q, saturated at zero,
+// are at most (lo - query)/s and (query - hi)/s, the box's gaps: one of them
+// is zero, and the sum of their squares over the dimensions times s^2 is at
+// most the squared distance to the box.  r2: a box whose sum is above it holds
+// no value within the radius.  Clamping a query outside the frame to its
+// border only shortens the gaps.
+template <int D>
+struct CodeBall {
+    uint32_t q[D];
+    uint32_t r2;
+};
+
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+
+// The sum of squared gaps between the ball's query and child box w, saturated.
+template <int D>
+__device__ __forceinline__ uint32_t code_gap2(const uint32_t (&q)[D], const uint32_t (&w)[D])
+{
+    uint32_t acc = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const ushort2_t g = __builtin_elementwise_sub_sat(__builtin_bit_cast(ushort2_t, w[d]),
+                                                          __builtin_bit_cast(ushort2_t, q[d]));
+        acc = __builtin_amdgcn_udot2(g, g, acc, true);
+    }
+    return acc;
+}
+
+// The code words of query c.  inv = 1/s; lo, hi: the frame.
+__device__ __forceinline__ uint32_t code_query(float c, float lo, float hi, double inv)
+{
+    // decode(code) is off by half an ulp of a coordinate at most; the last term covers the arithmetic here
+    const double m = fmax(fabs((double)lo), fabs((double)hi));
+    const double slop = (m * 0x1p-23 + 0x1p-148) * inv + 0x1p-8;
+    const double u = ((double)c - (double)lo) * inv;
+    const double up = ceil(u + slop), dn = floor(u - slop);
+    const uint32_t qhi = up >= (double)kQMax ? (uint32_t)kQMax : (up > 0.0 ? (uint32_t)up : 0u);
+    const uint32_t qlo = dn >= (double)kQMax ? (uint32_t)kQMax : (dn > 0.0 ? (uint32_t)dn : 0u);
+    return qhi | (((uint32_t)kQMax - qlo) << 16);
+}
+
+// Threshold on code_gap2 for squared radius r2.  A value matches when its
+// float32 squared distance, within a factor 1 +- 2^-20 and 16 * 2^-149 of the
+// real one, is at most r2.
+__device__ __forceinline__ uint32_t code_radius2(float r2, double inv)
+{
+    const double r = ((double)r2 * (1.0 + 0x1p-18) + 0x1p-144) * inv * inv * (1.0 + 0x1p-30) + 1.0;
+    return r < 4294967295.0 ? (uint32_t)r : UINT32_MAX;
 }
 
 template <int D>

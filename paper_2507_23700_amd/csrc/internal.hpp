@@ -25,6 +25,10 @@ struct TreeHeader {
     float lo[kMaxDim];
     float hi[kMaxDim];
     float qscale[kMaxDim];  // quantized-node frame: coordinate = lo + code * qscale
+    // One step for every dimension, 1/qscale; 0 where the extents differ too
+    // much for that (quant_frame) or there is no extent: sphere walks then take
+    // the float nodes.
+    double qinv;
 };
 
 // Device-resident per-call header of a CSR query, written by the scan.
@@ -61,8 +65,7 @@ const Tuning &tuning(int op = OP_SPATIAL);
 void set_tuning_op(int op, const Tuning &t);
 // Node format the thread schedule of `op` walks on a tree (or forest) of
 // dimension `dim` over values of `kind`: the tuning's; under the library's
-// defaults 1 for the radius walks over points and for kNN over points in 6D,
-// and 0 for every other walk (kNN up to 3D, box values, forests).
+// defaults 1 over points and 0 for every other walk (box values, forests).
 int node_format(int op, int dim, int kind, bool forest);
 int node_format_of(const Tuning &t, int op, int dim, int kind, bool forest);
 // Quantized (1) and four-wide (2) nodes are built only while some operation

@@ -104,8 +104,19 @@ __global__ void k_pair_degree(const Node<D> *__restrict__ nodes, const QNode<D> 
             atomicAdd(deg + q, 1);
         };
         if constexpr (Q) {
-            auto f1 = [&](int q, int qid, float d) { f(0, q, qid, d); };
-            traverse_pairs_q<D>(qnodes, *hdr, (int)(n - 1), (int)p0, pred[0], st, f1);
+            if (hdr->qinv != 0.0) {
+                TopStack<int> ts(s_stack + threadIdx.x, blockDim.x, stack_cap, spill, -1);
+                auto f1 = [&](int at, bool h0, int i0, bool h1, int i1) {
+                    if (h0 || h1) {
+                        f(0, h0 ? at : at + 1, h0 ? i0 : i1, 0.0f);
+                        if (h0 && h1)
+                            f(0, at + 1, i1, 0.0f);
+                    }
+                };
+                traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+            } else {  // no common step of the frame: float nodes
+                traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
+            }
         } else {
             traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
         }
@@ -254,8 +265,19 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
         ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
         auto f = [&](int j, int q, int qid, float) { pair(j, q, qid); };
         if constexpr (Q) {
-            auto f1 = [&](int q, int qid, float) { pair(0, q, qid); };
-            traverse_pairs_q<D>(qnodes, *hdr, (int)(n - 1), (int)p0, pred[0], st, f1);
+            if (hdr->qinv != 0.0) {
+                TopStack<int> ts(s_stack + threadIdx.x, blockDim.x, stack_cap, spill, -1);
+                auto f1 = [&](int at, bool h0, int i0, bool h1, int i1) {
+                    if (h0 || h1) {
+                        f(0, h0 ? at : at + 1, h0 ? i0 : i1, 0.0f);
+                        if (h0 && h1)
+                            f(0, at + 1, i1, 0.0f);
+                    }
+                };
+                traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+            } else {  // no common step of the frame: float nodes
+                traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
+            }
         } else {
             traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
         }
@@ -323,7 +345,7 @@ PairLaunch pair_launch(const TreeDev &t)
     launch_shape(OP_REDUCE, dim, L.block, L.cap);
     while (L.cap > 1 && (size_t)L.cap * L.block * sizeof(int) > 65536)
         L.cap >>= 1;
-    L.lds = L.nq ? (size_t)L.cap * L.block * sizeof(int) : 0;
+    L.lds = L.nq ? (size_t)(L.cap > 2 ? L.cap : 2) * L.block * sizeof(int) : 0;  // a TopStack has at least two slots
     const int64_t per = L.nq ? L.nq : 1;
     L.grid = grid_for((n - 1 + per - 1) / per, L.block, INT32_MAX);
     return L;

@@ -28,6 +28,56 @@ namespace {
 // Node slots of a single tree (one-value trees still have one node).
 __device__ __forceinline__ int node_count(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
 
+// Walk of one query over a tree that holds quantized nodes: in codes for a
+// sphere over points whose frame has one step; for a frame without one
+// (quant_frame), over the float nodes, which the decoded boxes of such a frame
+// only approximate; other predicates and box values decode the boxes.
+template <int D, class P, class F, class S = NeverStop>
+__device__ __forceinline__ void walk_quantized(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
+                                               const TreeHeader &h, const float *__restrict__ leaves, int kind,
+                                               const P &pred, int *s_stack, int cap, int (&spill)[kSpill], F &f,
+                                               const S &stop = S())
+{
+    if constexpr (std::is_same<P, Sphere<D>>::value) {
+        if (kind != ARBORX_BOXES) {
+            if (h.qinv != 0.0) {
+                TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
+                auto g1 = [&](int, int idx, float d2) { f(idx, d2); };
+                auto g = each_hit(g1);
+                const P preds[1] = {pred};
+                traverse_codes<D, 1, false>(qnodes, h, node_count(&h), preds, -1, st, g, stop);
+            } else {
+                ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+                traverse_spatial<D>(nodes, h.root, node_count(&h), pred, st, f, stop);
+            }
+            return;
+        }
+    }
+    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+    traverse_spatial_q<D>(qnodes, h, node_count(&h), leaves, kind, pred, st, f, stop);
+}
+
+// The same for NQ neighbouring sphere queries of one thread.
+template <int D, int NQ, class F>
+__device__ __forceinline__ void walk_quantized_packet(const Node<D> *__restrict__ nodes,
+                                                      const QNode<D> *__restrict__ qnodes, const TreeHeader &h,
+                                                      const float *__restrict__ leaves, int kind,
+                                                      const Sphere<D> (&pred)[NQ], int *s_stack, int cap,
+                                                      int (&spill)[kSpill], F &f)
+{
+    if (kind != ARBORX_BOXES && h.qinv != 0.0) {
+        TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
+        auto g = each_hit(f);
+        traverse_codes<D, NQ, false>(qnodes, h, node_count(&h), pred, -1, st, g);
+        return;
+    }
+    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+    if (kind != ARBORX_BOXES)
+        traverse_spatial_packet<D, NQ>(nodes, h.root, node_count(&h), pred, st, f);
+    else
+        traverse_spatial_packet_q<D, NQ>(qnodes, h, node_count(&h), leaves, kind, pred, st, f);
+}
+
 // Match number c (c >= R, counted from 0) of query qi, past its stash row of
 // R: stored in the query's overflow chain, whose current chunk is `cur` (one
 // register per query; -2 once the row is given up).  Chunks come from the
@@ -76,6 +126,7 @@ template <bool OUT>
 struct StashGroup {
     int g[4];
     float dg[OUT ? 4 : 1];
+    __device__ __forceinline__ explicit StashGroup(int * = nullptr) {}
     __device__ __forceinline__ void add(int c, int idx, float d2, int32_t *row, float *drow)
     {
         const int k = c & 3;
@@ -96,6 +147,52 @@ struct StashGroup {
     {
         if (c < R && (c & 3) != 0)
             flush(c & ~3, row, drow);
+    }
+};
+
+// The row writer of the one-query walks over quantized nodes: matches gather
+// in a ring of eight LDS entries, [entry][thread] so that a wavefront's stores
+// spread over the banks, and go to the stash row when the ring is full, and at
+// the end.  A match costs one store where StashGroup selects among registers:
+// with some lane of a wavefront matching in nearly every step, that was half
+// of the count walk's vector instructions.  (16 entries, the whole 3D row,
+// measured the same.)
+constexpr int kRing = 8;
+template <int D, bool OUT>
+struct StashRing {
+    static constexpr int N = kRing;
+    int *ring;  // this thread's column
+    int stride;
+    __device__ __forceinline__ StashRing(int *lds) : ring(lds + threadIdx.x), stride(blockDim.x) {}
+    __device__ __forceinline__ void add(int c, int idx, float d2, int32_t *row, float *drow)
+    {
+        const int k = c & (N - 1);
+        ring[k * stride] = idx;
+        if constexpr (OUT)
+            ring[(N + k) * stride] = __float_as_int(d2);
+        if (k == N - 1)
+            flush(c - k, N, row, drow);
+    }
+    // the first n entries of the ring to the row from `base` on, in groups of four
+    __device__ __forceinline__ void flush(int base, int n, int32_t *row, float *drow) const
+    {
+#pragma unroll
+        for (int k = 0; k < N; k += 4)
+            if (k < n) {
+                *reinterpret_cast<int4 *>(row + base + k) = make_int4(ring[k * stride], ring[(k + 1) * stride],
+                                                                      ring[(k + 2) * stride], ring[(k + 3) * stride]);
+                if constexpr (OUT)
+                    *reinterpret_cast<int4 *>(drow + base + k) =
+                        make_int4(ring[(N + k) * stride], ring[(N + k + 1) * stride], ring[(N + k + 2) * stride],
+                                  ring[(N + k + 3) * stride]);
+            }
+    }
+    // after the walk, for a row of c matches with a stash row of R
+    __device__ __forceinline__ void finish(int c, int R, int32_t *row, float *drow) const
+    {
+        const int m = c < R ? c : R, done = m & ~(N - 1);
+        if (done < m)
+            flush(done, m - done, row, drow);
     }
 };
 
@@ -170,7 +267,8 @@ __global__ void k_spatial_count(const Node<D> *__restrict__ nodes, const QNode<D
     int *wstack = s_stack + wave_id() * kWaveStack;
     constexpr int R = stash_regs(D);
     int c = 0;
-    StashGroup<OUT> grp;
+    typename std::conditional<SCHED == 3, StashRing<D, OUT>, StashGroup<OUT>>::type grp(
+        s_stack + (stack_cap > 2 ? stack_cap : 2) * (int)blockDim.x);
     int32_t *row = STASH ? stash + qi * R : nullptr;
     float *drow = OUT ? stash_d2 + qi * R : nullptr;
     int32_t ov = -1;
@@ -188,7 +286,7 @@ __global__ void k_spatial_count(const Node<D> *__restrict__ nodes, const QNode<D
     else if (SCHED == 2)
         traverse_spatial_rope<D>(nodes, hdr->root, node_count(hdr), hdr->start + hdr->n - 1, pred, f);
     else if (SCHED == 3)
-        traverse_spatial_q<D>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (SCHED == 4)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -258,7 +356,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(NQ == 2 && D <= 3 && !OUT ? 6 : 1)
             }
     };
     if (Q)
-        traverse_spatial_packet_q<D, NQ>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f);
+        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
     else
         traverse_spatial_packet<D, NQ>(nodes, hdr->root, node_count(hdr), pred, st, f);
 #pragma unroll
@@ -431,7 +529,7 @@ __global__ void k_spatial_fill_rows(const Node<D> *__restrict__ nodes, const QNo
         ++k;
     };
     if (FMT == 1)
-        traverse_spatial_q<D>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (FMT == 2)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -648,7 +746,7 @@ __global__ void k_spatial_reduce(const Node<D> *__restrict__ nodes, const QNode<
     else if (SCHED == 2)
         traverse_spatial_rope<D>(nodes, hdr->root, node_count(hdr), hdr->start + hdr->n - 1, pred, f);
     else if (SCHED == 3)
-        traverse_spatial_q<D>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (SCHED == 4)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -705,7 +803,7 @@ __global__ void k_spatial_reduce_packet(const Node<D> *__restrict__ nodes, const
             }
     };
     if (Q)
-        traverse_spatial_packet_q<D, NQ>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f);
+        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
     else
         traverse_spatial_packet<D, NQ>(nodes, hdr->root, node_count(hdr), pred, st, f);
 #pragma unroll
@@ -723,7 +821,8 @@ __global__ void k_spatial_reduce_packet(const Node<D> *__restrict__ nodes, const
 // at 10^7 points took 7.7 ms instead of 8.4 (shell 6.8 instead of 7.4).  The
 // 6D k = 8 walk on quantized nodes, held from 88 to 80 registers (6 waves
 // instead of 5), spilled and ran slower (7.0 against 6.8 ms), so the other
-// shapes are left to the compiler.
+// shapes are left to the compiler; so is the 3D walk over codes, whose 68
+// registers held to 64 measured the same.
 template <int D, int K, bool WAVE, int FMT>
 constexpr int knn_waves()
 {
@@ -757,7 +856,12 @@ __global__ __attribute__((amdgpu_waves_per_eu(knn_waves<D, K, WAVE, FMT>()))) vo
     } else {
         KnnEntry spill[kSpill];
         ShortStack<KnnEntry> st(reinterpret_cast<KnnEntry *>(s_stack) + threadIdx.x, blockDim.x, stack_cap, spill);
-        if (FMT == 1)
+        if (FMT == 1 && kind != ARBORX_BOXES && hdr->qinv != 0.0) {
+            TopStack<KnnCode> ts(reinterpret_cast<KnnCode *>(s_stack) + threadIdx.x, blockDim.x, stack_cap,
+                                 reinterpret_cast<KnnCode *>(spill), knn_code(-1, 0u));
+            knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, *hdr, q, best, ts, seed,
+                                   SeedKeys{codes, 0, 63 / D});
+        } else if (FMT == 1 && kind == ARBORX_BOXES)
             knn_search_q<D, K>(qnodes, n_nodes, leaves, kind, *hdr, q, best, st, seed, SeedKeys{codes, 0, 63 / D});
         else if (FMT == 2)
             knn_search4<D, K>(nodes, wnodes, n_nodes, leaves, kind, *hdr, q, best, st, seed, SeedKeys{codes, 0, 63 / D});
@@ -826,7 +930,7 @@ __global__ void k_count_up_to(const Node<D> *__restrict__ nodes, const QNode<D> 
     auto stop = [&]() { return c >= n_max; };
     if (n_max > 0) {
         if constexpr (Q)
-            traverse_spatial_q<D>(qnodes, *hdr, node_count(hdr), leaves, kind, pred, st, f, stop);
+            walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f, stop);
         else
             traverse_spatial<D>(nodes, hdr->root, node_count(hdr), pred, st, f, stop);
     }
@@ -935,7 +1039,9 @@ Launch traversal_launch(int64_t m, size_t entry_bytes, int op, int dim, bool wav
     L.grid = (unsigned)((m + L.block - 1) / L.block);
     while (L.cap > 1 && (size_t)L.cap * L.block * entry_bytes > 65536)
         L.cap >>= 1;
-    L.lds = wave ? (size_t)(L.block / kWave) * kWaveStack * entry_bytes : (size_t)L.cap * L.block * entry_bytes;
+    // a TopStack has at least two slots
+    L.lds = wave ? (size_t)(L.block / kWave) * kWaveStack * entry_bytes
+                 : (size_t)(L.cap > 2 ? L.cap : 2) * L.block * entry_bytes;
     return L;
 }
 
@@ -989,7 +1095,9 @@ arborx_status count_impl(const TreeDev &t, Pred pred, const float *q, int64_t m,
         AX_HIP(hipGetLastError());
         return ARBORX_OK;
     }
-    const Launch L = traversal_launch(m, sizeof(int), OP_SPATIAL, D, sched == 1);
+    Launch L = traversal_launch(m, sizeof(int), OP_SPATIAL, D, sched == 1);
+    if (sched == 3)  // the rings of StashRing behind the stacks
+        L.lds += (size_t)L.block * kRing * (out ? 2 : 1) * sizeof(int);
     const Node<D> *nodes = static_cast<const Node<D> *>(t.nodes);
     const QNode<D> *qnodes = static_cast<const QNode<D> *>(t.qnodes);
     const Node4<D> *wnodes = static_cast<const Node4<D> *>(t.wnodes);

@@ -62,6 +62,51 @@ struct ShortStack {
     }
 };
 
+// The deferred subtrees of a walk over codes.  A step reads the top before it
+// knows whether it needs it, so that the read runs beside the node's fetch,
+// and writes the entry above the top without asking whether it counts; moving
+// `at` decides, with no branch.  at, lim and stride are LDS byte offsets in
+// this thread's column of `slots` (at least 2) entries, words of type E; slot 0 holds the entry
+// that ends the walk, the last one only what is written above a full stack.
+// A stack of slots - 2 entries is full: deeper ones go to a private array and
+// come back from it (the two branches below, taken only there).
+template <typename E>
+struct TopStack {
+    typedef __attribute__((address_space(3))) char *Lds;
+    Lds at;
+    Lds lim;
+    int stride;
+    E *spill;
+    int ns = 0;
+    __device__ __forceinline__ TopStack(E *col, int threads, int slots, E *spill_, E end)
+        : stride(threads * (int)sizeof(E)), spill(spill_)
+    {
+        at = (Lds)(__attribute__((address_space(3))) E *)col;
+        lim = at + (slots > 2 ? slots - 2 : 0) * stride;
+        *(__attribute__((address_space(3))) E *)at = end;
+    }
+    __device__ __forceinline__ E top() const { return *(__attribute__((address_space(3))) E *)at; }
+    __device__ __forceinline__ void put(E x) const { *(__attribute__((address_space(3))) E *)(at + stride) = x; }
+    // both: the entry put above the top stays; none: the top is taken
+    __device__ __forceinline__ void move(bool both, bool none, E x, E &taken)
+    {
+        int by = both ? stride : (none ? -stride : 0);
+        if (at == lim && (both || ns > 0)) {
+            if (both) {
+                if (ns < kSpill)  // always true (see kSpill); keeps the store in bounds
+                    spill[ns] = x;
+                ++ns;
+                by = 0;
+            } else if (none) {
+                --ns;
+                taken = spill[ns < kSpill ? ns : kSpill - 1];
+                by = 0;
+            }
+        }
+        at += by;
+    }
+};
+
 // Blocks are dealt round-robin over the 8 XCDs; renumber them so that each
 // XCD (and its L2) works on one contiguous run of Morton-ordered queries.
 __device__ __forceinline__ int64_t xcd_block()
@@ -122,6 +167,22 @@ struct BoxQuery {
         }
     }
 };
+
+// Squared distance from q to the point stored in a leaf child's words: box_d2
+// of the degenerate box, bit for bit.
+template <int D>
+__device__ __forceinline__ float point_d2(const float *q, const uint32_t (&w)[D])
+{
+#pragma clang fp contract(off)
+    float acc = 0.0f;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const float t = q[d] - __uint_as_float(w[d]);
+        const float s = t * t;
+        acc = acc + s;
+    }
+    return acc;
+}
 
 // A ray o + t*dir, t >= 0 (Section 2.5).  It meets a closed box when its slab
 // intervals overlap: slabs taken in dimension order from tmin = 0, tmax =
@@ -655,55 +716,94 @@ __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__rest
     }
 }
 
-// Pair walk over the quantized nodes of a tree of points, one leaf (sorted
-// position p) per thread: f(q, index, d2) for every later position q whose
-// point is in range.  A node is entered only when its leaf range holds a
-// position after p: the root unless p is the last leaf; a left child [l, c]
-// when c > p; a right child always, as its range ends where its parent's does.
-// So only the leaf children need a position test (the left leaf sits at c,
-// the right one at c + 1) and the node needs no stored range.
-template <int D, class P, class F>
-__device__ __forceinline__ void traverse_pairs_q(const QNode<D> *__restrict__ nodes, const TreeHeader &h,
-                                                 int n_nodes, int p, const P &pred, ShortStack<int> &st, F &f)
+// Depth-first walk of NQ neighbouring sphere queries over the quantized nodes
+// of a tree of points, in the codes of its frame: an internal child costs one
+// saturating pair subtraction and one dot product per dimension instead of
+// twelve instructions to decode and test it, a leaf child its exact distance
+// from the node's words; both are formed and one is taken.  The next node is
+// chosen and its fetch issued before the matches of this one are reported:
+// f(j, hit0, index0, d0, hit1, index1, d1) tells which of the node's leaf
+// children query j matches.  With PAIRS it is the pair walk of the leaf at
+// sorted position lpos: only later positions match, and f gets `at`, the
+// position of the left leaf (the right one is at + 1), first; node c
+// separates leaves c and c + 1, so a left child [l, c] is entered when c >
+// lpos and a right one always (its range ends where its parent's does).
+// Bound: two 16-byte loads a visit (four in 6D), which leave the compute unit
+// at about 1.3 lane-loads a clock, then vector instructions (busy 0.6 of the
+// time in the CSR count at 10^7 cube points).  Against the decoded boxes that
+// walk fell from 1.5e9 to 1.0e9 vector instructions and from 3.28 to 2.70 ms;
+// CSR with distances of 5*10^5 6D mixture points, build included, from 3.95
+// to 3.09 ms; DBSCAN of 5*10^6 points from 5.3 to 4.7 ms.
+template <int D, int NQ, bool PAIRS, class F, class S = NeverStop>
+__device__ __forceinline__ void traverse_codes(const QNode<D> *__restrict__ nodes, const TreeHeader &h, int n_nodes,
+                                               const Sphere<D> (&pred)[NQ], int lpos, TopStack<int> &st, F &f,
+                                               const S &stop = S())
 {
-    if (p >= h.start + h.n - 1)
-        return;
-    float flo[D], fsc[D];
+    CodeBall<D> ball[NQ];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        flo[d] = h.lo[d];
-        fsc[d] = h.qscale[d];
+    for (int j = 0; j < NQ; ++j) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            ball[j].q[d] = code_query(pred[j].c[d], h.lo[d], h.hi[d], h.qinv);
+        ball[j].r2 = code_radius2(pred[j].r2, h.qinv);
     }
+    const unsigned last = (unsigned)n_nodes - 1u;
     int cur = h.root;
+    QNode<D> nd;
+    load_qnode(nodes, (int)min((unsigned)cur, last), nd);
     for (int iter = 0; iter <= n_nodes; ++iter) {
-        if ((unsigned)cur >= (unsigned)n_nodes)
+        if ((unsigned)cur > last)
             break;
-        QNode<D> nd;
-        load_qnode(nodes, cur, nd);
-        float lo[2][D], hi[2][D];
-        qboxes<D>(nd, true, flo, fsc, lo, hi);
+        int deferred = st.top();
         const int c0 = nd.child[0], c1 = nd.child[1];
-        float d0, d1;
-        const bool h0 = cur > p && pred.hit(lo[0], hi[0], d0);
-        const bool h1 = (c1 >= 0 || cur + 1 > p) && pred.hit(lo[1], hi[1], d1);
-        if (h0 && c0 < 0 && c0 != kEmptyRef)
-            f(cur, ~c0, d0);
-        if (h1 && c1 < 0 && c1 != kEmptyRef)
-            f(cur + 1, ~c1, d1);
-        const bool g0 = h0 && c0 >= 0;
-        const bool g1 = h1 && c1 >= 0;
-        if (g0) {
-            if (g1)
-                st.push(c1);
-            cur = c0;
-        } else if (g1) {
-            cur = c1;
-        } else {
-            if (st.empty())
-                break;
-            cur = st.pop();
+        st.put(c1);
+        bool g0 = false, g1 = false, h0[NQ], h1[NQ];
+        float d0[NQ], d1[NQ];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            g0 = g0 | (code_gap2<D>(ball[j].q, nd.w[0]) <= ball[j].r2);
+            g1 = g1 | (code_gap2<D>(ball[j].q, nd.w[1]) <= ball[j].r2);
+            d0[j] = point_d2<D>(pred[j].c, nd.w[0]);
+            d1[j] = point_d2<D>(pred[j].c, nd.w[1]);
+            h0[j] = c0 < 0 && (!PAIRS || cur > lpos) && d0[j] <= pred[j].r2;
+            h1[j] = c1 < 0 && (!PAIRS || cur >= lpos) && d1[j] <= pred[j].r2;
+        }
+        g0 = g0 && c0 >= 0 && (!PAIRS || cur > lpos);
+        g1 = g1 && c1 >= 0;
+        const int at = cur;
+        st.move(g0 && g1, !(g0 || g1), c1, deferred);
+        cur = g0 ? c0 : (g1 ? c1 : deferred);
+        load_qnode(nodes, (int)min((unsigned)cur, last), nd);  // in flight while the matches below are reported
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            if constexpr (PAIRS)
+                f(at, h0[j], ~c0, h1[j], ~c1);
+            else
+                f(j, h0[j], ~c0, d0[j], h1[j], ~c1, d1[j]);
+        }
+        if (stop())
+            break;
+    }
+}
+
+// A reporter for traverse_codes from f(j, index, d2): one call for a node's
+// first match and a rarer one for a second, instead of one for each slot.
+template <class F>
+struct EachHit {
+    F &f;
+    __device__ __forceinline__ void operator()(int j, bool h0, int i0, float d0, bool h1, int i1, float d1) const
+    {
+        if (h0 || h1) {
+            f(j, h0 ? i0 : i1, h0 ? d0 : d1);
+            if (h0 && h1)
+                f(j, i1, d1);
         }
     }
+};
+template <class F>
+__device__ __forceinline__ EachHit<F> each_hit(F &f)
+{
+    return EachHit<F>{f};
 }
 
 // One term of the fixed-point distance sum: trunc(sqrtf(d2) * scale), scale
@@ -749,6 +849,11 @@ struct KnnEntry {
     int32_t ref;
     float d2;
 };
+// A deferred subtree of a kNN walk over codes: its squared gap above its
+// reference, one word of a TopStack.
+typedef uint64_t KnnCode;
+static_assert(sizeof(KnnCode) == sizeof(KnnEntry), "the two share a stack area");
+__device__ __forceinline__ KnnCode knn_code(int32_t ref, uint32_t gap2) { return ((uint64_t)gap2 << 32) | (uint32_t)ref; }
 
 // Minimum and maximum of two top-k keys held as doubles.  The bit pattern of
 // a float32 distance >= 0 (up to +inf, and NaN) in the high word makes a
@@ -798,9 +903,9 @@ struct TopK {
     // slots are done in groups of eight from the back, until no lane goes on.
     // (Against 64-bit compares and selects slot by slot: 1000 queries of k = 10
     // in 2*10^4 points 111 -> 77 us, k = 16 at 10^7 points 8.6 -> 8.0 ms.)
-    __device__ __forceinline__ void offer(float d, int id)
+    __device__ __forceinline__ void offer(float d, int id) { offer_key(pack(d, id)); }
+    __device__ __forceinline__ void offer_key(double v)
     {
-        const double v = pack(d, id);
         if (!(v < key[K - 1]))
             return;
 #pragma unroll
@@ -1255,6 +1360,70 @@ __device__ __forceinline__ void knn_search_wave(const Node<D> *__restrict__ node
             if (cur < 0)
                 break;
         }
+    }
+}
+
+// kNN over the quantized nodes of a tree of points in the codes of its frame
+// (see traverse_codes): as knn_search, seeded and software-pipelined, with
+// internal children ordered and pruned by their squared code gaps against the
+// bound in codes, and leaf children offered with their exact distances.  The
+// bound in codes is rounded up in float32: k and a hold 1/s^2 with the margins
+// of code_radius2 and more.  Half the loads of the float nodes and no decoding:
+// k = 16 at 10^7 cube points 7.3 -> 6.0 ms, and k = 8 over 2*10^6 6D mixture
+// points, against decoded boxes, 7.1 -> 5.9 ms.  (Gathering admitted leaves in
+// LDS and merging eight at a time with a sorting network took 13 % fewer
+// vector instructions at k = 16, none fewer at k = 8, and 6.5 and 6.7 ms: the
+// bound lags and the queue takes LDS.)
+template <int D, int K>
+__device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ nodes, int n_nodes,
+                                                 const float *__restrict__ leaves, int kind, const TreeHeader &hdr,
+                                                 const float (&q)[D], TopK<K> &best, TopStack<KnnCode> &st,
+                                                 int seed, const SeedKeys &keys)
+{
+    best.reset(INFINITY);
+    if (hdr.n <= 0)
+        return;
+    if (seed != 1 && hdr.n >= K)
+        seed_window<D, K>(leaves, kind, hdr, leaf_position<D>(keys, hdr, q), q, best, seed);
+    uint32_t qc[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv);
+    const float k = (float)fmin(hdr.qinv * hdr.qinv * (1.0 + 0x1p-16), 3.0e38);
+    const float a = (float)fmin(hdr.qinv * hdr.qinv * 0x1p-144 + 2.0, 3.0e38);
+    const unsigned last = (unsigned)n_nodes - 1u;
+    int cur = hdr.root;
+    QNode<D> nd;
+    load_qnode(nodes, (int)min((unsigned)cur, last), nd);
+    for (int iter = 0; iter <= n_nodes; ++iter) {
+        if ((unsigned)cur > last)
+            break;
+        KnnCode deferred = st.top();
+        const int c0 = nd.child[0], c1 = nd.child[1];
+        const uint32_t s0 = code_gap2<D>(qc, nd.w[0]), s1 = code_gap2<D>(qc, nd.w[1]);
+        // leaf children as keys, the other slots above every key
+        const double none = TopK<K>::pack(__uint_as_float(0x7fc00000u), INT32_MAX);
+        const double v0 = c0 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[0]), ~c0) : none;
+        const double v1 = c1 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[1]), ~c1) : none;
+        const float fb = fmaf(best.bound(), k, a);
+        const uint32_t bound = fb < 4.29e9f ? (uint32_t)fb : UINT32_MAX;
+        const bool k0 = c0 >= 0 && s0 <= bound;
+        const bool k1 = c1 >= 0 && s1 <= bound;
+        const bool near1 = k1 && (!k0 || s1 < s0);
+        const KnnCode far = near1 ? knn_code(c0, s0) : knn_code(c1, s1);
+        st.put(far);
+        st.move(k0 && k1, !(k0 || k1), far, deferred);
+        cur = near1 ? c1 : c0;
+        if (!(k0 || k1)) {
+            while ((uint32_t)(deferred >> 32) > bound) {  // the last entry is below every bound
+                deferred = st.top();
+                st.move(false, true, deferred, deferred);
+            }
+            cur = (int)(uint32_t)deferred;
+        }
+        load_qnode(nodes, (int)min((unsigned)cur, last), nd);  // in flight during the insertions below
+        best.offer_key(key_min(v0, v1));
+        best.offer_key(key_max(v0, v1));
     }
 }
 
