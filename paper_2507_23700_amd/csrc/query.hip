@@ -983,7 +983,7 @@ __global__ void k_knn_empty(int64_t total, float *d2, int32_t *idx)
     }
 }
 
-// Morton codes of query centres on a coarse grid (order_bits bits in all:
+// Hilbert codes of query centres on a coarse grid (order_bits bits in all:
 // 24, or 16 for a two-pass sort), normalised by the tree's bounds.  The order
 // only affects speed: queries in one cell of the grid are treated alike.
 inline int order_bits(int order) { return order == 2 ? 16 : 24; }
@@ -1010,6 +1010,7 @@ __global__ void k_query_codes(const float *__restrict__ q, int64_t m, const Tree
                                         : q[i * D + d]);
             c[d] = quantise(x, lo[d], inv[d], bits);
         }
+        hilbert_transpose<D>(c, bits);
         codes[i] = (uint32_t)interleave<D>(c, bits);
         ids[i] = (uint32_t)i;
     }
