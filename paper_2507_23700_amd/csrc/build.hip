@@ -835,10 +835,11 @@ arborx_status build_impl(const float *values, int64_t n, int kind, TreeDev &t, h
         return st;
     codes = t.codes;
     if ((st = tmp.get(&partial, (size_t)pblocks * 2 * D)) != ARBORX_OK ||
-        (st = tmp.get(&codes2, n)) != ARBORX_OK || (st = tmp.get(&ids, n)) != ARBORX_OK ||
-        (st = tmp.get(&ids2, n)) != ARBORX_OK || (st = tmp.get(&flags, nn)) != ARBORX_OK ||
-        (st = tmp.get(&ws, radix_workspace_bytes(n))) != ARBORX_OK)
+        (st = tmp.get(&ids, n)) != ARBORX_OK || (st = tmp.get(&ids2, n)) != ARBORX_OK ||
+        (st = tmp.get(&flags, nn)) != ARBORX_OK || (st = tmp.get(&ws, radix_workspace_bytes(n))) != ARBORX_OK ||
+        (st = dalloc((void **)&codes2, (size_t)n * sizeof(uint64_t), s)) != ARBORX_OK)
         return st;
+    tmp.adopt(codes2);
 
     {
         ProfScope ps("build_bounds", s);
@@ -857,8 +858,10 @@ arborx_status build_impl(const float *values, int64_t n, int kind, TreeDev &t, h
         ProfScope ps("build_sort", s);
         AX_HIP(radix_sort_pairs<uint64_t>(codes, ids, codes2, ids2, n, 0, (63 / D) * D, ws, s, &alt));
     }
-    if (alt) {  // an odd number of passes (none for the dimensions compiled in): keep the result in t.codes
-        AX_HIP(hipMemcpyAsync(t.codes, codes2, (size_t)n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
+    if (alt) {  // the tree keeps whichever buffer holds the result
+        tmp.exchange(codes2, t.codes);
+        t.codes = codes2;
+        codes = codes2;
         ids = ids2;
     }
     Node<D> *nodes = static_cast<Node<D> *>(t.nodes);

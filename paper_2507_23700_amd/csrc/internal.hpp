@@ -129,6 +129,15 @@ struct Temps {
         *p = static_cast<T *>(q);
         return ARBORX_OK;
     }
+    // Take over a block from dalloc (there is room: callers hold few).
+    void adopt(void *q) { ptrs[n++] = q; }
+    // Free `b` at the end instead of `a`.
+    void exchange(void *a, void *b)
+    {
+        for (int i = 0; i < n; ++i)
+            if (ptrs[i] == a)
+                ptrs[i] = b;
+    }
 };
 
 inline unsigned grid_for(int64_t n, int block, int64_t cap = 1 << 20)

@@ -1010,8 +1010,7 @@ __global__ void k_query_codes(const float *__restrict__ q, int64_t m, const Tree
                                         : q[i * D + d]);
             c[d] = quantise(x, lo[d], inv[d], bits);
         }
-        hilbert_transpose<D>(c, bits);
-        codes[i] = (uint32_t)interleave<D>(c, bits);
+        codes[i] = bits == 24 / D ? hilbert_code<D>(c, 24 / D) : hilbert_code<D>(c, bits);  // the first unrolled
         ids[i] = (uint32_t)i;
     }
 }
