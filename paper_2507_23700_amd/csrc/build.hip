@@ -71,37 +71,37 @@ __device__ void quant_frame(const float *lo, const float *hi, float *qscale, dou
     }
 }
 
-// Largest code whose decoded value is <= x, and smallest whose decoded value
-// is >= x.  The estimate from the reciprocal step `inv` is corrected both ways
-// against the decode itself, so the result does not depend on its rounding.
-__device__ __forceinline__ uint32_t qcode_down(float x, float lo, float scale, float inv)
-{
-    if (!(scale > 0.0f) || !(x > lo))
-        return 0u;
-    const float u = floorf((x - lo) * inv);
-    uint32_t c = u >= (float)kQMax ? (uint32_t)kQMax : (u > 0.0f ? (uint32_t)u : 0u);
-    while (c > 0 && qdecode(c, lo, scale) > x)
-        --c;
-    while (c < (uint32_t)kQMax && qdecode(c + 1, lo, scale) <= x)
-        ++c;
-    return c;
-}
+// One dimension of a frame: codes rounded outward, so that the decoded box
+// contains the true one.  Decoding is off by half an ulp of a coordinate at
+// most; `slop` is that in codes, and a hair for the arithmetic here.
+struct CodeAxis {
+    double lo, inv, slop;
+    __device__ __forceinline__ void set(float l, float h, float scale)
+    {
+        lo = l;
+        inv = scale > 0.0f ? 1.0 / (double)scale : 0.0;
+        slop = (fmax(fabs((double)l), fabs((double)h)) * 0x1.01p-24 + 0x1p-149) * inv + 0x1p-10;
+    }
+    __device__ __forceinline__ uint32_t down(float x) const
+    {
+        return (uint32_t)fmin(fmax(((double)x - lo) * inv - slop, 0.0), (double)kQMax);
+    }
+    __device__ __forceinline__ uint32_t up(float x) const
+    {
+        return (double)x > lo ? (uint32_t)fmin(ceil(((double)x - lo) * inv + slop), (double)kQMax) : 0u;
+    }
+};
 
-__device__ __forceinline__ uint32_t qcode_up(float x, float lo, float scale, float inv)
-{
-    if (!(scale > 0.0f))
-        return 0u;
-    if (!(x > lo))
-        return 0u;
-    const float u = ceilf((x - lo) * inv);
-    uint32_t c = u >= (float)kQMax ? (uint32_t)kQMax : (u > 0.0f ? (uint32_t)u : 0u);
-    while (c < (uint32_t)kQMax && qdecode(c, lo, scale) < x)
-        ++c;
-    while (c > 0 && qdecode(c - 1, lo, scale) >= x)
-        --c;
-    return c;
-}
-
+template <int D>
+struct CodeFrame {
+    CodeAxis axis[D];
+    __device__ __forceinline__ explicit CodeFrame(const TreeHeader &h)
+    {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            axis[d].set(h.lo[d], h.hi[d], h.qscale[d]);
+    }
+};
 
 template <int D>
 __global__ __launch_bounds__(kBuildBlock) void bounds_partial(const float *__restrict__ values, int64_t n, int kind,
@@ -357,9 +357,8 @@ __global__ __launch_bounds__(kBuildBlock) void hierarchy_kernel(const uint64_t *
 // climb that reaches split cs-1 or ce-1 (the chunk's borders) stops and is
 // recorded as one of at most two escapes of the chunk.
 // Phase 2: one thread per escape continues the climb over the splits whose
-// subtrees span chunks, handing off through global memory with device-scope
-// acquire/release.  Only these few percent of nodes pay for device-wide
-// coherence.
+// subtrees span chunks, handing off through global memory; one workgroup takes
+// the escapes of 512 neighbouring chunks, and another what leaves those.
 // ---------------------------------------------------------------------------
 
 template <int D>
@@ -368,11 +367,26 @@ struct Escape {
     float lo[D], hi[D];
 };
 
-constexpr unsigned long long kDone = ~0ull;
+constexpr unsigned long long kDone = 1ull << 63;  // above an arrival word; with the node's local leaf range
 
 __device__ __forceinline__ unsigned long long arrival_word(int side, int h, int bound)
 {
     return ((unsigned long long)side << 48) | ((unsigned long long)(uint32_t)(h + 1) << 32) | (uint32_t)bound;
+}
+
+// While a child waits in a node, the node's range words hold the split key at
+// the child's outer bound (none, all ones, at an end of the tree): the climb
+// that meets it needs that key next.
+template <int D>
+__device__ __forceinline__ void put_wait_key(Node<D> &nd, uint64_t key)
+{
+    nd.range_l = (int32_t)(uint32_t)key;
+    nd.range_r = (int32_t)(uint32_t)(key >> 32);
+}
+template <int D>
+__device__ __forceinline__ uint64_t wait_key(const Node<D> &nd)
+{
+    return ((uint64_t)(uint32_t)nd.range_r << 32) | (uint32_t)nd.range_l;
 }
 
 template <int D>
@@ -403,14 +417,14 @@ __device__ __forceinline__ void load_value_box(const float *values, int kind, ui
     }
 }
 
-// Quantized form of float node p of a tree with header h.  A point tree's
+// Quantized form of float node p of a tree with the given frame.  A point tree's
 // leaf child keeps its point and reference unchanged (the point's float words
 // fill that child's code bytes); a box tree's leaf child becomes its sorted
 // leaf position: the left child of node p is leaf p, the right child leaf
 // p + 1.
 template <int D>
 __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const Node<D> &nd, int p, int kind,
-                                            const TreeHeader &h)
+                                            const CodeFrame<D> &frame)
 {
     QNode<D> qn;
 #pragma unroll
@@ -435,9 +449,8 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const float inv = h.qscale[d] > 0.0f ? 1.0f / h.qscale[d] : 0.0f;
-            qn.w[c][d] = qcode_down(nd.lo[c][d], h.lo[d], h.qscale[d], inv) |
-                         (((uint32_t)kQMax - qcode_up(nd.hi[c][d], h.lo[d], h.qscale[d], inv)) << 16);
+            const CodeAxis &a = frame.axis[d];
+            qn.w[c][d] = a.down(nd.lo[c][d]) | (((uint32_t)kQMax - a.up(nd.hi[c][d])) << 16);
         }
         qn.child[c] = ref >= 0 ? ref : ~(p + c);
     }
@@ -449,8 +462,8 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
 }
 
 template <int D>
-__device__ void write_single_leaf_tree(Node<D> *node, TreeHeader *hdr, const float *lo, const float *hi, int32_t ref,
-                                       int index)
+__device__ void write_single_leaf_tree(Node<D> *node, QNode<D> *qnode, int kind, TreeHeader *hdr, const float *lo,
+                                       const float *hi, int32_t ref, int index)
 {
     Node<D> nd;
 #pragma unroll
@@ -465,10 +478,18 @@ __device__ void write_single_leaf_tree(Node<D> *node, TreeHeader *hdr, const flo
     nd.range_l = index;
     nd.range_r = index;
     store_node(node, nd);
+    if (qnode)
+        store_qnode<D>(qnode, nd, index, kind, CodeFrame<D>(*hdr));
     hdr->root = index;
     hdr->height = 1;
 }
 
+// Chunks whose border climbs one workgroup of the second phase takes, one
+// thread for each of their two escapes.  Small groups: a compute unit serves
+// about one lane's load a clock, and a workgroup of 1024 climbs waited on that
+// (137 us for the one group of 10^6 points, against 2 launches of 25).
+constexpr int kGroupChunks = 128;
+constexpr int kTopBlock = 2 * kGroupChunks;
 template <int D> constexpr int chunk_leaves() { return D <= 3 ? 1024 : 512; }
 
 // Tree (segment) holding sorted leaf i: seg[s] <= i < seg[s+1].  Without
@@ -496,10 +517,10 @@ __device__ __forceinline__ void segment_of(int i, const int64_t *__restrict__ se
     te = (int)seg[lo + 1] - 1;
 }
 
-// Float nodes -> quantized nodes, a pass over the finished tree (a pass of
-// its own measured faster than writing both forms during the climb, whose
-// levels run one after another).  Node p belongs to the tree holding sorted
-// leaf p (a one-value tree's node sits at its own leaf position).
+// Float nodes -> quantized nodes, a pass over the finished tree, for the
+// single-pass climb (the chunked one writes both forms itself).  Node p
+// belongs to the tree holding sorted leaf p (a one-value tree's node sits at
+// its own leaf position).
 template <int D>
 __global__ void quantize_nodes(const Node<D> *__restrict__ nodes, int n_nodes, const int64_t *__restrict__ seg,
                                int nseg, int n, int kind, const TreeHeader *__restrict__ hdrs,
@@ -512,7 +533,7 @@ __global__ void quantize_nodes(const Node<D> *__restrict__ nodes, int n_nodes, c
     segment_of(p < n ? p : n - 1, seg, nseg, n, sg, ts, te);
     Node<D> nd;
     load_node(nodes, p, nd);
-    store_qnode<D>(qnodes + p, nd, p, kind, hdrs[sg]);
+    store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]));
 }
 
 
@@ -579,6 +600,7 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
                                                                       const uint32_t *__restrict__ ids,
                                                                       const float *__restrict__ values, int kind,
                                                                       int n, Node<D> *__restrict__ nodes,
+                                                                      QNode<D> *__restrict__ qnodes,
                                                                       float *__restrict__ leaves,
                                                                       unsigned long long *__restrict__ gflags,
                                                                       Escape<D> *__restrict__ escapes,
@@ -601,8 +623,6 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
         const int g = cs - 1 + j;
         s_key[j] = (g >= 0 && g <= ce - 1 && g <= n - 2) ? split_key(codes, g) : 0ull;
     }
-    for (int j = cs + tid; j < ce && j <= n - 2; j += C)
-        gflags[j] = 0;
     if (tid < 2)
         escapes[2 * blockIdx.x + tid].valid = 0;
     __syncthreads();
@@ -618,7 +638,7 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
         int sg, ts, te;
         segment_of(i, seg, nseg, n, sg, ts, te);
         if (ts == te) {  // a one-value tree: its node slot is the unused split at its end
-            write_single_leaf_tree<D>(nodes + ts, hdrs + sg, lo, hi, ref, ts);
+            write_single_leaf_tree<D>(nodes + ts, qnodes ? qnodes + ts : nullptr, kind, hdrs + sg, lo, hi, ref, ts);
             continue;
         }
         int l = i, r = i, h = 0;
@@ -661,29 +681,17 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
             const int os = 1 - side;
             const int oh = (int)((other >> 32) & 0xffff) - 1;
             const int ob = (int)(uint32_t)other;
-            Node<D> nd;
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                const float slo = s_lo[lp][os][d], shi = s_hi[lp][os][d];
-                nd.lo[0][d] = side == 0 ? lo[d] : slo;
-                nd.hi[0][d] = side == 0 ? hi[d] : shi;
-                nd.lo[1][d] = side == 0 ? slo : lo[d];
-                nd.hi[1][d] = side == 0 ? shi : hi[d];
-                lo[d] = fminf(lo[d], slo);
-                hi[d] = fmaxf(hi[d], shi);
+                lo[d] = fminf(lo[d], s_lo[lp][os][d]);
+                hi[d] = fmaxf(hi[d], s_hi[lp][os][d]);
             }
-            const int32_t sref = s_ref[lp][os];
-            nd.child[0] = side == 0 ? ref : sref;
-            nd.child[1] = side == 0 ? sref : ref;
             if (side == 0)
                 r = ob;
             else
                 l = ob;
             h = (h > oh ? h : oh) + 1;
-            nd.range_l = l;
-            nd.range_r = r;
-            store_node(nodes + p, nd);
-            s_flag[lp] = kDone;
+            s_flag[lp] = kDone | ((unsigned long long)(l - cs) << 16) | (unsigned long long)(r - cs);
             ref = p;
             if (l == ts && r == te) {
                 hdrs[sg].root = p;
@@ -693,90 +701,270 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
         }
     }
     __syncthreads();
-    // splits with a single arrival: publish that child's slot for phase 2
-    for (int lp = tid; lp <= ce - 2 - cs; lp += C) {
-        const unsigned long long w = s_flag[lp];
-        if (w != 0 && w != kDone) {
+    // Bound: memory (a 128-byte line for each 12-byte point, and the nodes, about 2.9 GB at 10^7 points, in 0.69 ms,
+    // where this kernel and the pass that read its nodes back took 0.66 + 0.27 ms).
+    // Both child slots of every finished split are in LDS: its nodes are written here, in order, in both forms
+    // (stores inside the climb lengthened its chain of levels, and a later pass for the quantized form read every
+    // node back).  Of a split with a single arrival, that child's slot is published for the second phase.
+    for (int lp = tid; lp <= ce - 1 - cs; lp += C) {
+        const int p = cs + lp;
+        if (p > n - 2)
+            break;
+        const unsigned long long w = lp < ce - 1 - cs ? s_flag[lp] : 0;
+        if (w & kDone) {
+            Node<D> nd;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    nd.lo[c][d] = s_lo[lp][c][d];
+                    nd.hi[c][d] = s_hi[lp][c][d];
+                }
+                nd.child[c] = s_ref[lp][c];
+            }
+            nd.range_l = cs + (int)((w >> 16) & 0xffff);
+            nd.range_r = cs + (int)(w & 0xffff);
+            store_node(nodes + p, nd);
+            if (qnodes) {
+                int sg, ts, te;
+                segment_of(p, seg, nseg, n, sg, ts, te);
+                store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]));
+            }
+            continue;
+        }
+        gflags[p] = w;
+        if (w != 0) {
             const int side = (int)(w >> 48);
-            Node<D> *np = nodes + cs + lp;
+            Node<D> *np = nodes + p;
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 np->lo[side][d] = s_lo[lp][side][d];
                 np->hi[side][d] = s_hi[lp][side][d];
             }
             np->child[side] = s_ref[lp][side];
-            gflags[cs + lp] = w;
+            const int bound = (int)(uint32_t)w;  // l of a left child, r of a right one
+            int sg, ts, te;
+            segment_of(p, seg, nseg, n, sg, ts, te);
+            put_wait_key(*np, side == 0 ? (bound == ts ? ~0ull : s_key[bound - cs]) :
+                                          (bound == te ? ~0ull : s_key[bound - cs + 1]));
         }
     }
 }
 
+// One level of the second phase: workgroup g continues the climbs of its
+// escapes, two for each of kGroupChunks parts of the level below, over the
+// splits inside its leaves [g * span, (g + 1) * span), and records those that
+// leave them (at most two) as escapes of its own (out; NULL for the last
+// level).
+//
+// A climb is a chain of dependent steps, so its latency is all that counts.
+// A split's other child either waits in the node, left there by an earlier
+// phase (its arrival word in gflags), or comes from another climb of this
+// workgroup.  Those two meet in LDS: the first enters its number under the
+// split in a hash table and stops, the second finds it there and takes its
+// box.  No store of a climb is waited for, and none is read back before the
+// kernel ends; what is still waiting then is written for the next level.
+// (Arrivals exchanged in global memory, with the fences that needs across the
+// XCDs' L2 caches, took 252 us at 10^7 points, 52 at 10^6, 27 at 2*10^4; this
+// takes 100, 53 and 21, the quantized nodes of the second phase included.)
 template <int D>
-__global__ __launch_bounds__(kBuildBlock) void hierarchy_top_kernel(const uint64_t *__restrict__ codes, int n,
-                                                                    Node<D> *nodes, unsigned long long *gflags,
-                                                                    const Escape<D> *__restrict__ escapes,
-                                                                    int n_escapes, const int64_t *__restrict__ seg,
-                                                                    int nseg, TreeHeader *hdrs)
+__global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t *__restrict__ codes, int n, int kind,
+                                                                  Node<D> *__restrict__ nodes,
+                                                                  QNode<D> *__restrict__ qnodes,
+                                                                  unsigned long long *__restrict__ gflags,
+                                                                  const Escape<D> *__restrict__ escapes,
+                                                                  int n_escapes, int64_t span,
+                                                                  Escape<D> *__restrict__ out,
+                                                                  const int64_t *__restrict__ seg, int nseg,
+                                                                  TreeHeader *__restrict__ hdrs)
 {
-    const int e_i = blockIdx.x * kBuildBlock + threadIdx.x;
-    if (e_i >= n_escapes)
-        return;
-    const Escape<D> &e = escapes[e_i];
-    if (!e.valid)
-        return;
-    float lo[D], hi[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        lo[d] = e.lo[d];
-        hi[d] = e.hi[d];
-    }
-    int p = e.p, side = e.side, l = e.l, r = e.r, h = e.h;
-    int32_t ref = e.ref;
-    int sg, ts, te;
-    segment_of(l, seg, nseg, n, sg, ts, te);
-    // a climb visits at most n-1 splits
-    for (int guard = 0; guard < n; ++guard) {
-        if (p < 0 || p > n - 2)
-            return;
-        Node<D> *np = nodes + p;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            np->lo[side][d] = lo[d];
-            np->hi[side][d] = hi[d];
-        }
-        np->child[side] = ref;
-        const unsigned long long other = __hip_atomic_exchange(
-            gflags + p, arrival_word(side, h, side == 0 ? l : r), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (other == 0)
-            return;
-        const int oh = (int)((other >> 32) & 0xffff) - 1;
-        const int ob = (int)(uint32_t)other;
-        if (side == 0)
-            r = ob;
-        else
-            l = ob;
-        h = (h > oh ? h : oh) + 1;
-        const int os = 1 - side;
+    constexpr int E = kTopBlock;                      // escapes of a workgroup
+    constexpr int kTableBits = 9, kTable = 1 << kTableBits;
+    static_assert(kTable >= 2 * E, "a climb enters the table once");
+    __shared__ unsigned long long s_table[kTable];    // (split + 1) << 32 | climb; 0: free
+    __shared__ float s_lo[D][E], s_hi[D][E];
+    __shared__ int32_t s_ref[E];
+    __shared__ unsigned long long s_word[E];          // arrival word of a climb that waits; 0: none, or met
+    __shared__ uint64_t s_key[E];                     // split key at its outer bound
+    __shared__ int32_t s_at[E];                       // the split it waits at
+
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kTable; i += kTopBlock)
+        s_table[i] = 0;
+    s_word[tid] = 0;
+    if (out && tid < 2)
+        out[2 * blockIdx.x + tid].valid = 0;
+    __syncthreads();
+
+    const int64_t cs = (int64_t)blockIdx.x * span, ce = cs + span < n ? cs + span : n;
+    const int64_t e_i = (int64_t)blockIdx.x * E + tid;
+    if (e_i < n_escapes && escapes[e_i].valid) {  // climbs never wait for one another
+        const Escape<D> &e = escapes[e_i];
+        float lo[D], hi[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            lo[d] = fminf(lo[d], np->lo[os][d]);
-            hi[d] = fmaxf(hi[d], np->hi[os][d]);
+            lo[d] = e.lo[d];
+            hi[d] = e.hi[d];
         }
-        np->range_l = l;
-        np->range_r = r;
-        ref = p;
-        if (l == ts && r == te) {
-            hdrs[sg].root = p;
-            hdrs[sg].height = h;
-            return;
-        }
-        if (l == ts || (r != te && split_key(codes, r) < split_key(codes, l - 1))) {
-            p = r;
-            side = 0;
-        } else {
-            p = l - 1;
-            side = 1;
+        int p = e.p, side = e.side, l = e.l, r = e.r, h = e.h;
+        int32_t ref = e.ref;
+        int sg, ts, te;
+        segment_of(l, seg, nseg, n, sg, ts, te);
+        const CodeFrame<D> frame(hdrs[sg]);
+        // split keys at the subtree's two ends (none at an end of the tree)
+        uint64_t kl = l == ts ? ~0ull : split_key(codes, l - 1), kr = r == te ? ~0ull : split_key(codes, r);
+        // a climb visits at most n-1 splits
+        for (int guard = 0; guard < n; ++guard) {
+            if (p < 0 || p > n - 2)
+                break;
+            if (out && (p < cs || p > ce - 2)) {
+                Escape<D> &o = out[2 * blockIdx.x + (p >= cs ? 1 : 0)];
+                o.p = p;
+                o.side = side;
+                o.l = l;
+                o.r = r;
+                o.h = h;
+                o.ref = ref;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    o.lo[d] = lo[d];
+                    o.hi[d] = hi[d];
+                }
+                o.valid = 1;
+                break;
+            }
+            Node<D> *np = nodes + p;
+            unsigned long long other = gflags[p];
+            Node<D> nd;  // the waiting child's words, if there is one
+            load_node(nodes, p, nd);
+            float slo[D], shi[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                slo[d] = side ? nd.lo[0][d] : nd.lo[1][d];
+                shi[d] = side ? nd.hi[0][d] : nd.hi[1][d];
+            }
+            int32_t sref = side ? nd.child[0] : nd.child[1];
+            uint64_t okey = wait_key(nd);
+            if (other == 0) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    s_lo[d][tid] = lo[d];
+                    s_hi[d][tid] = hi[d];
+                }
+                s_ref[tid] = ref;
+                s_word[tid] = arrival_word(side, h, side == 0 ? l : r);
+                s_at[tid] = p;
+                s_key[tid] = side == 0 ? kl : kr;  // at its outer bound
+                const unsigned long long mine = ((unsigned long long)(uint32_t)(p + 1) << 32) | (uint32_t)tid;
+                uint32_t at = ((uint32_t)p * 2654435761u) >> (32 - kTableBits);  // borders differ in high bits only
+                int sib = -1;
+                for (int probe = 0; probe < kTable; ++probe) {  // at most E entries: a free one is found
+                    unsigned long long seen = 0;
+                    if (__hip_atomic_compare_exchange_strong(&s_table[at], &seen, mine, __ATOMIC_ACQ_REL,
+                                                             __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))
+                        break;
+                    if ((uint32_t)(seen >> 32) == (uint32_t)(p + 1)) {
+                        sib = (int)(uint32_t)seen;
+                        break;
+                    }
+                    at = (at + 1) & (kTable - 1);
+                }
+                if (sib < 0)  // first of the two
+                    break;
+                s_word[tid] = 0;
+                other = s_word[sib];
+                s_word[sib] = 0;
+                okey = s_key[sib];
+                sref = s_ref[sib];
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    slo[d] = s_lo[d][sib];
+                    shi[d] = s_hi[d][sib];
+                }
+            }
+            const int oh = (int)((other >> 32) & 0xffff) - 1;
+            const int ob = (int)(uint32_t)other;
+            if (side == 0)
+                r = ob;
+            else
+                l = ob;
+            h = (h > oh ? h : oh) + 1;
+            if (side == 0)
+                kr = okey;
+            else
+                kl = okey;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                nd.lo[0][d] = side == 0 ? lo[d] : slo[d];
+                nd.hi[0][d] = side == 0 ? hi[d] : shi[d];
+                nd.lo[1][d] = side == 0 ? slo[d] : lo[d];
+                nd.hi[1][d] = side == 0 ? shi[d] : hi[d];
+                lo[d] = fminf(lo[d], slo[d]);
+                hi[d] = fmaxf(hi[d], shi[d]);
+            }
+            nd.child[0] = side == 0 ? ref : sref;
+            nd.child[1] = side == 0 ? sref : ref;
+            nd.range_l = l;
+            nd.range_r = r;
+            store_node(np, nd);
+            if (qnodes)
+                store_qnode<D>(qnodes + p, nd, p, kind, frame);
+            ref = p;
+            if (l == ts && r == te) {
+                hdrs[sg].root = p;
+                hdrs[sg].height = h;
+                break;
+            }
+            if (l == ts || (r != te && kr < kl)) {
+                p = r;
+                side = 0;
+            } else {
+                p = l - 1;
+                side = 1;
+            }
         }
     }
+    __syncthreads();
+    const unsigned long long w = s_word[tid];
+    if (w != 0) {
+        const int side = (int)(w >> 48);
+        Node<D> *np = nodes + s_at[tid];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            np->lo[side][d] = s_lo[d][tid];
+            np->hi[side][d] = s_hi[d][tid];
+        }
+        np->child[side] = s_ref[tid];
+        put_wait_key(*np, s_key[tid]);
+        gflags[s_at[tid]] = w;
+    }
+}
+
+// The second phase over all chunks: levels of groups of kGroupChunks, until one
+// workgroup takes all that is left.  esc has room for escape_entries<D>(chunks).
+template <int D>
+void hierarchy_top(const uint64_t *codes, int n, int kind, Node<D> *nodes, QNode<D> *qnodes, unsigned long long *flags,
+                   Escape<D> *esc, int chunks, const int64_t *seg, int nseg, TreeHeader *hdrs, hipStream_t s)
+{
+    int64_t span = chunk_leaves<D>();
+    for (int parts = chunks; parts > 1;) {
+        const int groups = (parts + kGroupChunks - 1) / kGroupChunks;
+        span *= kGroupChunks;
+        Escape<D> *out = groups > 1 ? esc + 2 * (size_t)parts : nullptr;
+        hierarchy_top_kernel<D><<<groups, kTopBlock, 0, s>>>(codes, n, kind, nodes, qnodes, flags, esc, 2 * parts, span,
+                                                             out, seg, nseg, hdrs);
+        esc = out;
+        parts = groups;
+    }
+}
+template <int D>
+size_t escape_entries(int chunks)
+{
+    constexpr int G = kGroupChunks;
+    size_t all = 2 * (size_t)chunks;
+    for (int parts = chunks; parts > 1; parts = (parts + G - 1) / G)
+        all += 2 * (size_t)((parts + G - 1) / G);
+    return all;
 }
 
 __global__ void empty_header(TreeHeader *hdr, int dim)
@@ -875,16 +1063,15 @@ arborx_status build_impl(const float *values, int64_t n, int kind, TreeDev &t, h
         constexpr int C = chunk_leaves<D>();
         const int chunks = (int)((n + C - 1) / C);
         Escape<D> *esc;
-        if ((st = tmp.get(&esc, (size_t)2 * chunks)) != ARBORX_OK)
+        if ((st = tmp.get(&esc, escape_entries<D>(chunks))) != ARBORX_OK)
             return st;
         ProfScope ps("build_hierarchy", s);
-        hierarchy_chunk_kernel<D><<<chunks, C, 0, s>>>(codes, ids, values, kind, (int)n, nodes, t.leaves,
-                                                                 flags, esc, nullptr, 0, t.hdr);
-        if (chunks > 1)
-            hierarchy_top_kernel<D><<<grid_for(2 * chunks, kBuildBlock), kBuildBlock, 0, s>>>(
-                codes, (int)n, nodes, flags, esc, 2 * chunks, nullptr, 0, t.hdr);
+        QNode<D> *qnodes = static_cast<QNode<D> *>(t.qnodes);
+        hierarchy_chunk_kernel<D><<<chunks, C, 0, s>>>(codes, ids, values, kind, (int)n, nodes, qnodes, t.leaves, flags,
+                                                       esc, nullptr, 0, t.hdr);
+        hierarchy_top<D>(codes, (int)n, kind, nodes, qnodes, flags, esc, chunks, nullptr, 0, t.hdr, s);
     }
-    if (quantized) {
+    if (quantized && tuning(OP_SPATIAL).build == 1) {
         ProfScope ps("build_quantize", s);
         quantize_nodes<D><<<grid_for(nn, kBuildBlock), kBuildBlock, 0, s>>>(nodes, (int)nn, nullptr, 0, (int)n, t.kind,
                                                                             t.hdr, static_cast<QNode<D> *>(t.qnodes));
@@ -1170,7 +1357,7 @@ size_t forest_build_ws(int64_t n, int T, int max_tiles, uint8_t *base, ForestBui
     uint8_t *tiles = take(sizeof(int32_t) * 3 * (size_t)max_tiles);
     uint8_t *codes = take(8 * nn), *codes2 = take(8 * nn), *ids = take(4 * nn), *ids2 = take(4 * nn);
     uint8_t *flags = take(8 * nn), *rws = take(radix_workspace_bytes(nn));
-    uint8_t *esc = take(sizeof(Escape<D>) * 2 * (size_t)chunks), *offs = take(sizeof(int64_t) * (T + 1));
+    uint8_t *esc = take(sizeof(Escape<D>) * escape_entries<D>(chunks)), *offs = take(sizeof(int64_t) * (T + 1));
     if (w) {
         w->tmin = reinterpret_cast<uint32_t *>(tmin);
         w->tmax = reinterpret_cast<uint32_t *>(tmax);
@@ -1268,14 +1455,10 @@ arborx_status forest_rebuild_impl(const float *values, const int64_t *offs, Fore
     Escape<D> *esc = static_cast<Escape<D> *>(w.esc);
     Node<D> *nodes = static_cast<Node<D> *>(f.nodes);
     ProfScope ps("build_hierarchy", s);
-    hierarchy_chunk_kernel<D><<<chunks, C, 0, s>>>(codes, ids, values, kind, (int)n, nodes, f.leaves, w.flags, esc,
-                                                   f.seg, T, f.hdrs);
-    if (chunks > 1)
-        hierarchy_top_kernel<D><<<grid_for(2 * chunks, kBuildBlock), kBuildBlock, 0, s>>>(
-            codes, (int)n, nodes, w.flags, esc, 2 * chunks, f.seg, T, f.hdrs);
-    if (f.qnodes)
-        quantize_nodes<D><<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(nodes, (int)n, f.seg, T, (int)n, f.kind,
-                                                                           f.hdrs, static_cast<QNode<D> *>(f.qnodes));
+    QNode<D> *qnodes = static_cast<QNode<D> *>(f.qnodes);
+    hierarchy_chunk_kernel<D><<<chunks, C, 0, s>>>(codes, ids, values, kind, (int)n, nodes, qnodes, f.leaves, w.flags,
+                                                   esc, f.seg, T, f.hdrs);
+    hierarchy_top<D>(codes, (int)n, kind, nodes, qnodes, w.flags, esc, chunks, f.seg, T, f.hdrs, s);
     if (f.wnodes)
         widen_nodes<D><<<grid_for(n, kBuildBlock), kBuildBlock, 0, s>>>(nodes, (int)n,
                                                                         static_cast<Node4<D> *>(f.wnodes));
