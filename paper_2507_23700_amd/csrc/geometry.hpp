@@ -154,8 +154,10 @@ __device__ __forceinline__ void qchild(const QNode<D> &nd, int c, bool exact, co
 // are at most (lo - query)/s and (query - hi)/s, the box's gaps: one of them
 // is zero, and the sum of their squares over the dimensions times s^2 is at
 // most the squared distance to the box.  r2: a box whose sum is above it holds
-// no value within the radius.  Clamping a query outside the frame to its
-// border only shortens the gaps.
+// no value within the radius.  A query outside the frame is clamped to its
+// border, which takes the excess e past it off the gaps of that dimension:
+// (e + g)^2 = e^2 + g (2 e + g), so r2 lacks the sum of the e^2, and a search
+// whose radius is about e long also counts the middle terms (CodeExcess).
 template <int D>
 struct CodeBall {
     uint32_t q[D];
@@ -178,8 +180,43 @@ __device__ __forceinline__ uint32_t code_gap2(const uint32_t (&q)[D], const uint
     return acc;
 }
 
-// The code words of query c.  inv = 1/s; lo, hi: the frame.
-__device__ __forceinline__ uint32_t code_query(float c, float lo, float hi, double inv)
+// The excesses of a query past the frame, for gaps of the form g (g + 2 e):
+// e2 = 2 e in both halves (the half of the other side has no gap), scaled with
+// g by 2^-shift where the largest is above 16 bits.  All rounded down.
+template <int D>
+struct CodeExcess {
+    uint32_t e2[D];
+    uint32_t shift;  // in both halves
+    __device__ __forceinline__ explicit CodeExcess(const double (&e)[D])
+    {
+        double most = 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            most = fmax(most, 2.0 * e[d]);
+        const int sh = most < 65536.0 ? 0 : (most < 0x1p31 ? ilogb(most) - 15 : 15);
+        shift = (uint32_t)sh * 0x10001u;
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            e2[d] = (uint32_t)fmin(ldexp(2.0 * e[d], -sh), 65535.0) * 0x10001u;
+    }
+    __device__ __forceinline__ uint32_t gap2(const uint32_t (&q)[D], const uint32_t (&w)[D]) const
+    {
+        uint32_t acc = 0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const ushort2_t g = __builtin_elementwise_sub_sat(__builtin_bit_cast(ushort2_t, w[d]),
+                                                              __builtin_bit_cast(ushort2_t, q[d]));
+            const ushort2_t g2 = __builtin_elementwise_add_sat((ushort2_t)(g >> __builtin_bit_cast(ushort2_t, shift)),
+                                                               __builtin_bit_cast(ushort2_t, e2[d]));
+            acc = __builtin_amdgcn_udot2(g, g2, acc, true);
+        }
+        return acc;
+    }
+};
+
+// The code words of query c and its excess past the frame, rounded down.
+// inv = 1/s; lo, hi: the frame.
+__device__ __forceinline__ uint32_t code_query(float c, float lo, float hi, double inv, double &e)
 {
     // decode(code) is off by half an ulp of a coordinate at most; the last term covers the arithmetic here
     const double m = fmax(fabs((double)lo), fabs((double)hi));
@@ -188,16 +225,33 @@ __device__ __forceinline__ uint32_t code_query(float c, float lo, float hi, doub
     const double up = ceil(u + slop), dn = floor(u - slop);
     const uint32_t qhi = up >= (double)kQMax ? (uint32_t)kQMax : (up > 0.0 ? (uint32_t)up : 0u);
     const uint32_t qlo = dn >= (double)kQMax ? (uint32_t)kQMax : (dn > 0.0 ? (uint32_t)dn : 0u);
+    e = fmax(0.0, fmax(-(u + slop), u - slop - (double)kQMax) * (1.0 - 0x1p-40));
     return qhi | (((uint32_t)kQMax - qlo) << 16);
 }
 
-// Threshold on code_gap2 for squared radius r2.  A value matches when its
-// float32 squared distance, within a factor 1 +- 2^-20 and 16 * 2^-149 of the
-// real one, is at most r2.
-__device__ __forceinline__ uint32_t code_radius2(float r2, double inv)
+// The ball of squared radius r2 around c.  A value matches when its float32
+// squared distance, within a factor 1 +- 2^-20 and 16 * 2^-149 of the real
+// one, is at most r2.  One that does not reach the frame meets only boxes that
+// span it.
+template <int D>
+__device__ __forceinline__ void code_ball(const float (&c)[D], float r2, const float *lo, const float *hi,
+                                          double inv, CodeBall<D> &ball)
 {
-    const double r = ((double)r2 * (1.0 + 0x1p-18) + 0x1p-144) * inv * inv * (1.0 + 0x1p-30) + 1.0;
-    return r < 4294967295.0 ? (uint32_t)r : UINT32_MAX;
+    double past = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        double e;
+        ball.q[d] = code_query(c[d], lo[d], hi[d], inv, e);
+        past += e * e;
+    }
+    const double r = ((double)r2 * (1.0 + 0x1p-18) + 0x1p-144) * inv * inv * (1.0 + 0x1p-30) + 1.0 -
+                     fmin(past, 1.0e300);
+    ball.r2 = r < 4294967295.0 ? (uint32_t)fmax(r, 0.0) : UINT32_MAX;
+    if (r < 0.0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            ball.q[d] = 0;
+    }
 }
 
 template <int D>

@@ -25,59 +25,6 @@
 namespace ax {
 namespace {
 
-// Node slots of a single tree (one-value trees still have one node).
-__device__ __forceinline__ int node_count(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
-
-// Walk of one query over a tree that holds quantized nodes: in codes for a
-// sphere over points whose frame has one step; for a frame without one
-// (quant_frame), over the float nodes, which the decoded boxes of such a frame
-// only approximate; other predicates and box values decode the boxes.
-template <int D, class P, class F, class S = NeverStop>
-__device__ __forceinline__ void walk_quantized(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
-                                               const TreeHeader &h, const float *__restrict__ leaves, int kind,
-                                               const P &pred, int *s_stack, int cap, int (&spill)[kSpill], F &f,
-                                               const S &stop = S())
-{
-    if constexpr (std::is_same<P, Sphere<D>>::value) {
-        if (kind != ARBORX_BOXES) {
-            if (h.qinv != 0.0) {
-                TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
-                auto g1 = [&](int, int idx, float d2) { f(idx, d2); };
-                auto g = each_hit(g1);
-                const P preds[1] = {pred};
-                traverse_codes<D, 1, false>(qnodes, h, node_count(&h), preds, -1, st, g, stop);
-            } else {
-                ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
-                traverse_spatial<D>(nodes, h.root, node_count(&h), pred, st, f, stop);
-            }
-            return;
-        }
-    }
-    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
-    traverse_spatial_q<D>(qnodes, h, node_count(&h), leaves, kind, pred, st, f, stop);
-}
-
-// The same for NQ neighbouring sphere queries of one thread.
-template <int D, int NQ, class F>
-__device__ __forceinline__ void walk_quantized_packet(const Node<D> *__restrict__ nodes,
-                                                      const QNode<D> *__restrict__ qnodes, const TreeHeader &h,
-                                                      const float *__restrict__ leaves, int kind,
-                                                      const Sphere<D> (&pred)[NQ], int *s_stack, int cap,
-                                                      int (&spill)[kSpill], F &f)
-{
-    if (kind != ARBORX_BOXES && h.qinv != 0.0) {
-        TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
-        auto g = each_hit(f);
-        traverse_codes<D, NQ, false>(qnodes, h, node_count(&h), pred, -1, st, g);
-        return;
-    }
-    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
-    if (kind != ARBORX_BOXES)
-        traverse_spatial_packet<D, NQ>(nodes, h.root, node_count(&h), pred, st, f);
-    else
-        traverse_spatial_packet_q<D, NQ>(qnodes, h, node_count(&h), leaves, kind, pred, st, f);
-}
-
 // Match number c (c >= R, counted from 0) of query qi, past its stash row of
 // R: stored in the query's overflow chain, whose current chunk is `cur` (one
 // register per query; -2 once the row is given up).  Chunks come from the
@@ -286,7 +233,7 @@ __global__ void k_spatial_count(const Node<D> *__restrict__ nodes, const QNode<D
     else if (SCHED == 2)
         traverse_spatial_rope<D>(nodes, hdr->root, node_count(hdr), hdr->start + hdr->n - 1, pred, f);
     else if (SCHED == 3)
-        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (SCHED == 4)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -356,7 +303,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(NQ == 2 && D <= 3 && !OUT ? 6 : 1)
             }
     };
     if (Q)
-        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
+        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f);
     else
         traverse_spatial_packet<D, NQ>(nodes, hdr->root, node_count(hdr), pred, st, f);
 #pragma unroll
@@ -529,7 +476,7 @@ __global__ void k_spatial_fill_rows(const Node<D> *__restrict__ nodes, const QNo
         ++k;
     };
     if (FMT == 1)
-        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (FMT == 2)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -746,7 +693,7 @@ __global__ void k_spatial_reduce(const Node<D> *__restrict__ nodes, const QNode<
     else if (SCHED == 2)
         traverse_spatial_rope<D>(nodes, hdr->root, node_count(hdr), hdr->start + hdr->n - 1, pred, f);
     else if (SCHED == 3)
-        walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
+        walk_quantized<D>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f);
     else if (SCHED == 4)
         traverse_spatial4<D>(wnodes, hdr->root, node_count(hdr), pred, st, f);
     else
@@ -803,7 +750,7 @@ __global__ void k_spatial_reduce_packet(const Node<D> *__restrict__ nodes, const
             }
     };
     if (Q)
-        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f);
+        walk_quantized_packet<D, NQ>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f);
     else
         traverse_spatial_packet<D, NQ>(nodes, hdr->root, node_count(hdr), pred, st, f);
 #pragma unroll
@@ -821,12 +768,13 @@ __global__ void k_spatial_reduce_packet(const Node<D> *__restrict__ nodes, const
 // at 10^7 points took 7.7 ms instead of 8.4 (shell 6.8 instead of 7.4).  The
 // 6D k = 8 walk on quantized nodes, held from 88 to 80 registers (6 waves
 // instead of 5), spilled and ran slower (7.0 against 6.8 ms), so the other
-// shapes are left to the compiler; so is the 3D walk over codes, whose 68
-// registers held to 64 measured the same.
+// shapes are left to the compiler.  The 3D k = 16 walk over codes is held from
+// 78 registers to 72 (7 waves; the four spilled are of queries outside the
+// frame): 7.81 instead of 7.97 ms for build and search at 10^7 points.
 template <int D, int K, bool WAVE, int FMT>
 constexpr int knn_waves()
 {
-    return (!WAVE && D <= 3 && K == 16 && FMT == 0) ? 8 : 1;
+    return (!WAVE && D <= 3 && K == 16) ? (FMT == 0 ? 8 : FMT == 1 ? 7 : 1) : 1;
 }
 
 template <int D, int K, bool WAVE, int FMT>
@@ -930,7 +878,7 @@ __global__ void k_count_up_to(const Node<D> *__restrict__ nodes, const QNode<D> 
     auto stop = [&]() { return c >= n_max; };
     if (n_max > 0) {
         if constexpr (Q)
-            walk_quantized<D>(nodes, qnodes, *hdr, leaves, kind, pred, s_stack, stack_cap, spill, f, stop);
+            walk_quantized<D>(nodes, qnodes, *hdr, node_count(hdr), leaves, kind, pred, s_stack, stack_cap, spill, f, stop);
         else
             traverse_spatial<D>(nodes, hdr->root, node_count(hdr), pred, st, f, stop);
     }

@@ -3,6 +3,8 @@
 // register buffers, and the seeded nearest-first kNN walk.
 #pragma once
 
+#include <type_traits>
+
 #include "device_util.hpp"
 #include "geometry.hpp"
 #include "internal.hpp"
@@ -741,12 +743,8 @@ __device__ __forceinline__ void traverse_codes(const QNode<D> *__restrict__ node
 {
     CodeBall<D> ball[NQ];
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-            ball[j].q[d] = code_query(pred[j].c[d], h.lo[d], h.hi[d], h.qinv);
-        ball[j].r2 = code_radius2(pred[j].r2, h.qinv);
-    }
+    for (int j = 0; j < NQ; ++j)
+        code_ball<D>(pred[j].c, pred[j].r2, h.lo, h.hi, h.qinv, ball[j]);
     const unsigned last = (unsigned)n_nodes - 1u;
     int cur = h.root;
     QNode<D> nd;
@@ -1367,30 +1365,21 @@ __device__ __forceinline__ void knn_search_wave(const Node<D> *__restrict__ node
 // (see traverse_codes): as knn_search, seeded and software-pipelined, with
 // internal children ordered and pruned by their squared code gaps against the
 // bound in codes, and leaf children offered with their exact distances.  The
-// bound in codes is rounded up in float32: k and a hold 1/s^2 with the margins
-// of code_radius2 and more.  Half the loads of the float nodes and no decoding:
+// bound in codes, k d^2 + a, is rounded up in float32: k and a hold 1/s^2 with
+// the margins of code_ball and more.  A wavefront with a query outside the
+// frame counts the excesses past it (CodeExcess), or it would enter every node
+// near the projection on the frame: k = 1 between clouds of unlike extents
+// took 6.6 ms without them, 1.8 over float nodes.  Half the loads of the float nodes and no decoding:
 // k = 16 at 10^7 cube points 7.3 -> 6.0 ms, and k = 8 over 2*10^6 6D mixture
 // points, against decoded boxes, 7.1 -> 5.9 ms.  (Gathering admitted leaves in
 // LDS and merging eight at a time with a sorting network took 13 % fewer
 // vector instructions at k = 16, none fewer at k = 8, and 6.5 and 6.7 ms: the
 // bound lags and the queue takes LDS.)
-template <int D, int K>
-__device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ nodes, int n_nodes,
-                                                 const float *__restrict__ leaves, int kind, const TreeHeader &hdr,
-                                                 const float (&q)[D], TopK<K> &best, TopStack<KnnCode> &st,
-                                                 int seed, const SeedKeys &keys)
+template <int D, int K, bool PAST, class G>
+__device__ __forceinline__ void knn_walk_codes(const QNode<D> *__restrict__ nodes, int n_nodes, const TreeHeader &hdr,
+                                               const float (&q)[D], TopK<K> &best, TopStack<KnnCode> &st, float k,
+                                               float a, const G &gap2)
 {
-    best.reset(INFINITY);
-    if (hdr.n <= 0)
-        return;
-    if (seed != 1 && hdr.n >= K)
-        seed_window<D, K>(leaves, kind, hdr, leaf_position<D>(keys, hdr, q), q, best, seed);
-    uint32_t qc[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv);
-    const float k = (float)fmin(hdr.qinv * hdr.qinv * (1.0 + 0x1p-16), 3.0e38);
-    const float a = (float)fmin(hdr.qinv * hdr.qinv * 0x1p-144 + 2.0, 3.0e38);
     const unsigned last = (unsigned)n_nodes - 1u;
     int cur = hdr.root;
     QNode<D> nd;
@@ -1400,13 +1389,13 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
             break;
         KnnCode deferred = st.top();
         const int c0 = nd.child[0], c1 = nd.child[1];
-        const uint32_t s0 = code_gap2<D>(qc, nd.w[0]), s1 = code_gap2<D>(qc, nd.w[1]);
+        const uint32_t s0 = gap2(nd.w[0]), s1 = gap2(nd.w[1]);
         // leaf children as keys, the other slots above every key
         const double none = TopK<K>::pack(__uint_as_float(0x7fc00000u), INT32_MAX);
         const double v0 = c0 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[0]), ~c0) : none;
         const double v1 = c1 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[1]), ~c1) : none;
         const float fb = fmaf(best.bound(), k, a);
-        const uint32_t bound = fb < 4.29e9f ? (uint32_t)fb : UINT32_MAX;
+        const uint32_t bound = fb < 4.29e9f ? (uint32_t)(PAST ? fmaxf(fb, 0.0f) : fb) : UINT32_MAX;
         const bool k0 = c0 >= 0 && s0 <= bound;
         const bool k1 = c1 >= 0 && s1 <= bound;
         const bool near1 = k1 && (!k0 || s1 < s0);
@@ -1425,6 +1414,38 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
         best.offer_key(key_min(v0, v1));
         best.offer_key(key_max(v0, v1));
     }
+}
+
+template <int D, int K>
+__device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ nodes, int n_nodes,
+                                                 const float *__restrict__ leaves, int kind, const TreeHeader &hdr,
+                                                 const float (&q)[D], TopK<K> &best, TopStack<KnnCode> &st,
+                                                 int seed, const SeedKeys &keys)
+{
+    best.reset(INFINITY);
+    if (hdr.n <= 0)
+        return;
+    if (seed != 1 && hdr.n >= K)
+        seed_window<D, K>(leaves, kind, hdr, leaf_position<D>(keys, hdr, q), q, best, seed);
+    uint32_t qc[D];
+    double e[D], past = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv, e[d]);
+        past += e[d] * e[d];
+    }
+    const double k = hdr.qinv * hdr.qinv * (1.0 + 0x1p-19), a = hdr.qinv * hdr.qinv * 0x1p-144 + 2.0;
+    if (!__any(past > 1.0)) {
+        knn_walk_codes<D, K, false>(nodes, n_nodes, hdr, q, best, st, (float)fmin(k, 3.0e38), (float)fmin(a, 3.0e38),
+                             [&](const uint32_t(&w)[D]) { return code_gap2<D>(qc, w); });
+        return;
+    }
+    const CodeExcess<D> ex(e);
+    const double unit = ldexp(1.0, -(int)(ex.shift & 15u));
+    const double rest = (a - past * (1.0 - 0x1p-22)) * unit;
+    knn_walk_codes<D, K, true>(nodes, n_nodes, hdr, q, best, st, (float)fmin(k * unit, 3.0e38),
+                         (float)fmin(fmax(rest + 1.0, -3.0e38), 3.0e38),
+                         [&](const uint32_t(&w)[D]) { return ex.gap2(qc, w); });
 }
 
 // kNN over quantized nodes: as knn_search (seeded, software-pipelined),
@@ -1518,6 +1539,59 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
         }
         cur = next;
     }
+}
+
+// Node slots of a single tree (one-value trees still have one node).
+__device__ __forceinline__ int node_count(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
+
+// Walk of one query over a tree that holds quantized nodes: in codes for a
+// sphere over points whose frame has one step; for a frame without one
+// (quant_frame), over the float nodes, which the decoded boxes of such a frame
+// only approximate; other predicates and box values decode the boxes.
+template <int D, class P, class F, class S = NeverStop>
+__device__ __forceinline__ void walk_quantized(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
+                                               const TreeHeader &h, int n_nodes, const float *__restrict__ leaves,
+                                               int kind, const P &pred, int *s_stack, int cap, int (&spill)[kSpill],
+                                               F &f, const S &stop = S())
+{
+    if constexpr (std::is_same<P, Sphere<D>>::value) {
+        if (kind != ARBORX_BOXES) {
+            if (h.qinv != 0.0) {
+                TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
+                auto g1 = [&](int, int idx, float d2) { f(idx, d2); };
+                auto g = each_hit(g1);
+                const P preds[1] = {pred};
+                traverse_codes<D, 1, false>(qnodes, h, n_nodes, preds, -1, st, g, stop);
+            } else {
+                ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+                traverse_spatial<D>(nodes, h.root, n_nodes, pred, st, f, stop);
+            }
+            return;
+        }
+    }
+    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+    traverse_spatial_q<D>(qnodes, h, n_nodes, leaves, kind, pred, st, f, stop);
+}
+
+// The same for NQ neighbouring sphere queries of one thread.
+template <int D, int NQ, class F>
+__device__ __forceinline__ void walk_quantized_packet(const Node<D> *__restrict__ nodes,
+                                                      const QNode<D> *__restrict__ qnodes, const TreeHeader &h,
+                                                      int n_nodes, const float *__restrict__ leaves, int kind,
+                                                      const Sphere<D> (&pred)[NQ], int *s_stack, int cap,
+                                                      int (&spill)[kSpill], F &f)
+{
+    if (kind != ARBORX_BOXES && h.qinv != 0.0) {
+        TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
+        auto g = each_hit(f);
+        traverse_codes<D, NQ, false>(qnodes, h, n_nodes, pred, -1, st, g);
+        return;
+    }
+    ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
+    if (kind != ARBORX_BOXES)
+        traverse_spatial_packet<D, NQ>(nodes, h.root, n_nodes, pred, st, f);
+    else
+        traverse_spatial_packet_q<D, NQ>(qnodes, h, n_nodes, leaves, kind, pred, st, f);
 }
 
 }  // namespace
