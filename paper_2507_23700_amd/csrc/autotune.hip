@@ -368,7 +368,6 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
     if (st != ARBORX_OK)
         return st;
     const std::string key = "forest " + cache_key(op, dim, 0, k, n, m);
-    const int fkind = ARBORX_POINTS;  // under the defaults every forest walks format 0, whatever its values
     const Tuning base = tuning(op);
     Tuning cached = base;
     if (cache_lookup(key, cached)) {
@@ -381,7 +380,7 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
             best->build = cached.build;
             best->seed_mode = cached.seed;
             best->queries_per_thread = cached.packet;
-            best->node_format = node_format_of(cached, op, dim, fkind, true);
+            best->node_format = forest_format(cached, op, forest);
         }
         if (best_ms)
             *best_ms = -1.0;
@@ -390,7 +389,7 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
     std::vector<Candidate> cands;
     cands.push_back(Candidate{base, 0});
     Tuning fbase = base;  // the others start from the node format the forest walks under the tuning in force
-    fbase.nodes = node_format_of(base, op, dim, fkind, true);
+    fbase.nodes = forest_format(base, op, forest);
     for (int stack : {4, 8, 16, 32}) {
         Candidate c{fbase, 0};
         c.t.stack = stack;
@@ -489,7 +488,8 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
         return st != ARBORX_OK ? st : fail(ARBORX_E_DEVICE, "no candidate ran");
     }
     besti = keep_unless_faster(cands, besti);
-    const Tuning &b = cands[besti].t;
+    Tuning &b = cands[besti].t;
+    b.nodes = forest_format(b, op, forest);  // the defaults choose the format themselves: record the one that ran
     set_tuning_op(op, b);
     cache_store(key, b, cands[besti].ms);
     if (best) {
@@ -500,7 +500,7 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
         best->build = b.build;
         best->seed_mode = b.seed;
         best->queries_per_thread = b.packet;
-        best->node_format = node_format_of(b, op, dim, fkind, true);
+        best->node_format = b.nodes;
     }
     if (best_ms)
         *best_ms = cands[besti].ms;

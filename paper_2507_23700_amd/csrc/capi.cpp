@@ -180,8 +180,10 @@ int node_format_of(const Tuning &t, int op, int dim, int kind, bool forest)
 {
     if (!t.by_dim)
         return t.nodes;
-    if (forest || kind == ARBORX_BOXES)  // a box leaf is not exact in the node: its record is fetched again
+    if (kind == ARBORX_BOXES)  // a box leaf is not exact in the node: its record is fetched again
         return 0;
+    if (forest)  // quantized unless a saved choice for the reductions names another format
+        return op == OP_KNN || t.nodes == 1 ? 1 : 0;
     if (op == OP_KNN)  // four-wide nodes only where a saved choice of the autotuner names them
         return t.nodes == 2 && dim < 6 ? 2 : 1;
     return t.nodes;
@@ -219,6 +221,16 @@ int tree_format(int op, const TreeDev &t)
     const int f = walk_format(op, t.dim, t.kind);
     return (f == 1 && !t.qnodes && tuning(op).by_dim) ? 0 : f;
 }
+
+static int forest_format_of(const Tuning &t, int op, const ForestDev &f)
+{
+    const int fmt = node_format_of(t, op, f.dim, f.kind, true);
+    return (fmt == 1 && !f.qnodes && t.by_dim) ? 0 : fmt;
+}
+
+int forest_format(int op, const ForestDev &f) { return forest_format_of(tuning(op), op, f); }
+
+int forest_format(const Tuning &t, int op, arborx_forest forest) { return forest_format_of(t, op, forest->dev); }
 
 arborx_status check_nodes(const void *qnodes, const void *wnodes, int64_t n, int fmt)
 {

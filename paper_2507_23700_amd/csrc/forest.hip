@@ -1,14 +1,18 @@
 // Forest queries: B batches of queries, batch b = queries [boff[b], boff[b+1])
 // searched in tree btree[b] of a forest (radius btree-specific for reductions).
 //
-// 1. ordering: each query gets the key (batch << mbits) | Morton code of the
+// 1. ordering: each query gets the key (batch << mbits) | Hilbert code of the
 //    query inside its target tree's box, and one radix sort orders all
 //    queries by batch, then along the curve inside the batch;
-// 2. one persistent launch: a grid sized to fill the GPU once, each
-//    workgroup repeatedly takes the next block of sorted queries from an
-//    atomic counter until none are left, so uneven batches and uneven
-//    per-query work balance dynamically.  Each lane answers one query against
-//    its batch's tree.
+// 2. one launch over the sorted queries of all batches, each lane answering
+//    one query (or a few neighbours) against its batch's tree, which the
+//    sorted key names.  Workgroups are dealt to the XCDs in contiguous runs
+//    (xcd_block), so each XCD's L2 holds few trees.
+// Bound: as the walks of single trees (traverse_codes, knn_search_codes).  For
+// 512 batches of 6.5*10^6 queries in all on 32 trees of 9.4*10^6 points, against a
+// persistent grid over float nodes that took 256 sorted queries at a time from
+// an atomic counter, spread every tree over all eight L2 caches and searched
+// each query's batch: k = 8 3.8 -> 3.0 ms, count with distances 2.7 -> 1.85.
 // The query path allocates nothing once the forest's workspace is reserved, and
 // never synchronises, so it can be captured in a hipGraph.  Results use indices
 // local to the target tree (value index minus the tree's first value), the
@@ -39,219 +43,203 @@ __device__ __forceinline__ int batch_of(const int64_t *__restrict__ boff, int B,
     return lo;
 }
 
+// Batches are contiguous, so a workgroup finds the batch of its first query by
+// a search and the others step on from there.
 template <int D, typename K>
-__global__ void k_forest_codes(const float *__restrict__ q, int64_t m, const int64_t *__restrict__ boff, int B,
-                               const int32_t *__restrict__ btree, int T, const TreeHeader *__restrict__ hdrs,
-                               int mbits, K *__restrict__ codes, uint32_t *__restrict__ ids)
+__global__ __launch_bounds__(kForestBlock) void k_forest_codes(const float *__restrict__ q, int64_t m,
+                                                               const int64_t *__restrict__ boff, int B,
+                                                               const int32_t *__restrict__ btree, int T,
+                                                               const TreeHeader *__restrict__ hdrs, int mbits,
+                                                               K *__restrict__ codes, uint32_t *__restrict__ ids)
 {
+    __shared__ int s_first;
     const int bits = mbits / D;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const int b = batch_of(boff, B, i);
-        const int t = btree[b];
-        uint32_t c[D];
-        if (t >= 0 && t < T && hdrs[t].n > 0) {
+    const int64_t base = (int64_t)blockIdx.x * kForestBlock;
+    if (threadIdx.x == 0)
+        s_first = batch_of(boff, B, base);
+    __syncthreads();
+    const int64_t i = base + threadIdx.x;
+    if (i >= m)
+        return;
+    int b = s_first;
+    for (int step = 0; step < 8 && b + 1 < B && boff[b + 1] <= i; ++step)
+        ++b;
+    if (b + 1 < B && boff[b + 1] <= i)  // many small batches
+        b = batch_of(boff, B, i);
+    const int t = btree[b];
+    uint32_t c[D];
+    if (t >= 0 && t < T && hdrs[t].n > 0) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const float lo = hdrs[t].lo[d], ext = hdrs[t].hi[d] - lo;
-                c[d] = quantise(q[i * D + d], lo, ext > 0.0f ? 1.0f / ext : 0.0f, bits);
-            }
-        } else {
-#pragma unroll
-            for (int d = 0; d < D; ++d)
-                c[d] = 0;
+        for (int d = 0; d < D; ++d) {
+            const float lo = hdrs[t].lo[d], ext = hdrs[t].hi[d] - lo;
+            c[d] = quantise(q[i * D + d], lo, ext > 0.0f ? 1.0f / ext : 0.0f, bits);
         }
-        codes[i] = ((K)b << mbits) | (K)interleave<D>(c, bits);
-        ids[i] = (uint32_t)i;
+    } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            c[d] = 0;
     }
+    const K code = mbits <= 32 ? (K)hilbert_code<D>(c, bits) : (K)interleave<D>(c, bits);
+    codes[i] = ((K)b << mbits) | code;
+    ids[i] = (uint32_t)i;
 }
 
-// Next block of `span` sorted positions for this workgroup (one per thread by
-// default), or -1 when all are taken.
-__device__ __forceinline__ int64_t next_block(unsigned long long *counter, int64_t m, int64_t span = 0)
-{
-    __shared__ int64_t s_start;
-    if (threadIdx.x == 0) {
-        const unsigned long long c = atomicAdd(counter, 1ull);
-        s_start = (int64_t)c * (span > 0 ? span : (int64_t)blockDim.x);
+// The sorted queries of a call: the permutation, and the keys it was sorted by,
+// whose bits from mbits up are the batch.
+struct ForestOrder {
+    const uint32_t *perm;
+    const void *keys;
+    bool wide;  // 64-bit keys
+    int mbits;
+    __device__ __forceinline__ int batch(int64_t t) const
+    {
+        return wide ? (int)(static_cast<const uint64_t *>(keys)[t] >> mbits)
+                    : (int)(static_cast<const uint32_t *>(keys)[t] >> mbits);
     }
-    __syncthreads();
-    const int64_t start = s_start;
-    __syncthreads();
-    return start < m ? start : -1;
-}
+};
 
-template <int D, bool SUMDIST, int FMT>
+// One thread takes NQ consecutive sorted positions, which usually share a batch
+// and tree and are walked together; ones that straddle trees are walked one at
+// a time.  FMT: 0 float nodes, 1 quantized, 2 four-wide (the last two with the
+// walks of single trees; NQ up to 2 and 1).
+template <int D, bool SUMDIST, int NQ, int FMT>
 __global__ __launch_bounds__(kForestBlock) void k_forest_reduce(
     const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes, const Node4<D> *__restrict__ wnodes,
-    const float *__restrict__ leaves, int kind,
-    int n_nodes, const TreeHeader *__restrict__ hdrs, int T,
-    const float *__restrict__ queries, int64_t m, const uint32_t *__restrict__ perm, const int64_t *__restrict__ boff,
-    int B, const int32_t *__restrict__ btree, const float *__restrict__ bradius, float scale, int32_t *__restrict__ counts,
-    int64_t *__restrict__ sums, unsigned long long *counter, int stack_cap)
+    const float *__restrict__ leaves, int kind, int n_nodes, const TreeHeader *__restrict__ hdrs, int T,
+    const float *__restrict__ queries, int64_t m, ForestOrder order, int B, const int32_t *__restrict__ btree,
+    const float *__restrict__ bradius, float scale, int32_t *__restrict__ counts, int64_t *__restrict__ sums,
+    int stack_cap)
 {
     extern __shared__ int s_stack[];
+    const int64_t t0 = (xcd_block() * blockDim.x + threadIdx.x) * NQ;
+    if (t0 >= m)
+        return;
     int spill[kSpill];
-    for (int64_t start; (start = next_block(counter, m)) >= 0;) {
-        const int64_t t = start + threadIdx.x;
-        if (t >= m)
-            continue;
-        const int64_t qi = perm[t];
-        if (qi < 0 || qi >= m)
-            continue;
-        const int b = batch_of(boff, B, qi);
-        const int tr = btree[b];
-        int c = 0;
-        long long s = 0;
-        if (tr >= 0 && tr < T) {
-            const float r = bradius[b];
-            Sphere<D> pred;
-            pred.load(queries, qi, r * r);
-            ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
-            auto f = [&](int, float d2) {
-                ++c;
-                if (SUMDIST)
-                    s += fixed_term(d2, scale);
-            };
-            if (FMT == 1)
-                traverse_spatial_q<D>(qnodes, hdrs[tr], n_nodes, leaves, kind, pred, st, f);
-            else if (FMT == 2)
-                traverse_spatial4<D>(wnodes, hdrs[tr].root, n_nodes, pred, st, f);
-            else
-                traverse_spatial<D>(nodes, hdrs[tr].root, n_nodes, pred, st, f);
-        }
-        counts[qi] = c;
-        if (SUMDIST)
-            sums[qi] = s;
-    }
-}
-
-// Packet form of the forest reduction (binary nodes): thread t of a block
-// takes NQ consecutive sorted positions.  Sorting is by (batch, Morton code),
-// so they usually share a batch and tree and are walked together; a packet
-// that straddles trees is walked one query at a time.
-template <int D, bool SUMDIST, int NQ>
-__global__ __launch_bounds__(kForestBlock) void k_forest_reduce_packet(
-    const Node<D> *__restrict__ nodes, int n_nodes, const TreeHeader *__restrict__ hdrs, int T,
-    const float *__restrict__ queries, int64_t m, const uint32_t *__restrict__ perm, const int64_t *__restrict__ boff,
-    int B, const int32_t *__restrict__ btree, const float *__restrict__ bradius, float scale, int32_t *__restrict__ counts,
-    int64_t *__restrict__ sums, unsigned long long *counter, int stack_cap)
-{
-    extern __shared__ int s_stack[];
-    int spill[kSpill];
-    for (int64_t start; (start = next_block(counter, m, (int64_t)kForestBlock * NQ)) >= 0;) {
-        int64_t qi[NQ];
-        int tr[NQ];
-        Sphere<D> pred[NQ];
-        bool same = true;
+    int64_t qi[NQ];
+    int tr[NQ];
+    Sphere<D> pred[NQ];
+    bool same = true;
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const int64_t p = start + (int64_t)threadIdx.x * NQ + j;
-            qi[j] = p < m ? (int64_t)perm[p] : -1;
-            tr[j] = -1;
-            if (qi[j] >= 0 && qi[j] < m) {
-                const int b = batch_of(boff, B, qi[j]);
+    for (int j = 0; j < NQ; ++j) {
+        qi[j] = t0 + j < m ? (int64_t)order.perm[t0 + j] : -1;
+        tr[j] = -1;
+        if (qi[j] >= 0 && qi[j] < m) {
+            const int b = order.batch(t0 + j);
+            if (b >= 0 && b < B) {
                 tr[j] = btree[b] >= 0 && btree[b] < T ? btree[b] : -1;
                 const float r = bradius[b];
                 pred[j].load(queries, qi[j], r * r);
             } else {
-                qi[j] = -1;
                 pred[j].dead();
             }
-            if (qi[j] >= 0 && tr[j] != tr[0])
-                same = false;
-        }
-        int c[NQ];
-        long long s[NQ];
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            c[j] = 0;
-            s[j] = 0;
-        }
-        ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
-        if (same && tr[0] >= 0) {
-            auto f = [&](int j, int, float d2) {
-#pragma unroll
-                for (int jj = 0; jj < NQ; ++jj)
-                    if (jj == j) {
-                        ++c[jj];
-                        if (SUMDIST)
-                            s[jj] += fixed_term(d2, scale);
-                    }
-            };
-            traverse_spatial_packet<D, NQ>(nodes, hdrs[tr[0]].root, n_nodes, pred, st, f);
         } else {
-#pragma unroll
-            for (int j = 0; j < NQ; ++j)
-                if (qi[j] >= 0 && tr[j] >= 0) {
-                    st.clear();
-                    auto f = [&](int, float d2) {
-                        ++c[j];
-                        if (SUMDIST)
-                            s[j] += fixed_term(d2, scale);
-                    };
-                    traverse_spatial<D>(nodes, hdrs[tr[j]].root, n_nodes, pred[j], st, f);
-                }
+            qi[j] = -1;
+            pred[j].dead();
         }
+        if (qi[j] >= 0 && tr[j] != tr[0])
+            same = false;
+    }
+    int c[NQ];
+    long long s[NQ];
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        c[j] = 0;
+        s[j] = 0;
+    }
+    auto one = [&](const TreeHeader &h, const Sphere<D> &p, auto &f) {
+        ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
+        if (FMT == 1)
+            walk_quantized<D>(nodes, qnodes, h, n_nodes, leaves, kind, p, s_stack, stack_cap, spill, f);
+        else if (FMT == 2)
+            traverse_spatial4<D>(wnodes, h.root, n_nodes, p, st, f);
+        else
+            traverse_spatial<D>(nodes, h.root, n_nodes, p, st, f);
+    };
+    if (NQ > 1 && same && tr[0] >= 0) {
+        auto f = [&](int j, int, float d2) {
+#pragma unroll
+            for (int jj = 0; jj < NQ; ++jj)
+                if (jj == j) {
+                    ++c[jj];
+                    if (SUMDIST)
+                        s[jj] += fixed_term(d2, scale);
+                }
+        };
+        if (FMT == 1) {
+            walk_quantized_packet<D, NQ>(nodes, qnodes, hdrs[tr[0]], n_nodes, leaves, kind, pred, s_stack, stack_cap,
+                                         spill, f);
+        } else {
+            ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
+            traverse_spatial_packet<D, NQ>(nodes, hdrs[tr[0]].root, n_nodes, pred, st, f);
+        }
+    } else {
 #pragma unroll
         for (int j = 0; j < NQ; ++j)
-            if (qi[j] >= 0) {
-                counts[qi[j]] = c[j];
-                if (SUMDIST)
-                    sums[qi[j]] = s[j];
+            if (qi[j] >= 0 && tr[j] >= 0) {
+                auto f = [&](int, float d2) {
+                    ++c[j];
+                    if (SUMDIST)
+                        s[j] += fixed_term(d2, scale);
+                };
+                one(hdrs[tr[j]], pred[j], f);
             }
     }
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+        if (qi[j] >= 0) {
+            counts[qi[j]] = c[j];
+            if (SUMDIST)
+                sums[qi[j]] = s[j];
+        }
 }
 
 template <int D, int K, int FMT>
 __global__ __launch_bounds__(kForestBlock) void k_forest_knn(
     const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes, const Node4<D> *__restrict__ wnodes,
-    int n_nodes,
-    const float *__restrict__ leaves, int kind,
-    const TreeHeader *__restrict__ hdrs, int T, const float *__restrict__ queries, int64_t m,
-    const uint32_t *__restrict__ perm, const int64_t *__restrict__ boff, int B, const int32_t *__restrict__ btree,
-    int k_out, float *__restrict__ out_d2, int32_t *__restrict__ out_idx, unsigned long long *counter, int stack_cap,
-    int seed, const uint64_t *__restrict__ keys, int mbits)
+    int n_nodes, const float *__restrict__ leaves, int kind, const TreeHeader *__restrict__ hdrs, int T,
+    const float *__restrict__ queries, int64_t m, ForestOrder order, int B, const int32_t *__restrict__ btree,
+    int k_out, float *__restrict__ out_d2, int32_t *__restrict__ out_idx, int stack_cap, int seed,
+    const uint64_t *__restrict__ keys, int mbits)
 {
     extern __shared__ int s_stack[];
+    const int64_t t = xcd_block() * blockDim.x + threadIdx.x;
+    if (t >= m)
+        return;
+    const int64_t qi = order.perm[t];
+    if (qi < 0 || qi >= m)
+        return;
     KnnEntry spill[kSpill];
-    for (int64_t start; (start = next_block(counter, m)) >= 0;) {
-        const int64_t t = start + threadIdx.x;
-        if (t >= m)
-            continue;
-        const int64_t qi = perm[t];
-        if (qi < 0 || qi >= m)
-            continue;
-        const int b = batch_of(boff, B, qi);
-        const int tr = btree[b];
-        TopK<K> best;
-        TreeHeader h;
-        if (tr >= 0 && tr < T) {
-            h = hdrs[tr];
-        } else {
-            h.n = 0;
-            h.root = -1;
-            h.start = 0;
-        }
+    const int b = order.batch(t);
+    const int tr = b >= 0 && b < B ? btree[b] : -1;
+    TopK<K> best;
+    best.reset(INFINITY);
+    int start = 0;
+    if (tr >= 0 && tr < T) {
+        const TreeHeader &h = hdrs[tr];
+        start = h.start;
         float q[D];
 #pragma unroll
         for (int d = 0; d < D; ++d)
             q[d] = queries[qi * D + d];
         ShortStack<KnnEntry> st(reinterpret_cast<KnnEntry *>(s_stack) + threadIdx.x, blockDim.x, stack_cap, spill);
         // the seed searches this tree's segment of the forest's sorted build keys
-        const SeedKeys sk{keys, tr >= 0 && tr < T ? (uint64_t)tr << mbits : 0, mbits / D};
-        if (FMT == 1)
+        const SeedKeys sk{keys, (uint64_t)tr << mbits, mbits / D};
+        if (FMT == 1 && kind != ARBORX_BOXES && h.qinv != 0.0) {
+            TopStack<KnnCode> ts(reinterpret_cast<KnnCode *>(s_stack) + threadIdx.x, blockDim.x, stack_cap,
+                                 reinterpret_cast<KnnCode *>(spill), knn_code(-1, 0u));
+            knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, h, q, best, ts, seed, sk);
+        } else if (FMT == 1 && kind == ARBORX_BOXES)
             knn_search_q<D, K>(qnodes, n_nodes, leaves, kind, h, q, best, st, seed, sk);
         else if (FMT == 2)
             knn_search4<D, K>(nodes, wnodes, n_nodes, leaves, kind, h, q, best, st, seed, sk);
         else
             knn_search<D, K>(nodes, n_nodes, leaves, kind, h, q, best, st, seed, sk);
-        best.store(k_out, out_d2 + qi * k_out, out_idx + qi * k_out, h.start);  // indices local to the tree
     }
+    best.store(k_out, out_d2 + qi * k_out, out_idx + qi * k_out, start);  // indices local to the tree
 }
 
-// Local indices for reductions are not needed (no indices are output); kNN
-// converts above.  Workspace layout for m queries:
-//   codes[2][m] (K), ids[2][m] (u32), radix workspace, counter.
+// Workspace layout for m queries:
+//   codes[2][m] (K), ids[2][m] (u32), radix workspace.
 template <typename K>
 size_t forest_ws_bytes(int64_t m)
 {
@@ -277,10 +265,10 @@ arborx_status reserve_ws(ForestDev &f, int64_t m, hipStream_t s)
     return st;
 }
 
-// Sorted permutation of the queries (by batch, then Morton inside the batch).
+// Sorted order of the queries (by batch, then along the curve inside it).
 template <int D, typename K>
-arborx_status forest_order(const ForestDev &f, const float *q, int64_t m, const int64_t *boff, int B,
-                           const int32_t *btree, uint32_t **perm, unsigned long long **counter, hipStream_t s)
+arborx_status forest_order_keys(const ForestDev &f, const float *q, int64_t m, const int64_t *boff, int B,
+                                const int32_t *btree, int bb, ForestOrder *order, hipStream_t s)
 {
     const int64_t mm = m > 0 ? m : 1;
     uint8_t *p = static_cast<uint8_t *>(f.ws);
@@ -290,31 +278,28 @@ arborx_status forest_order(const ForestDev &f, const float *q, int64_t m, const 
     uint32_t *ids2 = ids + mm;
     uint8_t *rws = reinterpret_cast<uint8_t *>(ids2 + mm);
     rws = reinterpret_cast<uint8_t *>((reinterpret_cast<uintptr_t>(rws) + 255) & ~uintptr_t(255));
-    *counter = reinterpret_cast<unsigned long long *>(rws + radix_workspace_bytes(mm));
-    int bb = 1;
-    while ((1 << bb) < B)
-        ++bb;
     const int kbits = (int)sizeof(K) * 8 - (sizeof(K) == 8 ? 1 : 0);
     int mbits = (kbits - bb) / D * D;
     if (mbits > 8 * D)
         mbits = 8 * D;  // 8 bits per dimension order the queries of one batch well enough
     ProfScope ps("forest_order", s);
-    k_forest_codes<D, K><<<grid_for(m, 256, 65536), 256, 0, s>>>(q, m, boff, B, btree, f.T, f.hdrs, mbits, codes,
-                                                                 ids);
+    k_forest_codes<D, K><<<grid_for(m, kForestBlock, INT32_MAX), kForestBlock, 0, s>>>(q, m, boff, B, btree, f.T, f.hdrs,
+                                                                                       mbits, codes, ids);
     bool alt = false;
     AX_HIP(radix_sort_pairs<K>(codes, ids, codes2, ids2, m, 0, mbits + bb, rws, s, &alt));
-    *perm = alt ? ids2 : ids;
+    *order = ForestOrder{alt ? ids2 : ids, alt ? codes2 : codes, sizeof(K) == 8, mbits};
     return ARBORX_OK;
 }
 
-int persistent_grid(const void *kernel, int block, size_t lds)
+template <int D>
+arborx_status forest_order(const ForestDev &f, const float *q, int64_t m, const int64_t *boff, int B,
+                           const int32_t *btree, ForestOrder *order, hipStream_t s)
 {
-    int dev = 0, cus = 256, per = 1;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, block, lds) != hipSuccess || per < 1)
-        per = 1;
-    return cus * per;
+    int bb = 1;
+    while ((1 << bb) < B)
+        ++bb;
+    return bb <= 20 ? forest_order_keys<D, uint32_t>(f, q, m, boff, B, btree, bb, order, s)
+                    : forest_order_keys<D, uint64_t>(f, q, m, boff, B, btree, bb, order, s);
 }
 
 template <int D>
@@ -322,75 +307,55 @@ arborx_status forest_reduce_impl(ForestDev &f, const float *q, int64_t m, const 
                                  const float *brad, int B, int op, int scale_bits, int32_t *counts, int64_t *sums,
                                  hipStream_t s)
 {
-    uint32_t *perm;
-    unsigned long long *counter;
-    int bb = 1;
-    while ((1 << bb) < B)
-        ++bb;
-    arborx_status st = bb <= 20 ? forest_order<D, uint32_t>(f, q, m, boff, B, btree, &perm, &counter, s)
-                                : forest_order<D, uint64_t>(f, q, m, boff, B, btree, &perm, &counter, s);
+    ForestOrder order;
+    arborx_status st = forest_order<D>(f, q, m, boff, B, btree, &order, s);
     if (st != ARBORX_OK)
         return st;
-    fill_kernel<unsigned long long><<<1, 64, 0, s>>>(counter, 1, 0ull);
     const Tuning &tu = tuning(OP_REDUCE);
     int block_unused = 0, cap = 0;
     launch_shape(OP_REDUCE, D, block_unused, cap);
     while (cap > 1 && (size_t)cap * kForestBlock * sizeof(int) > 65536)
         cap >>= 1;
-    const size_t lds = (size_t)cap * kForestBlock * sizeof(int);
+    const size_t lds = (size_t)(cap > 2 ? cap : 2) * kForestBlock * sizeof(int);  // a TopStack has at least two slots
     const float scale = ldexpf(1.0f, scale_bits);
     ProfScope ps(op == ARBORX_COUNT_SUMDIST ? "forest_reduce_sumdist" : "forest_reduce_count", s);
     const Node<D> *nodes = static_cast<const Node<D> *>(f.nodes);
     const QNode<D> *qnodes = static_cast<const QNode<D> *>(f.qnodes);
     const Node4<D> *wnodes = static_cast<const Node4<D> *>(f.wnodes);
     const int nn = (int)(f.n > 0 ? f.n : 1);
-    const int fmt = node_format(OP_REDUCE, D, f.kind, true);
-    const int nq = tu.packet ? tu.packet : (D <= 3 ? 4 : 1);
-    if (fmt == 0 && nq > 1) {
-#define AX_FRP(SD, N)                                                                                            \
-    do {                                                                                                         \
-        const int grid = persistent_grid((const void *)k_forest_reduce_packet<D, SD, N>, kForestBlock, lds);    \
-        k_forest_reduce_packet<D, SD, N><<<grid, kForestBlock, lds, s>>>(nodes, nn, f.hdrs, f.T, q, m, perm, boff, B, \
-                                                                         btree, brad, scale, counts, sums, counter, cap); \
+    const int fmt = forest_format(OP_REDUCE, f);
+    // as for single trees: up to 3D 4 queries a thread on float nodes and 2 on quantized ones
+    int nq = tu.packet ? tu.packet : (D <= 3 ? (fmt == 1 ? 2 : 4) : 1);
+    if (fmt == 2)
+        nq = 1;
+    else if (fmt == 1 && nq > 2)
+        nq = 2;
+#define AX_FR(SD, N, F)                                                                                          \
+    k_forest_reduce<D, SD, N, F><<<grid_for((m + N - 1) / N, kForestBlock, INT32_MAX), kForestBlock, lds, s>>>(  \
+        nodes, qnodes, wnodes, f.leaves, f.kind, nn, f.hdrs, f.T, q, m, order, B, btree, brad, scale, counts,    \
+        sums, cap)
+#define AX_FR_NODES(SD)           \
+    do {                          \
+        if (fmt == 2)             \
+            AX_FR(SD, 1, 2);      \
+        else if (fmt == 1) {      \
+            if (nq == 2)          \
+                AX_FR(SD, 2, 1);  \
+            else                  \
+                AX_FR(SD, 1, 1);  \
+        } else if (nq == 4)       \
+            AX_FR(SD, 4, 0);      \
+        else if (nq == 2)         \
+            AX_FR(SD, 2, 0);      \
+        else                      \
+            AX_FR(SD, 1, 0);      \
     } while (0)
-        if (op == ARBORX_COUNT_SUMDIST) {
-            if (nq == 2)
-                AX_FRP(true, 2);
-            else
-                AX_FRP(true, 4);
-        } else {
-            if (nq == 2)
-                AX_FRP(false, 2);
-            else
-                AX_FRP(false, 4);
-        }
-#undef AX_FRP
-        AX_HIP(hipGetLastError());
-        return ARBORX_OK;
-    }
-#define AX_FREDUCE(SD, F)                                                                                        \
-    do {                                                                                                         \
-        const int grid = persistent_grid((const void *)k_forest_reduce<D, SD, F>, kForestBlock, lds);           \
-        k_forest_reduce<D, SD, F><<<grid, kForestBlock, lds, s>>>(nodes, qnodes, wnodes, f.leaves, f.kind, nn, f.hdrs, \
-                                                                  f.T, q, m, perm, boff, B, btree, brad, scale,  \
-                                                                  counts, sums, counter, cap);                 \
-    } while (0)
-    if (op == ARBORX_COUNT_SUMDIST) {
-        if (fmt == 1)
-            AX_FREDUCE(true, 1);
-        else if (fmt == 2)
-            AX_FREDUCE(true, 2);
-        else
-            AX_FREDUCE(true, 0);
-    } else {
-        if (fmt == 1)
-            AX_FREDUCE(false, 1);
-        else if (fmt == 2)
-            AX_FREDUCE(false, 2);
-        else
-            AX_FREDUCE(false, 0);
-    }
-#undef AX_FREDUCE
+    if (op == ARBORX_COUNT_SUMDIST)
+        AX_FR_NODES(true);
+    else
+        AX_FR_NODES(false);
+#undef AX_FR_NODES
+#undef AX_FR
     AX_HIP(hipGetLastError());
     return ARBORX_OK;
 }
@@ -399,32 +364,25 @@ template <int D, int K>
 arborx_status forest_knn_launch(ForestDev &f, const float *q, int64_t m, const int64_t *boff, const int32_t *btree,
                                 int B, int k, float *d2, int32_t *idx, hipStream_t s)
 {
-    uint32_t *perm;
-    unsigned long long *counter;
-    int bb = 1;
-    while ((1 << bb) < B)
-        ++bb;
-    arborx_status st = bb <= 20 ? forest_order<D, uint32_t>(f, q, m, boff, B, btree, &perm, &counter, s)
-                                : forest_order<D, uint64_t>(f, q, m, boff, B, btree, &perm, &counter, s);
+    ForestOrder order;
+    arborx_status st = forest_order<D>(f, q, m, boff, B, btree, &order, s);
     if (st != ARBORX_OK)
         return st;
-    fill_kernel<unsigned long long><<<1, 64, 0, s>>>(counter, 1, 0ull);
     const Tuning &tu = tuning(OP_KNN);
-    const int fmt = node_format(OP_KNN, D, f.kind, true);
-    int block_unused = 0, cap = 0;
-    launch_shape(OP_KNN, D, block_unused, cap);
-    while (cap > 1 && (size_t)cap * kForestBlock * sizeof(KnnEntry) > 65536)
+    const int fmt = forest_format(OP_KNN, f);
+    int block = 0, cap = 0;
+    launch_shape(OP_KNN, D, block, cap);
+    if (block > kForestBlock)
+        block = kForestBlock;
+    while (cap > 1 && (size_t)cap * block * sizeof(KnnEntry) > 65536)
         cap >>= 1;
-    const size_t lds = (size_t)cap * kForestBlock * sizeof(KnnEntry);
+    const size_t lds = (size_t)(cap > 2 ? cap : 2) * block * sizeof(KnnEntry);
     ProfScope ps("forest_knn", s);
-#define AX_FKNN(F)                                                                                                 \
-    do {                                                                                                           \
-        const int grid = persistent_grid((const void *)k_forest_knn<D, K, F>, kForestBlock, lds);                 \
-        k_forest_knn<D, K, F><<<grid, kForestBlock, lds, s>>>(                                                    \
-            static_cast<const Node<D> *>(f.nodes), static_cast<const QNode<D> *>(f.qnodes),                        \
-            static_cast<const Node4<D> *>(f.wnodes), (int)(f.n > 0 ? f.n : 1), f.leaves, f.kind, f.hdrs, f.T, q, m, \
-            perm, boff, B, btree, k, d2, idx, counter, cap, tu.seed, f.keys, f.mbits);                             \
-    } while (0)
+#define AX_FKNN(F)                                                                                                  \
+    k_forest_knn<D, K, F><<<grid_for(m, block, INT32_MAX), block, lds, s>>>(                                        \
+        static_cast<const Node<D> *>(f.nodes), static_cast<const QNode<D> *>(f.qnodes),                             \
+        static_cast<const Node4<D> *>(f.wnodes), (int)(f.n > 0 ? f.n : 1), f.leaves, f.kind, f.hdrs, f.T, q, m,     \
+        order, B, btree, k, d2, idx, cap, tu.seed, f.keys, f.mbits)
     if (fmt == 1)
         AX_FKNN(1);
     else if (fmt == 2)
@@ -463,7 +421,7 @@ arborx_status forest_query_reduce(ForestDev &f, const float *q, int64_t m, const
 {
     if (m == 0)
         return ARBORX_OK;
-    arborx_status st = check_nodes(f.qnodes, f.wnodes, f.n, node_format(OP_REDUCE, f.dim, f.kind, true));
+    arborx_status st = check_nodes(f.qnodes, f.wnodes, f.n, forest_format(OP_REDUCE, f));
     if (st == ARBORX_OK)
         st = reserve_ws(f, m, s);
     if (st != ARBORX_OK)
@@ -481,7 +439,7 @@ arborx_status forest_query_knn(ForestDev &f, const float *q, int64_t m, const in
 {
     if (m == 0)
         return ARBORX_OK;
-    arborx_status st = check_nodes(f.qnodes, f.wnodes, f.n, node_format(OP_KNN, f.dim, f.kind, true));
+    arborx_status st = check_nodes(f.qnodes, f.wnodes, f.n, forest_format(OP_KNN, f));
     if (st == ARBORX_OK)
         st = reserve_ws(f, m, s);
     if (st != ARBORX_OK)

@@ -215,6 +215,9 @@ struct ForestDev {
     size_t bws_bytes = 0;
     int max_tiles = 0;         // upper bound of the build's per-tree tiles: n / tile + T + 1
 };
+// As tree_format, for the walks over a forest.
+int forest_format(int op, const ForestDev &f);
+int forest_format(const Tuning &t, int op, arborx_forest forest);
 arborx_status build_forest(const float *values, const int64_t *seg_host, int T, int dim, int kind, ForestDev &f,
                            hipStream_t s);
 // Every allocation of a forest of n values in T trees (structure and build
