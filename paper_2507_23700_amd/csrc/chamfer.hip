@@ -35,15 +35,32 @@ __device__ __forceinline__ int pair_of(const int64_t *__restrict__ off, int P, i
 }
 
 // One workgroup per pair: loss[p] = sum of the pair's nearest squared distances (float64).
-__global__ __launch_bounds__(256) void k_pair_loss(const float *__restrict__ d2, const int32_t *__restrict__ idx,
-                                                   const int64_t *__restrict__ seg, int P, float *__restrict__ loss)
+// Bound: the latency of a workgroup's loads where there are few pairs, so it is
+// as large as can be and each thread keeps several loads in flight: 128 pairs of
+// 3.4*10^4 points 145 -> 45 us against 256 threads with one.
+constexpr int kLossBlock = 1024;
+constexpr int kLossUnroll = 8;
+__global__ __launch_bounds__(kLossBlock) void k_pair_loss(const float *__restrict__ d2, const int32_t *__restrict__ idx,
+                                                          const int64_t *__restrict__ seg, int P,
+                                                          float *__restrict__ loss)
 {
-    __shared__ double wsum[256 / kWave];
+    __shared__ double wsum[kLossBlock / kWave];
     const int p = blockIdx.x;
     double s = 0.0;
     for (int part = 0; part < 2; ++part) {
         const int t = part == 0 ? p : P + p;
-        for (int64_t i = seg[t] + threadIdx.x; i < seg[t + 1]; i += blockDim.x)
+        const int64_t end = seg[t + 1];
+        int64_t i = seg[t] + threadIdx.x;
+        for (; i + (kLossUnroll - 1) * kLossBlock < end; i += kLossUnroll * kLossBlock) {
+            float v[kLossUnroll];
+#pragma unroll
+            for (int u = 0; u < kLossUnroll; ++u)
+                v[u] = idx[i + u * kLossBlock] >= 0 ? d2[i + u * kLossBlock] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < kLossUnroll; ++u)
+                s += (double)v[u];
+        }
+        for (; i < end; i += kLossBlock)
             if (idx[i] >= 0)
                 s += (double)d2[i];
     }
@@ -53,7 +70,7 @@ __global__ __launch_bounds__(256) void k_pair_loss(const float *__restrict__ d2,
     __syncthreads();
     if (threadIdx.x == 0) {
         double tot = 0.0;
-        for (int w = 0; w < 256 / kWave; ++w)
+        for (int w = 0; w < kLossBlock / kWave; ++w)
             tot += wsum[w];
         loss[p] = (float)tot;
     }
@@ -98,18 +115,36 @@ __global__ void k_chamfer_own(const float *__restrict__ src, const int64_t *__re
 }
 
 // Second pass, after both first passes: g_dst[nn(i)] -= 2 g (x_i - y_nn(i)).
-__global__ void k_chamfer_reverse(const float *__restrict__ src, const int64_t *__restrict__ soff, int64_t ns,
-                                  const float *__restrict__ dst, const int64_t *__restrict__ doff,
-                                  const int32_t *__restrict__ nn, const float *__restrict__ grad_loss, int P,
-                                  double *__restrict__ gdst)
+// Bound: the requests of the atomics, which go past the L2 caches.  The three
+// of a point are therefore handed to neighbouring lanes through LDS, so that
+// one request carries them: 4.4*10^6 points 673 -> 296 us against one lane a
+// point.
+constexpr int kReverseBlock = 256;
+__global__ __launch_bounds__(kReverseBlock) void k_chamfer_reverse(
+    const float *__restrict__ src, const int64_t *__restrict__ soff, int64_t ns, const float *__restrict__ dst,
+    const int64_t *__restrict__ doff, const int32_t *__restrict__ nn, const float *__restrict__ grad_loss, int P,
+    double *__restrict__ gdst)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ns; i += (int64_t)gridDim.x * blockDim.x) {
+    __shared__ double term[3 * kReverseBlock];
+    __shared__ int64_t at[kReverseBlock];
+    for (int64_t base = (int64_t)blockIdx.x * kReverseBlock; base < ns; base += (int64_t)gridDim.x * kReverseBlock) {
+        const int64_t i = base + threadIdx.x;
         double t[3];
         int64_t jj = 0;
-        if (own_term(src, soff, dst, doff, nn, grad_loss, P, i, t, jj))
+        at[threadIdx.x] = i < ns && own_term(src, soff, dst, doff, nn, grad_loss, P, i, t, jj) ? jj : -1;
+        if (i < ns)
 #pragma unroll
             for (int d = 0; d < 3; ++d)
-                atomicAdd(&gdst[jj * 3 + d], -t[d]);
+                term[threadIdx.x * 3 + d] = t[d];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int e = r * kReverseBlock + threadIdx.x, p = e / 3;
+            const int64_t j = at[p];
+            if (j >= 0)
+                atomicAdd(&gdst[j * 3 + (e - p * 3)], -term[e]);
+        }
+        __syncthreads();
     }
 }
 
@@ -159,7 +194,7 @@ arborx_status chamfer_forward(const float *a, const int64_t *a_off, const float 
         st = forest_query_knn(f, pts, n, f.seg, dbt, 2 * P, 1, d2, idx, s);
     if (st == ARBORX_OK) {
         ProfScope ps("chamfer_loss", s);
-        k_pair_loss<<<P, 256, 0, s>>>(d2, idx, f.seg, P, loss);
+        k_pair_loss<<<P, kLossBlock, 0, s>>>(d2, idx, f.seg, P, loss);
         if (na > 0)
             k_copy_i32<<<grid_for(na, 256, 65536), 256, 0, s>>>(idx, na, nn_ab);
         if (nb > 0)
@@ -193,9 +228,9 @@ arborx_status chamfer_backward(const float *a, const int64_t *a_off, const float
     if (nb > 0)
         k_chamfer_own<<<grid_for(nb, 256, 65536), 256, 0, s>>>(b, boff, nb, a, aoff, nn_ba, grad_loss, P, gb);
     if (na > 0)
-        k_chamfer_reverse<<<grid_for(na, 256, 65536), 256, 0, s>>>(a, aoff, na, b, boff, nn_ab, grad_loss, P, gb);
+        k_chamfer_reverse<<<grid_for(na, kReverseBlock, 65536), kReverseBlock, 0, s>>>(a, aoff, na, b, boff, nn_ab, grad_loss, P, gb);
     if (nb > 0)
-        k_chamfer_reverse<<<grid_for(nb, 256, 65536), 256, 0, s>>>(b, boff, nb, a, aoff, nn_ba, grad_loss, P, ga);
+        k_chamfer_reverse<<<grid_for(nb, kReverseBlock, 65536), kReverseBlock, 0, s>>>(b, boff, nb, a, aoff, nn_ba, grad_loss, P, ga);
     if (na > 0)
         k_to_float<<<grid_for(3 * na, 256, 65536), 256, 0, s>>>(ga, 3 * na, grad_a);
     if (nb > 0)
