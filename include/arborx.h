@@ -83,14 +83,14 @@ typedef struct arborx_tuning {
                              per fetch).  Every format gives identical results.  Formats 1 and 2 are built only
                              while some operation asks for them when the tree is built; asking later is
                              ARBORX_E_INVALID.  The defaults (arborx_set_tuning(NULL)): 1 for ARBORX_OP_SPATIAL
-                             and ARBORX_OP_REDUCE, 0 for ARBORX_OP_KNN, over trees of points; under them a
-                             kNN over points also walks format 1, while trees of boxes, forests and a tree built
-                             without format 1 are walked on format 0 */
+                             and ARBORX_OP_REDUCE, 0 for ARBORX_OP_KNN, over trees and forests of points; under
+                             them a kNN over points also walks format 1, while trees and forests of boxes, and
+                             ones built without format 1, are walked on format 0 */
     int32_t queries_per_thread; /* radius searches (CSR count pass of sphere queries, fused reductions) with
                                    the thread schedule on binary nodes: 1, 2 or 4 Morton-neighbouring queries
                                    answered by one thread in one walk over the union of their paths; 0 = by
                                    operation, dimension and format (up to 3D: 2 for CSR; for reductions 4 on
-                                   format 0, 2 on format 1; 1 in 6D).  Defaults: 1 for ARBORX_OP_SPATIAL, 0
+                                   format 0, 1 on format 1; 1 in 6D).  Defaults: 1 for ARBORX_OP_SPATIAL, 0
                                    otherwise */
 } arborx_tuning;
 

@@ -12,7 +12,7 @@
 // 512 batches of 6.5*10^6 queries in all on 32 trees of 9.4*10^6 points, against a
 // persistent grid over float nodes that took 256 sorted queries at a time from
 // an atomic counter, spread every tree over all eight L2 caches and searched
-// each query's batch: k = 8 3.8 -> 3.0 ms, count with distances 2.7 -> 1.85.
+// each query's batch: k = 8 3.8 -> 3.0 ms, count with distances 2.7 -> 1.65.
 // The query path allocates nothing once the forest's workspace is reserved, and
 // never synchronises, so it can be captured in a hipGraph.  Results use indices
 // local to the target tree (value index minus the tree's first value), the
@@ -324,8 +324,8 @@ arborx_status forest_reduce_impl(ForestDev &f, const float *q, int64_t m, const 
     const Node4<D> *wnodes = static_cast<const Node4<D> *>(f.wnodes);
     const int nn = (int)(f.n > 0 ? f.n : 1);
     const int fmt = forest_format(OP_REDUCE, f);
-    // as for single trees: up to 3D 4 queries a thread on float nodes and 2 on quantized ones
-    int nq = tu.packet ? tu.packet : (D <= 3 ? (fmt == 1 ? 2 : 4) : 1);
+    // as for single trees: up to 3D 4 queries a thread on float nodes; 1 on quantized ones
+    int nq = tu.packet ? tu.packet : (D <= 3 && fmt != 1 ? 4 : 1);
     if (fmt == 2)
         nq = 1;
     else if (fmt == 1 && nq > 2)

@@ -49,7 +49,7 @@ struct Tuning {
     int nodes = 0;  // 0: binary float, 1: binary with quantized 16-bit child boxes (exact leaf tests), 2: four-wide
     int packet = 0; // radius walks on binary nodes: queries per thread (1, 2 or 4) walked together; 0 = by
                     // operation, dimension and format (up to 3D, where neighbouring paths overlap most: for
-                    // the fused reductions 4 on float nodes, 2 on quantized ones; 2 for the CSR count; 1 in
+                    // the fused reductions 4 on float nodes, 1 on quantized ones; 2 for the CSR count; 1 in
                     // 6D)
     bool by_dim = false;  // the library's defaults: block and stack also follow the dimension (launch_shape)
 };

@@ -980,10 +980,27 @@ struct Launch {
     size_t lds;
 };
 
+// The chip has 256 compute units; a launch with less than two workgroups for
+// each is bound by its longest chain of node visits, which is the longest over
+// the lanes of a wavefront.  Under the defaults its workgroups are halved until
+// there are as many, down to kSmallBlock lanes of one wavefront, and the stack
+// is as deep as a walk is likely to need (occupancy does not matter here): k =
+// 10 of 1000 queries on 2*10^4 points 82 -> 74 us, of 2*10^4 91 -> 85, CSR of
+// 1000 queries 141 -> 120.  With the line at 1024 or 256 workgroups k = 10 of
+// 2*10^4 queries took 88 and 92.
+constexpr int64_t kFillBlocks = 512;
+constexpr int kSmallBlock = 8;
+constexpr int kSmallStack = 32;
+
 Launch traversal_launch(int64_t m, size_t entry_bytes, int op, int dim, bool wave = false)
 {
     Launch L;
     launch_shape(op, dim, L.block, L.cap);
+    if (tuning(op).by_dim && !wave && (m + kWave - 1) / kWave < kFillBlocks) {
+        L.cap = kSmallStack;
+        while (L.block > kSmallBlock && (m + L.block - 1) / L.block < kFillBlocks)
+            L.block >>= 1;
+    }
     L.grid = (unsigned)((m + L.block - 1) / L.block);
     while (L.cap > 1 && (size_t)L.cap * L.block * entry_bytes > 65536)
         L.cap >>= 1;
@@ -1166,7 +1183,9 @@ arborx_status reduce_impl(const TreeDev &t, const float *q, int64_t m, float r2,
                           const uint32_t *perm, int32_t *counts, int64_t *sums, hipStream_t s)
 {
     const int sched = effective_schedule(OP_REDUCE, t);
-    const int nq = tuning(OP_REDUCE).packet ? tuning(OP_REDUCE).packet : (D <= 3 ? (sched == 3 ? 2 : 4) : 1);
+    // queries a thread walks together: neighbours share most float nodes, but a step in codes costs too little to
+    // carry a second query: one instead of two, 10^6 queries with distances 286 -> 226 us, 2*10^4 97 -> 56
+    const int nq = tuning(OP_REDUCE).packet ? tuning(OP_REDUCE).packet : (D <= 3 && sched != 3 ? 4 : 1);
     if ((sched == 0 || sched == 3) && nq > 1) {  // NQ queries per thread over binary nodes
         const Launch L = traversal_launch((m + nq - 1) / nq, sizeof(int), OP_REDUCE, D);
         const Node<D> *nodes = static_cast<const Node<D> *>(t.nodes);
