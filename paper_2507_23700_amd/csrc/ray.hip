@@ -68,9 +68,9 @@ __global__ void k_ray_nearest(const Node<D> *__restrict__ nodes, const TreeHeade
         Node<D> nd;
         load_node(nodes, cur, nd);
         float t0, t1;
-        const bool h0 = p.hit(nd.lo[0], nd.hi[0], t0);
-        const bool h1 = p.hit(nd.lo[1], nd.hi[1], t1);
         const int c0 = nd.child[0], c1 = nd.child[1];
+        const bool h0 = child_hit<D>(p, nd.lo[0], nd.hi[0], c0, t0);  // an internal child's t is a lower bound
+        const bool h1 = child_hit<D>(p, nd.lo[1], nd.hi[1], c1, t1);
         if (h0 && c0 < 0 && c0 != kEmptyRef)
             best.offer(t0, ~c0);
         if (h1 && c1 < 0 && c1 != kEmptyRef)

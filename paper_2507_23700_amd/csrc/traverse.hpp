@@ -192,16 +192,27 @@ __device__ __forceinline__ float point_d2(const float *q, const uint32_t (&w)[D]
 // division, a zero direction component requiring lo <= o <= hi.  The entry
 // parameter tmin is reported in the distance slot.  Subtraction and division
 // are monotone, so a box inside another is met no earlier: pruning by a
-// parent's box is exact.
+// parent's box is exact.  An internal box only has to be entered whenever that
+// test passes, so reach() multiplies by 1/dir and widens the result: t' =
+// fl(x fl(1/dir)) is within a factor 1 +- 2^-22 of fl(x/dir), or 2^-147 where it
+// is that small.  The walks divide for leaf boxes that pass reach() alone: a
+// correctly rounded division is about ten instructions, and a step had twelve
+// in 3D: the all-hits walk of 3*10^5 rays over 10^6 boxes 2.78 -> 2.41 ms.  Rays
+// with components for which the bound does not hold take hit().
 template <int D>
 struct RayPred {
-    float o[D], dir[D];
+    float o[D], dir[D], inv[D];
+    bool plain;  // reach() may multiply
     __device__ __forceinline__ void load(const float *rays, int64_t i, float)
     {
+        plain = true;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             o[d] = rays[i * 2 * D + d];
             dir[d] = rays[i * 2 * D + D + d];
+            const float a = fabsf(dir[d]);
+            plain = plain && fabsf(o[d]) < INFINITY && (a == 0.0f || (a >= 0x1p-100f && a <= 0x1p100f));
+            inv[d] = 1.0f / dir[d];
         }
     }
     __device__ __forceinline__ void dead()  // origin at +inf, no direction: outside every finite box
@@ -209,8 +220,31 @@ struct RayPred {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             o[d] = INFINITY;
-            dir[d] = 0.0f;
+            dir[d] = inv[d] = 0.0f;
         }
+        plain = false;
+    }
+    // True whenever hit() is, with t at most its t.  A NaN bound of a box acts as in hit().
+    __device__ __forceinline__ bool reach(const float *lo, const float *hi, float &t) const
+    {
+        if (!plain)
+            return hit(lo, hi, t);
+        float tmin = 0.0f, tmax = INFINITY;
+        bool inside = true;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            if (dir[k] == 0.0f) {
+                inside = inside && !(o[k] < lo[k] || o[k] > hi[k]);
+                continue;
+            }
+            const float t1 = (lo[k] - o[k]) * inv[k];
+            const float t2 = (hi[k] - o[k]) * inv[k];
+            const bool up = t1 < t2;
+            tmin = fmaxf(tmin, up ? t1 : t2);
+            tmax = fminf(tmax, up ? t2 : t1);
+        }
+        t = fmaf(tmin, 1.0f - 0x1p-20f, -0x1p-120f);
+        return inside && tmin <= fmaf(tmax, 1.0f + 0x1p-20f, 0x1p-120f);
     }
     __device__ __forceinline__ bool hit(const float *lo, const float *hi, float &t) const
     {
@@ -232,6 +266,25 @@ struct RayPred {
         return inside && !(tmin > tmax);
     }
 };
+
+// The predicate's first test of a node's child box, and its test of one with
+// child reference ref: for rays reach(), and for leaf boxes that pass it hit().
+template <int D, class P>
+__device__ __forceinline__ bool first_hit(const P &pred, const float *lo, const float *hi, float &d)
+{
+    if constexpr (std::is_same<P, RayPred<D>>::value)
+        return pred.reach(lo, hi, d);
+    else
+        return pred.hit(lo, hi, d);
+}
+template <int D, class P>
+__device__ __forceinline__ bool child_hit(const P &pred, const float *lo, const float *hi, int ref, float &d)
+{
+    bool h = first_hit<D>(pred, lo, hi, d);
+    if (std::is_same<P, RayPred<D>>::value && h && ref < 0)
+        h = pred.hit(lo, hi, d);
+    return h;
+}
 
 // Exact test of the sorted leaf record `pos` (the value's own box) against
 // the predicate, calling f(index, d2) on a match.
@@ -257,6 +310,9 @@ struct NeverStop {
 // Depth-first walk calling f(index, d2) on every matching value; with a stop
 // functor, the walk ends as soon as stop() holds after a node's matches were
 // reported (the early termination of Section 2.2).
+// The next node is chosen and its fetch issued before the matches are reported
+// (and a ray's leaf boxes divided for): 10^5 2D rays over 3*10^5 boxes 6.1 ->
+// 5.2 ms, box overlaps of 10^6 2D boxes 190 -> 186 us.
 // A depth-first walk enters each internal node at most once, so `limit`
 // iterations (more than the node count) bound every walk even on a corrupt
 // tree, and node indices are range-checked before use.
@@ -264,39 +320,35 @@ template <int D, class P, class F, class S = NeverStop>
 __device__ __forceinline__ void traverse_spatial(const Node<D> *__restrict__ nodes, int root, int n_nodes,
                                                  const P &pred, ShortStack<int> &st, F &f, const S &stop = S())
 {
+    constexpr bool two = std::is_same<P, RayPred<D>>::value;  // leaf boxes that pass the first test take a second
+    const unsigned last = (unsigned)n_nodes - 1u;
     int cur = root;
+    Node<D> nd;
+    load_node(nodes, (int)min((unsigned)cur, last), nd);
     for (int iter = 0; iter <= n_nodes; ++iter) {
-        if ((unsigned)cur >= (unsigned)n_nodes)
+        if ((unsigned)cur > last)
             break;
-        Node<D> nd;
-        load_node(nodes, cur, nd);
+        const Node<D> at = nd;
         float d0, d1;
-        bool h0 = pred.hit(nd.lo[0], nd.hi[0], d0);
-        bool h1 = pred.hit(nd.lo[1], nd.hi[1], d1);
-        const int c0 = nd.child[0], c1 = nd.child[1];
-        if (h0 && c0 < 0) {
-            if (c0 != kEmptyRef)
-                f(~c0, d0);
-            h0 = false;
-        }
-        if (h1 && c1 < 0) {
-            if (c1 != kEmptyRef)
-                f(~c1, d1);
-            h1 = false;
-        }
-        if (stop())
-            break;
-        if (h0) {
-            if (h1)
+        const int c0 = at.child[0], c1 = at.child[1];
+        const bool h0 = first_hit<D>(pred, at.lo[0], at.hi[0], d0);
+        const bool h1 = first_hit<D>(pred, at.lo[1], at.hi[1], d1);
+        if (h0 && c0 >= 0) {
+            if (h1 && c1 >= 0)
                 st.push(c1);
             cur = c0;
-        } else if (h1) {
+        } else if (h1 && c1 >= 0) {
             cur = c1;
         } else {
-            if (st.empty())
-                break;
-            cur = st.pop();
+            cur = st.empty() ? -1 : st.pop();
         }
+        load_node(nodes, (int)min((unsigned)cur, last), nd);  // in flight while the matches below are reported
+        if (h0 && c0 < 0 && c0 != kEmptyRef && (!two || pred.hit(at.lo[0], at.hi[0], d0)))
+            f(~c0, d0);
+        if (h1 && c1 < 0 && c1 != kEmptyRef && (!two || pred.hit(at.lo[1], at.hi[1], d1)))
+            f(~c1, d1);
+        if (stop())
+            break;
     }
 }
 
@@ -619,9 +671,10 @@ __device__ __forceinline__ void traverse_spatial_q(const QNode<D> *__restrict__ 
         float lo[2][D], hi[2][D];
         qboxes<D>(nd, points, flo, fsc, lo, hi);
         float d0, d1;
-        bool h0 = pred.hit(lo[0], hi[0], d0);
-        bool h1 = pred.hit(lo[1], hi[1], d1);
         const int c0 = nd.child[0], c1 = nd.child[1];
+        // a box tree's leaf box is decided by leaf_exact
+        bool h0 = child_hit<D>(pred, lo[0], hi[0], points ? c0 : 0, d0);
+        bool h1 = child_hit<D>(pred, lo[1], hi[1], points ? c1 : 0, d1);
         if (h0 && c0 < 0) {
             if (c0 != kEmptyRef) {
                 if (points)
