@@ -15,13 +15,12 @@
 // DBSCAN, two passes over the pairs:
 //   1. pair counts: a point is core when its pairs plus itself reach min_pts;
 //   2. one pair walk: core-core pairs are united in a lock-free union-find
-//      over value indices whose links always go from the larger root to the
-//      smaller, so each cluster's root ends as its smallest core index (over
-//      sorted positions instead, the lanes of a wavefront, Morton neighbours,
-//      contend for the same few roots: eight times slower at 10^7 points); each
-//      non-core point keeps the smallest index among its core partners
-//      (atomic minimum, from whichever side of the pair meets it);
-// then labels: a core point takes its root, a non-core point the label of its
+//      over sorted positions whose links always go from the root of higher rank
+//      to the one of lower (a scrambled position, see rank_of); each non-core
+//      point keeps the smallest index among its core partners (atomic minimum,
+//      from whichever side of the pair meets it);
+// then labels: a cluster's smallest core index is gathered at its root, every
+// core point takes its root's, a non-core point the label of its
 // smallest-index core partner, or -1 (noise).  Labelling by smallest indices
 // makes the result unique, so it is compared with a brute-force definition
 // element by element.
@@ -139,9 +138,21 @@ __global__ void k_to_input_order(const int32_t *__restrict__ by_pos, const float
     }
 }
 
+// The order in which positions may link: a one-to-one scramble.  The links of
+// Morton neighbours lie close together, as their points do, and are found in
+// the caches (over value indices the walk of 5*10^6 cube points took 2.58 ms,
+// over positions 2.26).  Ordered by the position itself, neighbours form
+// chains and contend for the same few roots: eight times slower at 10^7 points.
+__device__ __forceinline__ uint32_t rank_of(int32_t x)
+{
+    uint32_t h = (uint32_t)x * 0x9e3779b1u;
+    h ^= h >> 15;
+    return h * 0x85ebca77u;
+}
+
 // Parent links are read and shortened with workgroup-scope accesses, which
 // the per-XCD L2 serves, so another XCD's recent link may not be visible yet.
-// That is safe: links only ever go from a value to a smaller value of the same
+// That is safe: links only ever go from a value to one of lower rank in the same
 // component and are never undone, so a stale parent is still an ancestor, and
 // a stale root is caught by the exchange in unite, which is device-wide and
 // returns the true parent.
@@ -150,14 +161,14 @@ __device__ __forceinline__ int32_t load_parent(const int32_t *parent, int32_t x)
     return __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Root of x.  Every link points to a smaller index (unions link the larger
-// root to the smaller; shortcuts below point a node at a smaller member of its
-// own chain), so a chain strictly decreases and ends at a root.  The nodes
-// above the root found are then pointed at it: they are not roots (and never
-// become roots again), and the root is a smaller member of the same
-// component, so the links still decrease.  Another thread may have shortcut a
-// node past r meanwhile; the walk stops at the first node not above r, so it
-// never points a smaller node at a larger one.
+// Root of x.  Every link points to a lower rank (unions link the root of higher
+// rank to the lower; shortcuts below point a node at a lower member of its own
+// chain), so a chain strictly decreases and ends at a root.  The nodes above
+// the root found are then pointed at it: they are not roots (and never become
+// roots again), and the root is a lower member of the same component, so the
+// links still decrease.  Another thread may have shortcut a node past r
+// meanwhile; the walk stops at the first node not above r, so it never points a
+// lower node at a higher one.
 __device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t x)
 {
     int32_t r = x, p = load_parent(parent, r);
@@ -165,7 +176,8 @@ __device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t x)
         r = p;
         p = load_parent(parent, r);
     }
-    while (x > r) {
+    const uint32_t floor = rank_of(r);
+    while (rank_of(x) > floor) {
         const int32_t next = load_parent(parent, x);
         if (next != r)
             __hip_atomic_store(parent + x, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -174,13 +186,13 @@ __device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t x)
     return r;
 }
 
-// Link the components of a and b: the larger root is pointed at the smaller
-// by a device-wide exchange.  When it fails, the value it returns is that
-// root's true parent, smaller than it, and the walk goes on from there; so
-// every failure moves one of the two ends to a smaller index, and at most 2n
-// rounds finish.  Returns the root the merged component had when the link
-// was made: an ancestor of both a and b from then on (links are never
-// undone), so a caller may start its next find there instead of at a.
+// Link the components of a and b: the root of higher rank is pointed at the
+// other by a device-wide exchange.  When it fails, the value it returns is that
+// root's true parent, of lower rank, and the walk goes on from there; so every
+// failure moves one of the two ends to a lower rank, and at most 2n rounds
+// finish.  Returns the root the merged component had when the link was made: an
+// ancestor of both a and b from then on (links are never undone), so a caller
+// may start its next find there instead of at a.
 __device__ __forceinline__ int32_t unite(int32_t *parent, int32_t a, int32_t b, int64_t n)
 {
     a = find_root(parent, a);
@@ -188,7 +200,7 @@ __device__ __forceinline__ int32_t unite(int32_t *parent, int32_t a, int32_t b, 
     for (int64_t iter = 0; iter <= 2 * n + 1; ++iter) {
         if (a == b)
             return a;
-        if (a < b) {
+        if (rank_of(a) < rank_of(b)) {
             const int32_t t = a;
             a = b;
             b = t;
@@ -210,9 +222,18 @@ __global__ void k_dbscan_init(int32_t *__restrict__ parent, int32_t *__restrict_
     }
 }
 
+// Matches a thread of the walk over codes holds in LDS before the wavefront
+// turns to their links together.  A match costs a chain of two to five dependent
+// loads, and some lane of a wavefront matches in nearly every step of the walk:
+// 5*10^6 cube points 2.26 ms at once, 2.09 with a look at the partner's link
+// beside its degree, 1.94 with the queue (the pair counts alone, over the same
+// walk, take 0.86).  Linking each point to its next three in sorted order first
+// took as long as it saved.
+constexpr int kPairQueue = 8;
+
 // Pass 2: one pair walk, NQ leaves per thread (NQ = 0: the rope walk; Q: one
-// leaf per thread over the quantized nodes).  parent is indexed by value
-// index, deg and border by sorted position.
+// leaf per thread over the quantized nodes).  parent, deg and border are
+// indexed by sorted position.
 template <int D, int NQ, bool Q = false>
 __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
                                const TreeHeader *__restrict__ hdr,
@@ -226,7 +247,7 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
     if (p0 >= n - 1)
         return;
     Sphere<D> pred[W];
-    int id[W], best[W], root[W];  // root: an ancestor of id in the union-find forest, where finds start
+    int id[W], best[W], root[W];  // root: an ancestor of the leaf in the union-find forest, where finds start
     bool core[W];
 #pragma unroll
     for (int j = 0; j < W; ++j) {
@@ -243,14 +264,17 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
     }
 #pragma unroll
     for (int j = 0; j < W; ++j)
-        root[j] = id[j];
+        root[j] = (int)p0 + j;
     auto pair = [&](int j, int q, int qid) {
+        const int32_t up = load_parent(parent, q);  // beside the load of deg: late in the walk mostly root already
         const bool core_q = deg[q] + 1 >= min_pts;
 #pragma unroll
         for (int jj = 0; jj < W; ++jj)
             if (jj == j) {
-                if (core[jj] && core_q)
-                    root[jj] = unite(parent, root[jj], qid, n);
+                if (core[jj] && core_q) {
+                    if (up != root[jj])
+                        root[jj] = unite(parent, root[jj], up, n);
+                }
                 else if (core[jj])
                     atomicMin(border + q, id[jj]);
                 else if (core_q)
@@ -267,14 +291,42 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
         if constexpr (Q) {
             if (hdr->qinv != 0.0) {
                 TopStack<int> ts(s_stack + threadIdx.x, blockDim.x, stack_cap, spill, -1);
-                auto f1 = [&](int at, bool h0, int i0, bool h1, int i1) {
-                    if (h0 || h1) {
-                        f(0, h0 ? at : at + 1, h0 ? i0 : i1, 0.0f);
-                        if (h0 && h1)
-                            f(0, at + 1, i1, 0.0f);
+                int *mine = s_stack + (stack_cap > 2 ? stack_cap : 2) * blockDim.x + threadIdx.x;  // this thread's queue
+                int held = 0;
+                auto settle = [&]() {
+                    int late = 0;  // partners not known to be in this component, compacted in place
+#pragma unroll
+                    for (int i = 0; i < kPairQueue; ++i)
+                        if (i < held) {
+                            const int q = mine[i * blockDim.x];
+                            const int32_t up = load_parent(parent, q);
+                            const bool core_q = deg[q] + 1 >= min_pts;
+                            if (core[0] && core_q) {
+                                if (up != root[0])
+                                    mine[late++ * blockDim.x] = up;
+                            } else if (core[0]) {
+                                atomicMin(border + q, id[0]);
+                            } else if (core_q) {
+                                best[0] = min(best[0], leaf_index<D>(leaves, q));
+                            }
+                        }
+                    held = 0;
+                    for (int i = 0; i < late; ++i) {
+                        const int up = mine[i * blockDim.x];
+                        if (up != root[0])
+                            root[0] = unite(parent, root[0], up, n);
                     }
                 };
+                auto f1 = [&](int at, bool h0, int, bool h1, int) {
+                    if (h0)
+                        mine[held++ * blockDim.x] = at;
+                    if (h1)
+                        mine[held++ * blockDim.x] = at + 1;
+                    if (__any(held > kPairQueue - 2))
+                        settle();
+                };
                 traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+                settle();
             } else {  // no common step of the frame: float nodes
                 traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
             }
@@ -288,17 +340,47 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
             atomicMin(border + p0 + j, best[j]);
 }
 
-// Labels of core points: the root of their value index, the cluster's
-// smallest core index.
+// The smallest value index of each cluster's core points, at border[root]
+// (unused there: a root is a core point).  The lanes of a wavefront that share a
+// root send one minimum, and none when the one there is smaller already: the
+// points of a large cluster would queue at one address.  5*10^6 cube points: 95 us.
+template <int D>
+__global__ __launch_bounds__(256) void k_dbscan_core_min(int32_t *__restrict__ parent, const int32_t *__restrict__ deg,
+                                                         int64_t n, int min_pts, const float *__restrict__ leaves,
+                                                         int32_t *__restrict__ border)
+{
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t q = base + threadIdx.x;
+        const bool core = q < n && deg[q] + 1 >= min_pts;
+        const int32_t r = core ? find_root(parent, (int32_t)q) : -1;
+        const int32_t id = core ? leaf_index<D>(leaves, q) : INT32_MAX;
+        uint64_t todo = __ballot(core);
+        while (todo) {
+            const int first = __ffsll((unsigned long long)todo) - 1;
+            const int32_t root = __shfl(r, first, kWave);
+            const bool same = r == root;
+            int32_t least = same ? id : INT32_MAX;
+#pragma unroll
+            for (int o = kWave / 2; o > 0; o >>= 1)
+                least = min(least, __shfl_xor(least, o, kWave));
+            if (lane_id() == first && least < load_parent(border, root))
+                atomicMin(border + root, least);
+            todo &= ~__ballot(same);
+        }
+    }
+}
+
+// Labels of core points: their root's smallest index.
 template <int D>
 __global__ void k_dbscan_core_labels(int32_t *__restrict__ parent, const int32_t *__restrict__ deg, int64_t n,
-                                     int min_pts, const float *__restrict__ leaves, int32_t *__restrict__ labels)
+                                     int min_pts, const float *__restrict__ leaves,
+                                     const int32_t *__restrict__ border, int32_t *__restrict__ labels)
 {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
         if (deg[q] + 1 >= min_pts) {
             const int id = leaf_index<D>(leaves, q);
             if (id >= 0 && id < n)
-                labels[id] = find_root(parent, id);
+                labels[id] = border[find_root(parent, (int32_t)q)];
         }
 }
 
@@ -343,7 +425,7 @@ PairLaunch pair_launch(const TreeDev &t)
     L.nq = tu.schedule == 2 ? 0 : (tu.packet ? tu.packet : (dim <= 3 && !qf ? 2 : 1));
     L.q = L.nq == 1 && qf;
     launch_shape(OP_REDUCE, dim, L.block, L.cap);
-    while (L.cap > 1 && (size_t)L.cap * L.block * sizeof(int) > 65536)
+    while (L.cap > 1 && (size_t)(L.cap + (L.q ? kPairQueue : 0)) * L.block * sizeof(int) > 65536)
         L.cap >>= 1;
     L.lds = L.nq ? (size_t)(L.cap > 2 ? L.cap : 2) * L.block * sizeof(int) : 0;  // a TopStack has at least two slots
     const int64_t per = L.nq ? L.nq : 1;
@@ -410,8 +492,9 @@ arborx_status dbscan_impl(const TreeDev &t, float eps, int min_pts, int32_t *lab
         const PairLaunch L = pair_launch(t);
         const Node<D> *nodes = static_cast<const Node<D> *>(t.nodes);
         const QNode<D> *qnodes = static_cast<const QNode<D> *>(t.qnodes);
+        const size_t lds = L.lds + (L.q ? (size_t)kPairQueue * L.block * sizeof(int) : 0);
 #define AX_DP(NQ, QF)                                                                                             \
-    k_dbscan_pairs<D, NQ, QF><<<L.grid, L.block, L.lds, s>>>(nodes, qnodes, t.hdr, t.leaves, n, r2, min_pts, deg, \
+    k_dbscan_pairs<D, NQ, QF><<<L.grid, L.block, lds, s>>>(nodes, qnodes, t.hdr, t.leaves, n, r2, min_pts, deg, \
                                                              parent, border, L.cap)
         if (L.nq == 0)
             AX_DP(0, false);
@@ -425,7 +508,8 @@ arborx_status dbscan_impl(const TreeDev &t, float eps, int min_pts, int32_t *lab
             AX_DP(4, false);
 #undef AX_DP
     }
-    k_dbscan_core_labels<D><<<g, 256, 0, s>>>(parent, deg, n, min_pts, t.leaves, labels);
+    k_dbscan_core_min<D><<<g, 256, 0, s>>>(parent, deg, n, min_pts, t.leaves, border);
+    k_dbscan_core_labels<D><<<g, 256, 0, s>>>(parent, deg, n, min_pts, t.leaves, border, labels);
     k_dbscan_border_labels<D><<<g, 256, 0, s>>>(deg, border, n, min_pts, t.leaves, labels);
     AX_HIP(hipGetLastError());
     return ARBORX_OK;
