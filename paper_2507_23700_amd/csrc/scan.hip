@@ -139,7 +139,9 @@ __global__ __launch_bounds__(kScanBlock) void csr_tile_prefix(int64_t *__restric
 }
 
 // Offsets in row order; long rows listed in the order of lcounts, as order[i]
-// (the row at position i) or i when order is NULL.
+// (the row at position i) or i when order is NULL.  The offsets leave through
+// LDS, so that the stores are contiguous: 10^7 rows 138 -> 52 us
+// against sixteen rows stored by each thread.
 __global__ __launch_bounds__(kScanBlock) void csr_apply(const int32_t *__restrict__ counts,
                                                         const int32_t *__restrict__ lcounts,
                                                         const uint32_t *__restrict__ order, int64_t m, int regs,
@@ -149,6 +151,7 @@ __global__ __launch_bounds__(kScanBlock) void csr_apply(const int32_t *__restric
                                                         int32_t *__restrict__ huge_list)
 {
     __shared__ int64_t wsum[kScanBlock / kWave];
+    __shared__ int64_t out[kScanTile + kScanTile / kScanItems];  // one pad a thread: columns spread over the banks
     const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int32_t c[kScanItems], lc[kScanItems];
     if (i0 + kScanItems <= m) {  // whole chunk: 16-byte loads (i0 is a multiple of kScanItems)
@@ -178,8 +181,8 @@ __global__ __launch_bounds__(kScanBlock) void csr_apply(const int32_t *__restric
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int64_t i = i0 + j;
+        out[threadIdx.x * (kScanItems + 1) + j] = run;
         if (i < m) {
-            offsets[i] = run;
             const int64_t fl = row_flags(lc[j], regs);
             if (fl != 0) {
                 const int32_t row = order ? (int32_t)order[i] : (int32_t)i;
@@ -193,6 +196,14 @@ __global__ __launch_bounds__(kScanBlock) void csr_apply(const int32_t *__restric
         run += c[j];
         if (i == m - 1)
             offsets[m] = run;
+    }
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kScanTile;
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) {
+        const int e = j * kScanBlock + threadIdx.x;
+        if (base + e < m)
+            offsets[base + e] = out[e + e / kScanItems];
     }
 }
 
