@@ -1450,6 +1450,7 @@ arborx_status forest_rebuild_impl(const float *values, const int64_t *offs, Fore
     }
     f.keys = codes;  // kept in the build workspace until the next rebuild: kNN seeds search them
     f.mbits = mbits;
+    f.ids = ids;
     constexpr int C = chunk_leaves<D>();
     const int chunks = (int)((n + C - 1) / C);
     Escape<D> *esc = static_cast<Escape<D> *>(w.esc);

@@ -191,7 +191,7 @@ arborx_status chamfer_forward(const float *a, const int64_t *a_off, const float 
     ForestDev f;
     st = build_forest(pts, seg.data(), 2 * P, 3, ARBORX_POINTS, f, s);
     if (st == ARBORX_OK)
-        st = forest_query_knn(f, pts, n, f.seg, dbt, 2 * P, 1, d2, idx, s);
+        st = forest_query_knn(f, pts, n, nullptr, dbt, 2 * P, 1, d2, idx, s);
     if (st == ARBORX_OK) {
         ProfScope ps("chamfer_loss", s);
         k_pair_loss<<<P, kLossBlock, 0, s>>>(d2, idx, f.seg, P, loss);

@@ -365,9 +365,13 @@ arborx_status forest_knn_launch(ForestDev &f, const float *q, int64_t m, const i
                                 int B, int k, float *d2, int32_t *idx, hipStream_t s)
 {
     ForestOrder order;
-    arborx_status st = forest_order<D>(f, q, m, boff, B, btree, &order, s);
-    if (st != ARBORX_OK)
-        return st;
+    if (boff) {
+        const arborx_status st = forest_order<D>(f, q, m, boff, B, btree, &order, s);
+        if (st != ARBORX_OK)
+            return st;
+    } else {  // the forest's own values: its build sorted them by tree and curve
+        order = ForestOrder{f.ids, f.keys, true, f.mbits};
+    }
     const Tuning &tu = tuning(OP_KNN);
     const int fmt = forest_format(OP_KNN, f);
     int block = 0, cap = 0;
@@ -440,7 +444,7 @@ arborx_status forest_query_knn(ForestDev &f, const float *q, int64_t m, const in
     if (m == 0)
         return ARBORX_OK;
     arborx_status st = check_nodes(f.qnodes, f.wnodes, f.n, forest_format(OP_KNN, f));
-    if (st == ARBORX_OK)
+    if (st == ARBORX_OK && boff)
         st = reserve_ws(f, m, s);
     if (st != ARBORX_OK)
         return st;

@@ -207,6 +207,7 @@ struct ForestDev {
     float *leaves = nullptr;   // n leaf records, sorted inside each tree
     uint64_t *keys = nullptr;  // [n] sorted build keys (tree << mbits | tree-local Morton code), in the build workspace
     int mbits = 0;             // bits of the tree-local code in a key
+    const uint32_t *ids = nullptr;  // [n] position in the packed values of each sorted key, beside the keys
     TreeHeader *hdrs = nullptr;  // [T]
     int64_t *seg = nullptr;    // [T+1] device copy of the tree offsets
     void *ws = nullptr;        // query workspace, grown on demand (reserve before graph capture)
@@ -231,6 +232,7 @@ arborx_status forest_reserve(ForestDev &f, int64_t m, hipStream_t s);
 arborx_status forest_query_reduce(ForestDev &f, const float *q, int64_t m, const int64_t *boff, const int32_t *btree,
                                   const float *brad, int B, int op, int scale_bits, int32_t *counts, int64_t *sums,
                                   hipStream_t s);
+// boff NULL: the queries are the packed values the forest was built over, batch b those of tree b.
 arborx_status forest_query_knn(ForestDev &f, const float *q, int64_t m, const int64_t *boff, const int32_t *btree,
                                int B, int k, float *d2, int32_t *idx, hipStream_t s);
 
