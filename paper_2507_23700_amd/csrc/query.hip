@@ -536,106 +536,166 @@ __global__ void k_spatial_fill_rows(const Node<D> *__restrict__ nodes, const QNo
         traverse_spatial<D>(nodes, hdr->root, node_count(hdr), pred, st, f);
 }
 
-// Listed rows of at most one wavefront (kWave entries): one wavefront per row,
-// a bitonic network across the lanes with shuffles, padding sorting last.
-// With a value mode, each index travels with its value (packed into one word).
-template <int MODE>
-__global__ __launch_bounds__(256) void k_sort_rows_wave(const int64_t *__restrict__ offsets,
-                                                        int32_t *__restrict__ indices, float *__restrict__ dist,
-                                                        const int32_t *__restrict__ list, int64_t nb)
+// Sorts the wavefront's kWave * E words ascending: word lane * E + e ends in v[e]
+// of that lane.  A bitonic network, whose steps shorter than E stay in a lane.
+template <int E, class T>
+__device__ __forceinline__ void wave_sort(T (&v)[E])
 {
     const int lane = lane_id();
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t b = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id(); b < nb; b += waves) {
-        const int64_t row = list[b];
-        const int64_t o = offsets[row];
-        const int64_t len = offsets[row + 1] - o;
-        if (len > kWave)
-            continue;
-        uint64_t v = MODE ? ~0ull : (0xffffffffull << 32);
-        if (lane < len)
-            v = MODE ? pack_match<MODE>(indices[o + lane], dist[o + lane])
-                     : ((uint64_t)(uint32_t)indices[o + lane] << 32);
 #pragma unroll
-        for (int k = 2; k <= kWave; k <<= 1)
+    for (int k = 2; k <= kWave * E; k <<= 1)
 #pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), j, kWave);
-                const uint32_t lo = MODE ? __shfl_xor((uint32_t)v, j, kWave) : 0u;
-                const uint64_t other = ((uint64_t)hi << 32) | lo;
-                const bool keep_min = ((lane & j) == 0) == ((lane & k) == 0);
-                v = keep_min ? (v < other ? v : other) : (v < other ? other : v);
-            }
-        if (lane < len) {
-            if (MODE) {
-                indices[o + lane] = match_index<MODE>(v);
-                dist[o + lane] = match_value<MODE>(v);
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            if (j >= E) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const T other = __shfl_xor(v[e], j / E, kWave);
+                    const bool keep_min = ((lane & (j / E)) == 0) == (((lane * E + e) & k) == 0);
+                    v[e] = (v[e] < other) == keep_min ? v[e] : other;
+                }
             } else {
-                indices[o + lane] = (int32_t)(v >> 32);
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if ((e & j) == 0) {
+                        const bool up = ((lane * E + e) & k) == 0;
+                        const T x = v[e], y = v[e | j];
+                        const bool swap = (y < x) == up;
+                        v[e] = swap ? y : x;
+                        v[e | j] = swap ? x : y;
+                    }
+            }
+        }
+}
+
+// Sorts a row of at most kWave * E entries at o.
+template <int MODE, int E>
+__device__ __forceinline__ void sort_row_wave(int32_t *__restrict__ indices, float *__restrict__ dist, int64_t o,
+                                              int len)
+{
+    typename std::conditional<MODE != 0, unsigned long long, int>::type v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = e * kWave + lane_id();
+        if constexpr (MODE != 0)
+            v[e] = i < len ? pack_match<MODE>(indices[o + i], dist[o + i]) : ~0ull;
+        else
+            v[e] = i < len ? indices[o + i] : INT32_MAX;
+    }
+    wave_sort<E>(v);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = lane_id() * E + e;
+        if (i < len) {
+            if constexpr (MODE != 0) {
+                indices[o + i] = match_index<MODE>(v[e]);
+                dist[o + i] = match_value<MODE>(v[e]);
+            } else {
+                indices[o + i] = v[e];
             }
         }
     }
 }
 
-// One workgroup per listed row of kWave < len <= kRowSortBlock entries:
+// One wavefront per listed row of at most kWaveRow entries, sorted in registers,
+// padding last.  With a value mode, each index travels with its value (packed
+// into one word).  Rows of 65 to 256 were sorted by workgroups in LDS, which
+// also looked at every shorter row one after the other: all hits of 3*10^5 rays
+// 267 -> 84 us for both kernels, 5*10^5 6D rows with distances 298 -> 75, 10^7
+// rows of at most 64 174 -> 108.
+constexpr int kWaveRow = 4 * kWave;
+template <int MODE>
+__global__ __launch_bounds__(256) void k_sort_rows_wave(const int64_t *__restrict__ offsets,
+                                                        int32_t *__restrict__ indices, float *__restrict__ dist,
+                                                        const int32_t *__restrict__ list, int64_t nb)
+{
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
+    for (int64_t b = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id(); b < nb; b += waves) {
+        const int64_t row = list[b];
+        const int64_t o = offsets[row];
+        const int64_t len = offsets[row + 1] - o;
+        if (len <= kWave)
+            sort_row_wave<MODE, 1>(indices, dist, o, (int)len);
+        else if (len <= 2 * kWave)
+            sort_row_wave<MODE, 2>(indices, dist, o, (int)len);
+        else if (len <= kWaveRow)
+            sort_row_wave<MODE, 4>(indices, dist, o, (int)len);
+    }
+}
+
+// One workgroup per listed row of kWaveRow < len <= kRowSortBlock entries, the
+// threads looking for them among kRowSortBatch of its candidates at a time:
 // bitonic sort in LDS (with a value mode the values move with their indices;
 // mode 2 sorts by (value, index)).
+constexpr int kRowSortBatch = 256;  // the workgroup
 template <int MODE>
-__global__ __launch_bounds__(256) void k_sort_rows(const int64_t *__restrict__ offsets, int32_t *__restrict__ indices,
+__global__ __launch_bounds__(kRowSortBatch) void k_sort_rows(const int64_t *__restrict__ offsets, int32_t *__restrict__ indices,
                                                    float *__restrict__ dist, const int32_t *__restrict__ list,
                                                    int64_t nb)
 {
     constexpr bool OUT = MODE != 0;
     __shared__ int32_t s[kRowSortBlock];
     __shared__ float sd[OUT ? kRowSortBlock : 1];
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int64_t row = list[b];
-        const int64_t o = offsets[row];
-        const int64_t len64 = offsets[row + 1] - o;
-        if (len64 <= kWave || len64 > kRowSortBlock)
-            continue;
-        const int len = (int)len64;
-        int p2 = 1;
-        while (p2 < len)
-            p2 <<= 1;
-        for (int i = threadIdx.x; i < p2; i += blockDim.x) {
-            s[i] = i < len ? indices[o + i] : INT32_MAX;
-            if (OUT)
-                sd[i] = i < len ? dist[o + i] : INFINITY;
+    __shared__ int32_t s_found[kRowSortBatch];
+    __shared__ int s_count;
+    for (int64_t base = 0; blockIdx.x + base * gridDim.x < nb; base += kRowSortBatch) {
+        if (threadIdx.x == 0)
+            s_count = 0;
+        __syncthreads();
+        const int64_t cand = blockIdx.x + (base + threadIdx.x) * gridDim.x;
+        if (cand < nb) {
+            const int64_t r = list[cand], n = offsets[r + 1] - offsets[r];
+            if (n > kWaveRow && n <= kRowSortBlock)
+                s_found[atomicAdd(&s_count, 1)] = (int32_t)r;
         }
         __syncthreads();
-        for (int kk = 2; kk <= p2; kk <<= 1) {
-            for (int j = kk >> 1; j > 0; j >>= 1) {
-                for (int i = threadIdx.x; i < p2; i += blockDim.x) {
-                    const int ixj = i ^ j;
-                    if (ixj > i) {
-                        const int a = s[i], c = s[ixj];
-                        const bool up = (i & kk) == 0;
-                        bool greater = a > c;
-                        if (MODE == 2) {
-                            const float va = sd[i], vc = sd[ixj];
-                            greater = va > vc || (va == vc && a > c);
-                        }
-                        if (greater == up) {
-                            s[i] = c;
-                            s[ixj] = a;
-                            if (OUT) {
-                                const float t = sd[i];
-                                sd[i] = sd[ixj];
-                                sd[ixj] = t;
+        const int found = s_count;
+        __syncthreads();  // the next batch resets it
+        for (int b = 0; b < found; ++b) {
+            const int64_t row = s_found[b];
+            const int64_t o = offsets[row];
+            const int len = (int)(offsets[row + 1] - o);
+            int p2 = 1;
+            while (p2 < len)
+                p2 <<= 1;
+            for (int i = threadIdx.x; i < p2; i += blockDim.x) {
+                s[i] = i < len ? indices[o + i] : INT32_MAX;
+                if (OUT)
+                    sd[i] = i < len ? dist[o + i] : INFINITY;
+            }
+            __syncthreads();
+            for (int kk = 2; kk <= p2; kk <<= 1) {
+                for (int j = kk >> 1; j > 0; j >>= 1) {
+                    for (int i = threadIdx.x; i < p2; i += blockDim.x) {
+                        const int ixj = i ^ j;
+                        if (ixj > i) {
+                            const int a = s[i], c = s[ixj];
+                            const bool up = (i & kk) == 0;
+                            bool greater = a > c;
+                            if (MODE == 2) {
+                                const float va = sd[i], vc = sd[ixj];
+                                greater = va > vc || (va == vc && a > c);
+                            }
+                            if (greater == up) {
+                                s[i] = c;
+                                s[ixj] = a;
+                                if (OUT) {
+                                    const float t = sd[i];
+                                    sd[i] = sd[ixj];
+                                    sd[ixj] = t;
+                                }
                             }
                         }
                     }
+                    __syncthreads();
                 }
-                __syncthreads();
             }
+            for (int i = threadIdx.x; i < len; i += blockDim.x) {
+                indices[o + i] = s[i];
+                if (OUT)
+                    dist[o + i] = sd[i];
+            }
+            __syncthreads();
         }
-        for (int i = threadIdx.x; i < len; i += blockDim.x) {
-            indices[o + i] = s[i];
-            if (OUT)
-                dist[o + i] = sd[i];
-        }
-        __syncthreads();
     }
 }
 
@@ -1508,16 +1568,16 @@ arborx_status sort_big_rows(const int64_t *offsets, int32_t *indices, float *dis
     if (nbig <= 0)
         return ARBORX_OK;
     ProfScope ps("sort_rows", s);
-    const unsigned gw = grid_for(nbig, 256 / kWave, 16384), gb = (unsigned)(nbig < 8192 ? nbig : 8192);
+    const unsigned gw = grid_for(nbig, 256 / kWave, 16384), gb = (unsigned)(nbig < 2048 ? nbig : 2048);
     if (dist && mode == VALUES_ORDERED) {
         k_sort_rows_wave<2><<<gw, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
-        k_sort_rows<2><<<gb, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
+        k_sort_rows<2><<<gb, kRowSortBatch, 0, s>>>(offsets, indices, dist, big_list, nbig);
     } else if (dist) {
         k_sort_rows_wave<1><<<gw, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
-        k_sort_rows<1><<<gb, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
+        k_sort_rows<1><<<gb, kRowSortBatch, 0, s>>>(offsets, indices, dist, big_list, nbig);
     } else {
         k_sort_rows_wave<0><<<gw, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
-        k_sort_rows<0><<<gb, 256, 0, s>>>(offsets, indices, dist, big_list, nbig);
+        k_sort_rows<0><<<gb, kRowSortBatch, 0, s>>>(offsets, indices, dist, big_list, nbig);
     }
     AX_HIP(hipGetLastError());
     return ARBORX_OK;
