@@ -138,8 +138,8 @@ namespace ax {
 
 static thread_local std::string g_error;
 // Defaults measured on MI355X at 10^7 points: 256-thread blocks for the radius
-// walks; 64-thread blocks and an 8-entry LDS ring for kNN (its 8-byte stack
-// entries and larger register set).  Over trees of points the radius walks
+// walks; an 8-entry LDS ring for kNN (its 8-byte stack entries and larger
+// register set), in blocks that launch_shape sets.  Over trees of points the radius walks
 // and kNN run over quantized nodes (half the node loads; a point's leaf is
 // exact in its parent; node_format_of below), the CSR count one query per
 // thread.
@@ -158,11 +158,21 @@ static Tuning default_tuning(int op)
     return t;
 }
 
+bool default_shape(int op)
+{
+    const Tuning &t = tuning(op), d = default_tuning(op);
+    return t.by_dim && t.block == d.block && t.stack == d.stack;
+}
+
 void launch_shape(int op, int dim, int &block, int &stack)
 {
     const Tuning &t = tuning(op);
     block = t.block;
     stack = t.stack;
+    // kNN over codes up to 3D: 256 threads, whose neighbouring wavefronts share a compute unit's cache (k = 16 at
+    // 10^7 points 5.71 ms, 5.84 with 64); in 6D 64 (k = 8 5.51 ms, 5.67 with 256) with 16 entries (7.87 with 8)
+    if (default_shape(op) && dim < 6 && op == OP_KNN)
+        block = 256;
     if (t.by_dim && dim >= 6) {
         if (op == OP_KNN) {
             block = 64;

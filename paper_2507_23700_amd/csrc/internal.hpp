@@ -53,6 +53,8 @@ struct Tuning {
                     // 6D)
     bool by_dim = false;  // the library's defaults: block and stack also follow the dimension (launch_shape)
 };
+// The block and stack of `op` are the library's defaults, not a saved choice's.
+bool default_shape(int op);
 // Block size and short-stack depth a launch of `op` in dimension `dim` uses:
 // the tuning's, except that the library's defaults in 6D take the shapes
 // measured best on the 6D Gaussian mixture at 2*10^6 points over quantized
