@@ -65,7 +65,7 @@ typedef enum { ARBORX_COUNT = 0, ARBORX_COUNT_SUMDIST = 1 } arborx_reducer;
 /* Traversal schedule knobs; every schedule returns identical results. */
 typedef struct arborx_tuning {
     int32_t block;        /* threads per workgroup for traversal kernels: 64, 128, 256 (0 = default) */
-    int32_t order;        /* sort queries along the Morton curve before traversal: 1 = on a 24-bit grid (three
+    int32_t order;        /* sort queries along a Hilbert curve before traversal: 1 = on a 24-bit grid (three
                              sort passes), 2 = on a 16-bit grid (two passes); 0 = input order */
     int32_t stack;        /* LDS short-stack entries per thread: 4..64 (0 = default); deeper trees spill */
     int32_t schedule;     /* 0 = thread per query with a short stack; 1 = wavefront packet (64 queries share
@@ -87,7 +87,7 @@ typedef struct arborx_tuning {
                              them a kNN over points also walks format 1, while trees and forests of boxes, and
                              ones built without format 1, are walked on format 0 */
     int32_t queries_per_thread; /* radius searches (CSR count pass of sphere queries, fused reductions) with
-                                   the thread schedule on binary nodes: 1, 2 or 4 Morton-neighbouring queries
+                                   the thread schedule on binary nodes: 1, 2 or 4 neighbouring queries
                                    answered by one thread in one walk over the union of their paths; 0 = by
                                    operation, dimension and format (up to 3D: 2 for CSR; for reductions 4 on
                                    format 0, 1 on format 1; 1 in 6D).  Defaults: 1 for ARBORX_OP_SPATIAL, 0
@@ -271,7 +271,7 @@ arborx_status arborx_query_knn(arborx_tree tree, const float *queries, int64_t m
  * Allocation-free k-nearest search, for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments and the same results, bit for bit, as
- * arborx_query_knn, but the call allocates nothing: the Morton ordering of the
+ * arborx_query_knn, but the call allocates nothing: the ordering of the
  * queries runs in a static scratch area that the library holds once per GPU
  * (ARBORX_NOALLOC_MAX_QUERIES x 16 bytes + 1 MiB, about 33 MiB, reserved with
  * the library's code on that GPU until the process ends), and the order is not
@@ -397,7 +397,7 @@ arborx_status arborx_self_join_degree(arborx_tree tree, float radius, int32_t *d
  *   rays      [m][2][dim]: origin row, then direction row (any length, zero
  *             components allowed); hits as in arborx_query_ray_count
  *   offsets, indices, capacity, total: as arborx_query_spatial; rows ascending
- * Rays are ordered by the Morton code of their origins before the walk.
+ * Rays are ordered by the Hilbert code of their origins before the walk.
  * Temporary device memory: as arborx_query_spatial, with an overflow pool four
  * times larger (rays meet many more values than a radius query).
  * Synchronises `stream` (to read the total).  Plan form:
@@ -503,8 +503,8 @@ arborx_status arborx_forest_reserve(arborx_forest forest, int64_t m, void *strea
  * DEVICE arrays; m [host] must equal batch_offsets[B].  Queries of a batch
  * whose tree index is out of range match nothing.  Results are per query, in
  * input order, with indices LOCAL to the target tree (identical to querying
- * that tree built alone).  All batches run in one persistent launch that takes
- * Morton-ordered blocks of queries from a work counter; nothing synchronises,
+ * that tree built alone).  All batches run in one launch over the queries in the
+ * order of their batch and a Hilbert curve inside it; nothing synchronises,
  * and after arborx_forest_reserve nothing allocates (graph-capturable; while
  * capturing, the call does not wait for the build: order it before capture).
  */

@@ -1,7 +1,7 @@
 // Batched queries over a built BVH (Section 2.1: spatial and nearest
 // predicates; storage query with CSR output; Section 2.2: pure callbacks).
 //
-// Queries are first put in Morton order (Section 2.6: sorting is used in
+// Queries are first put in Hilbert order (Section 2.6: sorting is used in
 // search as well as construction) so that the 64 lanes of a wavefront walk
 // neighbouring paths and share node fetches.  Each thread then answers one
 // query with a depth-first walk whose deferred subtrees sit on a short stack:

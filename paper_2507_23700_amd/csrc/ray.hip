@@ -17,7 +17,7 @@ namespace {
 
 __device__ __forceinline__ int ray_nodes(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
 
-// Thread t answers ray perm[t] (origins in Morton order: neighbouring rays
+// Thread t answers ray perm[t] (origins in Hilbert order: neighbouring rays
 // start in the same part of the tree), or ray t without an order.
 template <int D>
 __global__ void k_ray_count(const Node<D> *__restrict__ nodes, const TreeHeader *__restrict__ hdr,

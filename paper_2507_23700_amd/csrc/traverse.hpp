@@ -110,7 +110,7 @@ struct TopStack {
 };
 
 // Blocks are dealt round-robin over the 8 XCDs; renumber them so that each
-// XCD (and its L2) works on one contiguous run of Morton-ordered queries.
+// XCD (and its L2) works on one contiguous run of ordered queries.
 __device__ __forceinline__ int64_t xcd_block()
 {
     constexpr int64_t X = 8;
