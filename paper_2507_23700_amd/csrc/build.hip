@@ -52,7 +52,10 @@ __device__ __forceinline__ float quant_scale(float lo, float hi)
 // The frame of a tree: one step for every dimension, the largest of them, so
 // that walks measure distances in codes (CodeBall), unless some extent is
 // below 1/256 of the largest; that keeps at least 256 codes across every
-// extent, and the largest extent has no finer codes either way.
+// extent, and the largest extent has no finer codes either way.  Nor when the
+// step is so small that 1/step^2 leaves the range of float32, in which the
+// nearest searches turn their bound into codes.
+constexpr float kLeastStep = 1e-19f;
 template <int D>
 __device__ void quant_frame(const float *lo, const float *hi, float *qscale, double *qinv)
 {
@@ -64,7 +67,7 @@ __device__ void quant_frame(const float *lo, const float *hi, float *qscale, dou
             least = fminf(least, qscale[d]);
     }
     *qinv = 0.0;
-    if (most > 0.0f && most < INFINITY && most * (1.0f / 256.0f) <= least) {
+    if (most >= kLeastStep && most < INFINITY && most * (1.0f / 256.0f) <= least) {
         *qinv = 1.0 / (double)most;
         for (int d = 0; d < D; ++d)
             qscale[d] = most;

@@ -1419,7 +1419,8 @@ __device__ __forceinline__ void knn_search_wave(const Node<D> *__restrict__ node
 // internal children ordered and pruned by their squared code gaps against the
 // bound in codes, and leaf children offered with their exact distances.  The
 // bound in codes, k d^2 + a, is rounded up in float32: k and a hold 1/s^2 with
-// the margins of code_ball and more.  A wavefront with a query outside the
+// the margins of code_ball and more (a frame's step keeps them in range, see
+// quant_frame).  A wavefront with a query outside the
 // frame counts the excesses past it (CodeExcess), or it would enter every node
 // near the projection on the frame: k = 1 between clouds of unlike extents
 // took 6.6 ms without them, 1.8 over float nodes.  Half the loads of the float nodes and no decoding:
@@ -1489,16 +1490,15 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
     }
     const double k = hdr.qinv * hdr.qinv * (1.0 + 0x1p-19), a = hdr.qinv * hdr.qinv * 0x1p-144 + 2.0;
     if (!__any(past > 1.0)) {
-        knn_walk_codes<D, K, false>(nodes, n_nodes, hdr, q, best, st, (float)fmin(k, 3.0e38), (float)fmin(a, 3.0e38),
-                             [&](const uint32_t(&w)[D]) { return code_gap2<D>(qc, w); });
+        knn_walk_codes<D, K, false>(nodes, n_nodes, hdr, q, best, st, (float)k, (float)a,
+                                    [&](const uint32_t(&w)[D]) { return code_gap2<D>(qc, w); });
         return;
     }
     const CodeExcess<D> ex(e);
     const double unit = ldexp(1.0, -(int)(ex.shift & 15u));
     const double rest = (a - past * (1.0 - 0x1p-22)) * unit;
-    knn_walk_codes<D, K, true>(nodes, n_nodes, hdr, q, best, st, (float)fmin(k * unit, 3.0e38),
-                         (float)fmin(fmax(rest + 1.0, -3.0e38), 3.0e38),
-                         [&](const uint32_t(&w)[D]) { return ex.gap2(qc, w); });
+    knn_walk_codes<D, K, true>(nodes, n_nodes, hdr, q, best, st, (float)(k * unit), (float)fmax(rest + 1.0, -3.0e38),
+                               [&](const uint32_t(&w)[D]) { return ex.gap2(qc, w); });
 }
 
 // kNN over quantized nodes: as knn_search (seeded, software-pipelined),
