@@ -4,6 +4,7 @@
 #include <atomic>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <unordered_map>
@@ -85,6 +86,19 @@ struct NoteUse {
     ~NoteUse() { u.note(s); }
 };
 
+// A traversal order on the device.  Every call that walks by it holds it until
+// its use of the tree is recorded in `uses`, so when the last holder lets go
+// (a concurrent call with other queries has replaced it in the cache), all its
+// uses are known and the memory is released after them.
+struct QueryOrder {
+    StreamUses *uses;
+    uint32_t *perm = nullptr;
+    hipEvent_t ready = nullptr;
+    explicit QueryOrder(StreamUses *u) : uses(u) {}
+    QueryOrder(const QueryOrder &) = delete;
+    ~QueryOrder();
+};
+
 // The traversal order of the last query array a tree was asked about,
 // identified by its address, length, predicate kind and order mode.  A
 // repeated call reuses it; a changed array under the same address only makes
@@ -95,8 +109,7 @@ struct OrderCache {
     const float *queries = nullptr;
     int64_t m = -1;
     int pred = -1, mode = 0;
-    uint32_t *perm = nullptr;
-    hipEvent_t ready = nullptr;
+    std::shared_ptr<QueryOrder> last;
 };
 
 struct arborx_tree_s {
@@ -123,7 +136,6 @@ struct arborx_plan_s {
     int64_t *offsets;
     hipStream_t stream;
     ax::Temps tmp;
-    uint32_t *perm = nullptr;
     int32_t *counts = nullptr, *ordered_counts = nullptr, *stash = nullptr, *big_list = nullptr, *huge_list = nullptr;
     float *stash_d2 = nullptr;  // with per-match values (distances, or a ray's entry parameters)
     int mode = ax::VALUES_NONE; // how rows are sorted and whether values are kept
@@ -726,8 +738,11 @@ static void release_tree(arborx_tree t)
 {
     if (!t)
         return;
-    void *const blocks[] = {t->dev.nodes,  t->dev.qnodes, t->dev.wnodes,  t->dev.codes,
-                            t->dev.leaves, t->dev.hdr,    t->order.perm};
+    QueryOrder *order = t->order.last.get();
+    void *const blocks[] = {t->dev.nodes,  t->dev.qnodes, t->dev.wnodes, t->dev.codes,
+                            t->dev.leaves, t->dev.hdr,    order ? order->perm : nullptr};
+    if (order)
+        order->perm = nullptr;
     constexpr int n = (int)(sizeof(blocks) / sizeof(blocks[0]));
     hipEvent_t only = own_allocator() ? t->uses.take_only(t->stream, t->ready) : nullptr;
     if (only) {  // one stream built and used it: its next allocation takes the memory with no other stream between
@@ -737,59 +752,58 @@ static void release_tree(arborx_tree t)
         if (t->ready)
             (void)hipStreamWaitEvent(rs, t->ready, 0);
         t->uses.wait_all(rs);
-        if (t->order.ready)
-            (void)hipStreamWaitEvent(rs, t->order.ready, 0);
+        if (order && order->ready)
+            (void)hipStreamWaitEvent(rs, order->ready, 0);
         if (!rs)
             (void)hipDeviceSynchronize();
         dfree_many(blocks, n, rs);
     }
-    if (t->order.ready)
-        (void)hipEventDestroy(t->order.ready);
     if (t->ready)
         (void)hipEventDestroy(t->ready);
     delete t;
 }
 
 // Traversal order for a query call on tree t: the cached one when the call
-// repeats the last query array, else a new one that replaces it.
-static arborx_status tree_order(arborx_tree t, const float *queries, int64_t m, Pred pred, int op, uint32_t **perm,
-                                Temps &tmp, hipStream_t s)
+// repeats the last query array, else a new one that replaces it.  The caller
+// keeps `order` until its use is noted (declares it before its NoteUse).
+static arborx_status tree_order(arborx_tree t, const float *queries, int64_t m, Pred pred, int op,
+                                std::shared_ptr<QueryOrder> *order, Temps &tmp, hipStream_t s)
 {
-    *perm = nullptr;
     const int mode = tuning(op).order;
     if (!mode || t->dev.n == 0 || m <= 1)
         return ARBORX_OK;
     OrderCache &oc = t->order;
     std::lock_guard<std::mutex> lock(oc.mu);
-    if (oc.perm && oc.queries == queries && oc.m == m && oc.pred == (int)pred && oc.mode == mode) {
-        AX_HIP(hipStreamWaitEvent(s, oc.ready, 0));
-        *perm = oc.perm;
+    if (oc.last && oc.queries == queries && oc.m == m && oc.pred == (int)pred && oc.mode == mode) {
+        AX_HIP(hipStreamWaitEvent(s, oc.last->ready, 0));
+        *order = oc.last;
         return ARBORX_OK;
     }
-    uint32_t *fresh = nullptr, *keep = nullptr;
+    uint32_t *fresh = nullptr;
     arborx_status st = query_order(t->dev, queries, m, pred, op, &fresh, tmp, s);
     if (st != ARBORX_OK || !fresh)
         return st;
-    if ((st = dalloc((void **)&keep, (size_t)m * sizeof(uint32_t), s)) != ARBORX_OK)
+    auto keep = std::make_shared<QueryOrder>(&t->uses);
+    AX_HIP(hipEventCreateWithFlags(&keep->ready, hipEventDisableTiming));
+    if ((st = dalloc((void **)&keep->perm, (size_t)m * sizeof(uint32_t), s)) != ARBORX_OK)
         return st;
-    AX_HIP(hipMemcpyAsync(keep, fresh, (size_t)m * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    if (!oc.ready)
-        AX_HIP(hipEventCreateWithFlags(&oc.ready, hipEventDisableTiming));
-    if (oc.perm) {  // release the old order after every use of the tree so far
-        hipStream_t rs = release_stream();
-        (void)hipStreamWaitEvent(rs, oc.ready, 0);
-        t->uses.wait(rs);
-        dfree(oc.perm, rs);
+    hipError_t e = hipMemcpyAsync(keep->perm, fresh, (size_t)m * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess)
+        e = hipEventRecord(keep->ready, s);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(s);  // the copy is not covered by an event
+        return hip_fail(e, "keeping the query order");
     }
-    AX_HIP(hipEventRecord(oc.ready, s));
     oc.queries = queries;
     oc.m = m;
     oc.pred = (int)pred;
     oc.mode = mode;
-    oc.perm = keep;
-    *perm = keep;
+    oc.last = keep;  // the replaced order goes when the last call that walks by it lets go
+    *order = keep;
     return ARBORX_OK;
 }
+
+static const uint32_t *perm_of(const std::shared_ptr<QueryOrder> &order) { return order ? order->perm : nullptr; }
 
 static arborx_status wait_tree(arborx_tree t, hipStream_t s)
 {
@@ -798,6 +812,21 @@ static arborx_status wait_tree(arborx_tree t, hipStream_t s)
 }
 
 }  // namespace ax
+
+QueryOrder::~QueryOrder()
+{
+    if (perm) {
+        hipStream_t rs = ax::release_stream();
+        if (ready)
+            (void)hipStreamWaitEvent(rs, ready, 0);
+        uses->wait(rs);
+        if (!rs)
+            (void)hipDeviceSynchronize();
+        ax::dfree(perm, rs);
+    }
+    if (ready)
+        (void)hipEventDestroy(ready);
+}
 
 using namespace ax;
 
@@ -1015,6 +1044,7 @@ static arborx_status csr_begin(arborx_tree t, Pred pred, const float *queries, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     arborx_plan p = new arborx_plan_s(s);
     p->tree = t;
@@ -1050,15 +1080,16 @@ static arborx_status csr_begin(arborx_tree t, Pred pred, const float *queries, i
                       (st = p->tmp.get(&p->ovf.dpool, overflow_pool_ints(mm, t->dev.dim, overflow_factor(pred)))) !=
                           ARBORX_OK))
         return bail(st);
-    if ((st = tree_order(t, queries, m, pred, OP_SPATIAL, &p->perm, p->tmp, s)) != ARBORX_OK)
+    if ((st = tree_order(t, queries, m, pred, OP_SPATIAL, &order, p->tmp, s)) != ARBORX_OK)
         return bail(st);
+    const uint32_t *perm = perm_of(order);
     p->ovf.per = (int32_t)(overflow_pool_ints(mm, t->dev.dim, overflow_factor(pred)) / kOvfPools);
-    if ((st = spatial_count(t->dev, pred, queries, m, radius, p->perm, p->counts, p->ordered_counts, p->stash,
+    if ((st = spatial_count(t->dev, pred, queries, m, radius, perm, p->counts, p->ordered_counts, p->stash,
                             p->stash_d2, p->ovf, s)) != ARBORX_OK)
         return bail(st);
     {
         ProfScope ps("scan", s);
-        hipError_t e = csr_offsets_lists(p->counts, p->ordered_counts, p->perm, m, stash_regs(t->dev.dim), offsets,
+        hipError_t e = csr_offsets_lists(p->counts, p->ordered_counts, perm, m, stash_regs(t->dev.dim), offsets,
                                          p->big_list, p->huge_list,
                                          p->host, sws, s);
         if (e != hipSuccess)
@@ -1069,7 +1100,6 @@ static arborx_status csr_begin(arborx_tree t, Pred pred, const float *queries, i
         return bail(hip_fail(e, "reading the match total"));
     p->h = *p->host;
     *total = (int64_t)p->h.total;
-    p->perm = nullptr;  // the tree's cached order may be replaced once this call returns
     *out = p;
     return ARBORX_OK;
 }
@@ -1208,12 +1238,12 @@ arborx_status arborx_query_knn(arborx_tree t, const float *queries, int64_t m, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     Temps tmp(s);
-    uint32_t *perm = nullptr;
-    if ((st = tree_order(t, queries, m, Pred::Sphere, OP_KNN, &perm, tmp, s)) != ARBORX_OK)
+    if ((st = tree_order(t, queries, m, Pred::Sphere, OP_KNN, &order, tmp, s)) != ARBORX_OK)
         return st;
-    return knn_query(t->dev, queries, m, k, perm, dist2, indices, s);
+    return knn_query(t->dev, queries, m, k, perm_of(order), dist2, indices, s);
 }
 
 arborx_status arborx_query_knn_noalloc(arborx_tree t, const float *queries, int64_t m, int32_t k, float *dist2,
@@ -1264,12 +1294,12 @@ arborx_status arborx_query_spatial_reduce(arborx_tree t, const float *queries, i
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     Temps tmp(s);
-    uint32_t *perm = nullptr;
-    if ((st = tree_order(t, queries, m, Pred::Sphere, OP_REDUCE, &perm, tmp, s)) != ARBORX_OK)
+    if ((st = tree_order(t, queries, m, Pred::Sphere, OP_REDUCE, &order, tmp, s)) != ARBORX_OK)
         return st;
-    return spatial_reduce(t->dev, queries, m, radius, op, scale_bits, perm, counts, sum_fixed, s);
+    return spatial_reduce(t->dev, queries, m, radius, op, scale_bits, perm_of(order), counts, sum_fixed, s);
 }
 
 static arborx_status ray_args(arborx_tree t, const float *rays, int64_t m, const void *out1, const void *out2)
@@ -1319,12 +1349,12 @@ arborx_status arborx_query_ray_count(arborx_tree t, const float *rays, int64_t m
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     Temps tmp(s);
-    uint32_t *perm = nullptr;
-    if ((st = tree_order(t, rays, m, Pred::Ray, OP_REDUCE, &perm, tmp, s)) != ARBORX_OK)
+    if ((st = tree_order(t, rays, m, Pred::Ray, OP_REDUCE, &order, tmp, s)) != ARBORX_OK)
         return st;
-    return ray_count(t->dev, rays, m, perm, counts, s);
+    return ray_count(t->dev, rays, m, perm_of(order), counts, s);
 }
 
 arborx_status arborx_query_ray_nearest(arborx_tree t, const float *rays, int64_t m, int32_t k, float *t_entry,
@@ -1338,12 +1368,12 @@ arborx_status arborx_query_ray_nearest(arborx_tree t, const float *rays, int64_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     Temps tmp(s);
-    uint32_t *perm = nullptr;
-    if ((st = tree_order(t, rays, m, Pred::Ray, OP_KNN, &perm, tmp, s)) != ARBORX_OK)
+    if ((st = tree_order(t, rays, m, Pred::Ray, OP_KNN, &order, tmp, s)) != ARBORX_OK)
         return st;
-    return ray_nearest(t->dev, rays, m, perm, k, t_entry, indices, s);
+    return ray_nearest(t->dev, rays, m, perm_of(order), k, t_entry, indices, s);
 }
 
 arborx_status arborx_dbscan(arborx_tree t, const float *points, float eps, int32_t min_pts, int32_t *labels,
@@ -1432,12 +1462,12 @@ arborx_status arborx_query_spatial_count_up_to(arborx_tree t, const float *queri
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = wait_tree(t, s)) != ARBORX_OK)
         return st;
+    std::shared_ptr<QueryOrder> order;
     NoteUse note_use{t->uses, s};
     Temps tmp(s);
-    uint32_t *perm = nullptr;
-    if (n_max > 0 && (st = tree_order(t, queries, m, Pred::Sphere, OP_REDUCE, &perm, tmp, s)) != ARBORX_OK)
+    if (n_max > 0 && (st = tree_order(t, queries, m, Pred::Sphere, OP_REDUCE, &order, tmp, s)) != ARBORX_OK)
         return st;
-    return spatial_count_up_to(t->dev, queries, m, radius, n_max, perm, counts, s);
+    return spatial_count_up_to(t->dev, queries, m, radius, n_max, perm_of(order), counts, s);
 }
 
 // ---------------------------------------------------------------------------
