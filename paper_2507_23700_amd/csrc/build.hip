@@ -203,6 +203,7 @@ __global__ __launch_bounds__(kBuildBlock) void bounds_final(const float *__restr
     __syncthreads();
     if (d == 0) {
         quant_frame<D>(s_lo[0], s_hi[0], hdr->qscale, &hdr->qinv);
+        hdr->crowded = 0;
         hdr->n = (int32_t)n;
         hdr->root = n > 0 ? 0 : -1;
         hdr->height = 0;
@@ -425,11 +426,26 @@ __device__ __forceinline__ void load_value_box(const float *values, int kind, ui
 // fill that child's code bytes); a box tree's leaf child becomes its sorted
 // leaf position: the left child of node p is leaf p, the right child leaf
 // p + 1.
+//
+// A tree is crowded where its frame is coarse for its points: some subtree of
+// kCrowd or more values lies within kCrowdCodes codes, rounded outward, in
+// every dimension (and not all in one place, where no box can be left out).
+// In codes every box around there is next to every query, so a search leaves
+// nothing out and meets the whole crowd; float boxes have no such limit (see
+// codes_serve).  One stray point far from 10^6 uniform ones in 3D widens the
+// frame until a code is 1/S of the mean spacing; nearest 8 over codes and over
+// float nodes: S = 20 466 and 564 us, 7 621 and 703, 5 789 and 787, 4 899 and
+// 808, 2.2 1956 and 1063, 1.1 4063 and 1064, where the largest subtree within
+// four codes has 3, 6, 7, 9, 21 and 79 points.  With 10^4 of 10^6 points inside two
+// codes 4960 and 482 us.
+constexpr uint32_t kCrowdCodes = 5;
+constexpr int kCrowd = 8;
 template <int D>
 __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const Node<D> &nd, int p, int kind,
-                                            const CodeFrame<D> &frame)
+                                            const CodeFrame<D> &frame, int32_t *crowded)
 {
     QNode<D> qn;
+    bool crowd = false;
 #pragma unroll
     for (int k = 0; k < (int)(sizeof(qn.pad) / sizeof(qn.pad[0])); ++k)
         qn.pad[k] = 0;
@@ -450,10 +466,18 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
             qn.child[c] = ref;
             continue;
         }
+        uint32_t span = 0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const CodeAxis &a = frame.axis[d];
-            qn.w[c][d] = a.down(nd.lo[c][d]) | (((uint32_t)kQMax - a.up(nd.hi[c][d])) << 16);
+            const uint32_t lo = a.down(nd.lo[c][d]), hi = a.up(nd.hi[c][d]);
+            qn.w[c][d] = lo | (((uint32_t)kQMax - hi) << 16);
+            span = max(span, hi - lo);
+        }
+        if (span <= kCrowdCodes && ref >= 0 && (c == 0 ? p - nd.range_l + 1 : nd.range_r - p) >= kCrowd) {
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                crowd = crowd || nd.lo[c][d] < nd.hi[c][d];
         }
         qn.child[c] = ref >= 0 ? ref : ~(p + c);
     }
@@ -462,6 +486,8 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
 #pragma unroll
     for (int k = 0; k < (int)(sizeof(QNode<D>) / 16); ++k)
         d4[k] = s4[k];
+    if (crowd)
+        *crowded = 1;  // whoever finds one stores the same word
 }
 
 template <int D>
@@ -482,7 +508,7 @@ __device__ void write_single_leaf_tree(Node<D> *node, QNode<D> *qnode, int kind,
     nd.range_r = index;
     store_node(node, nd);
     if (qnode)
-        store_qnode<D>(qnode, nd, index, kind, CodeFrame<D>(*hdr));
+        store_qnode<D>(qnode, nd, index, kind, CodeFrame<D>(*hdr), &hdr->crowded);
     hdr->root = index;
     hdr->height = 1;
 }
@@ -526,7 +552,7 @@ __device__ __forceinline__ void segment_of(int i, const int64_t *__restrict__ se
 // its own leaf position).
 template <int D>
 __global__ void quantize_nodes(const Node<D> *__restrict__ nodes, int n_nodes, const int64_t *__restrict__ seg,
-                               int nseg, int n, int kind, const TreeHeader *__restrict__ hdrs,
+                               int nseg, int n, int kind, TreeHeader *__restrict__ hdrs,
                                QNode<D> *__restrict__ qnodes)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -536,7 +562,7 @@ __global__ void quantize_nodes(const Node<D> *__restrict__ nodes, int n_nodes, c
     segment_of(p < n ? p : n - 1, seg, nseg, n, sg, ts, te);
     Node<D> nd;
     load_node(nodes, p, nd);
-    store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]));
+    store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]), &hdrs[sg].crowded);
 }
 
 
@@ -731,7 +757,7 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
             if (qnodes) {
                 int sg, ts, te;
                 segment_of(p, seg, nseg, n, sg, ts, te);
-                store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]));
+                store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]), &hdrs[sg].crowded);
             }
             continue;
         }
@@ -911,7 +937,7 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
             nd.range_r = r;
             store_node(np, nd);
             if (qnodes)
-                store_qnode<D>(qnodes + p, nd, p, kind, frame);
+                store_qnode<D>(qnodes + p, nd, p, kind, frame, &hdrs[sg].crowded);
             ref = p;
             if (l == ts && r == te) {
                 hdrs[sg].root = p;
@@ -975,6 +1001,7 @@ __global__ void empty_header(TreeHeader *hdr, int dim)
     for (int d = 0; d < kMaxDim; ++d)
         hdr->qscale[d] = 0.0f;
     hdr->qinv = 0.0;
+    hdr->crowded = 0;
     hdr->root = -1;
     hdr->height = 0;
     hdr->n = 0;
@@ -1196,6 +1223,7 @@ __global__ void forest_headers(const int64_t *__restrict__ seg, int T, const uin
         h.qscale[d] = 0.0f;
     }
     h.qinv = 0.0;
+    h.crowded = 0;
     if (n > 0)
         quant_frame<D>(h.lo, h.hi, h.qscale, &h.qinv);
 }

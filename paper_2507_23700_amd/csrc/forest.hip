@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kForestBlock) void k_forest_knn(
         ShortStack<KnnEntry> st(reinterpret_cast<KnnEntry *>(s_stack) + threadIdx.x, blockDim.x, stack_cap, spill);
         // the seed searches this tree's segment of the forest's sorted build keys
         const SeedKeys sk{keys, (uint64_t)tr << mbits, mbits / D};
-        if (FMT == 1 && kind != ARBORX_BOXES && h.qinv != 0.0) {
+        if (FMT == 1 && kind != ARBORX_BOXES && codes_serve(h)) {
             TopStack<KnnCode> ts(reinterpret_cast<KnnCode *>(s_stack) + threadIdx.x, blockDim.x, stack_cap,
                                  reinterpret_cast<KnnCode *>(spill), knn_code(-1, 0u));
             knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, h, q, best, ts, seed, sk);

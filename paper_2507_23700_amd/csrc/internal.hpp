@@ -29,6 +29,7 @@ struct TreeHeader {
     // much for that (quant_frame) or there is no extent: sphere walks then take
     // the float nodes.
     double qinv;
+    int32_t crowded;  // 1: points lie too close together for codes of that step (store_qnode)
 };
 
 // Device-resident per-call header of a CSR query, written by the scan.

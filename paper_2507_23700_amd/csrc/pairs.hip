@@ -103,7 +103,7 @@ __global__ void k_pair_degree(const Node<D> *__restrict__ nodes, const QNode<D> 
             atomicAdd(deg + q, 1);
         };
         if constexpr (Q) {
-            if (hdr->qinv != 0.0) {
+            if (codes_serve<D>(*hdr, r2)) {
                 TopStack<int> ts(s_stack + threadIdx.x, blockDim.x, stack_cap, spill, -1);
                 auto f1 = [&](int at, bool h0, int i0, bool h1, int i1) {
                     if (h0 || h1) {
@@ -113,7 +113,7 @@ __global__ void k_pair_degree(const Node<D> *__restrict__ nodes, const QNode<D> 
                     }
                 };
                 traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
-            } else {  // no common step of the frame: float nodes
+            } else {
                 traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
             }
         } else {
@@ -289,7 +289,7 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
         ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, stack_cap, spill);
         auto f = [&](int j, int q, int qid, float) { pair(j, q, qid); };
         if constexpr (Q) {
-            if (hdr->qinv != 0.0) {
+            if (codes_serve<D>(*hdr, r2)) {
                 TopStack<int> ts(s_stack + threadIdx.x, blockDim.x, stack_cap, spill, -1);
                 int *mine = s_stack + (stack_cap > 2 ? stack_cap : 2) * blockDim.x + threadIdx.x;  // this thread's queue
                 int held = 0;
@@ -327,7 +327,7 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
                 };
                 traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
                 settle();
-            } else {  // no common step of the frame: float nodes
+            } else {
                 traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
             }
         } else {

@@ -917,7 +917,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(knn_waves<D, K, WAVE, FMT>()))) vo
     } else {
         KnnEntry spill[kSpill];
         ShortStack<KnnEntry> st(reinterpret_cast<KnnEntry *>(s_stack) + threadIdx.x, blockDim.x, stack_cap, spill);
-        if (FMT == 1 && kind != ARBORX_BOXES && hdr->qinv != 0.0) {
+        if (FMT == 1 && kind != ARBORX_BOXES && codes_serve(*hdr)) {
             TopStack<KnnCode> ts(reinterpret_cast<KnnCode *>(s_stack) + threadIdx.x, blockDim.x, stack_cap,
                                  reinterpret_cast<KnnCode *>(spill), knn_code(-1, 0u));
             knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, *hdr, q, best, ts, seed,
