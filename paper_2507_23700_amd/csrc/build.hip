@@ -50,27 +50,28 @@ __device__ __forceinline__ float quant_scale(float lo, float hi)
 }
 
 // The frame of a tree: one step for every dimension, the largest of them, so
-// that walks measure distances in codes (CodeBall), unless some extent is
+// that walks measure distances in codes (CodeMetric), unless some extent is
 // below 1/256 of the largest; that keeps at least 256 codes across every
-// extent, and the largest extent has no finer codes either way.  Nor when the
-// step is so small that 1/step^2 leaves the range of float32, in which the
-// nearest searches turn their bound into codes.
-constexpr float kLeastStep = 1e-19f;
+// extent, and the largest extent has no finer codes either way.  Else each
+// dimension has its own step (the largest where it has no extent), and the
+// walks weigh the gaps of the dimensions.
 template <int D>
-__device__ void quant_frame(const float *lo, const float *hi, float *qscale, double *qinv)
+__device__ void quant_frame(const float *lo, const float *hi, TreeHeader &h)
 {
     float most = 0.0f, least = INFINITY;
     for (int d = 0; d < D; ++d) {
-        qscale[d] = quant_scale(lo[d], hi[d]);
-        most = fmaxf(most, qscale[d]);
-        if (qscale[d] > 0.0f)
-            least = fminf(least, qscale[d]);
+        h.qscale[d] = quant_scale(lo[d], hi[d]);
+        most = fmaxf(most, h.qscale[d]);
+        if (h.qscale[d] > 0.0f)
+            least = fminf(least, h.qscale[d]);
     }
-    *qinv = 0.0;
-    if (most >= kLeastStep && most < INFINITY && most * (1.0f / 256.0f) <= least) {
-        *qinv = 1.0 / (double)most;
-        for (int d = 0; d < D; ++d)
-            qscale[d] = most;
+    h.qinv = most > 0.0f && most < INFINITY ? 1.0 / (double)most : 0.0;
+    h.even = most * (1.0f / 256.0f) <= least;
+    for (int d = 0; d < D; ++d) {
+        if (h.even || !(h.qscale[d] > 0.0f))
+            h.qscale[d] = most;
+        h.qweight[d] = (float)((double)h.qscale[d] * h.qinv);
+        h.qinvs[d] = h.qinv > 0.0 ? 1.0 / (double)h.qscale[d] : 0.0;
     }
 }
 
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(kBuildBlock) void bounds_final(const float *__restr
     }
     __syncthreads();
     if (d == 0) {
-        quant_frame<D>(s_lo[0], s_hi[0], hdr->qscale, &hdr->qinv);
+        quant_frame<D>(s_lo[0], s_hi[0], *hdr);
         hdr->crowded = 0;
         hdr->n = (int32_t)n;
         hdr->root = n > 0 ? 0 : -1;
@@ -427,22 +428,23 @@ __device__ __forceinline__ void load_value_box(const float *values, int kind, ui
 // leaf position: the left child of node p is leaf p, the right child leaf
 // p + 1.
 //
-// A tree is crowded where its frame is coarse for its points: some subtree of
-// kCrowd or more values lies within kCrowdCodes codes, rounded outward, in
-// every dimension (and not all in one place, where no box can be left out).
-// In codes every box around there is next to every query, so a search leaves
-// nothing out and meets the whole crowd; float boxes have no such limit (see
-// codes_serve).  One stray point far from 10^6 uniform ones in 3D widens the
-// frame until a code is 1/S of the mean spacing; nearest 8 over codes and over
-// float nodes: S = 20 466 and 564 us, 7 621 and 703, 5 789 and 787, 4 899 and
-// 808, 2.2 1956 and 1063, 1.1 4063 and 1064, where the largest subtree within
-// four codes has 3, 6, 7, 9, 21 and 79 points.  With 10^4 of 10^6 points inside two
-// codes 4960 and 482 us.
+// Returns whether a child of the node makes its tree crowded (whoever finds one
+// stores the same word in the header): the frame is coarse for its points, some
+// subtree of kCrowd or more values lies within kCrowdCodes codes, rounded
+// outward, in every dimension (and not all in one place, where no box can be
+// left out).  In codes every box around there is next to every query, so a
+// search leaves nothing out and meets the whole crowd; float boxes have no such
+// limit (see codes_serve).  One stray point far from 10^6 uniform ones in 3D
+// widens the frame until a code is 1/S of the mean spacing; nearest 8 over codes
+// and over float nodes: S = 20 466 and 564 us, 7 621 and 703, 5 789 and 787, 4
+// 899 and 808, 2.2 1956 and 1063, 1.1 4063 and 1064, where the largest subtree
+// within four codes has 3, 6, 7, 9, 21 and 79 points.  With 10^4 of 10^6 points
+// inside two codes 4960 and 482 us.
 constexpr uint32_t kCrowdCodes = 5;
 constexpr int kCrowd = 8;
 template <int D>
-__device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const Node<D> &nd, int p, int kind,
-                                            const CodeFrame<D> &frame, int32_t *crowded)
+__device__ __forceinline__ bool store_qnode(QNode<D> *__restrict__ dst, const Node<D> &nd, int p, int kind,
+                                            const CodeFrame<D> &frame)
 {
     QNode<D> qn;
     bool crowd = false;
@@ -486,8 +488,7 @@ __device__ __forceinline__ void store_qnode(QNode<D> *__restrict__ dst, const No
 #pragma unroll
     for (int k = 0; k < (int)(sizeof(QNode<D>) / 16); ++k)
         d4[k] = s4[k];
-    if (crowd)
-        *crowded = 1;  // whoever finds one stores the same word
+    return crowd;
 }
 
 template <int D>
@@ -508,7 +509,7 @@ __device__ void write_single_leaf_tree(Node<D> *node, QNode<D> *qnode, int kind,
     nd.range_r = index;
     store_node(node, nd);
     if (qnode)
-        store_qnode<D>(qnode, nd, index, kind, CodeFrame<D>(*hdr), &hdr->crowded);
+        store_qnode<D>(qnode, nd, index, kind, CodeFrame<D>(*hdr));
     hdr->root = index;
     hdr->height = 1;
 }
@@ -562,7 +563,8 @@ __global__ void quantize_nodes(const Node<D> *__restrict__ nodes, int n_nodes, c
     segment_of(p < n ? p : n - 1, seg, nseg, n, sg, ts, te);
     Node<D> nd;
     load_node(nodes, p, nd);
-    store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]), &hdrs[sg].crowded);
+    if (store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg])))
+        hdrs[sg].crowded = 1;
 }
 
 
@@ -757,7 +759,8 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
             if (qnodes) {
                 int sg, ts, te;
                 segment_of(p, seg, nseg, n, sg, ts, te);
-                store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg]), &hdrs[sg].crowded);
+                if (store_qnode<D>(qnodes + p, nd, p, kind, CodeFrame<D>(hdrs[sg])))
+                    hdrs[sg].crowded = 1;
             }
             continue;
         }
@@ -842,6 +845,7 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
         const CodeFrame<D> frame(hdrs[sg]);
         // split keys at the subtree's two ends (none at an end of the tree)
         uint64_t kl = l == ts ? ~0ull : split_key(codes, l - 1), kr = r == te ? ~0ull : split_key(codes, r);
+        bool crowd = false;
         // a climb visits at most n-1 splits
         for (int guard = 0; guard < n; ++guard) {
             if (p < 0 || p > n - 2)
@@ -937,7 +941,7 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
             nd.range_r = r;
             store_node(np, nd);
             if (qnodes)
-                store_qnode<D>(qnodes + p, nd, p, kind, frame, &hdrs[sg].crowded);
+                crowd |= store_qnode<D>(qnodes + p, nd, p, kind, frame);
             ref = p;
             if (l == ts && r == te) {
                 hdrs[sg].root = p;
@@ -952,6 +956,8 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
                 side = 1;
             }
         }
+        if (crowd)
+            hdrs[sg].crowded = 1;
     }
     __syncthreads();
     const unsigned long long w = s_word[tid];
@@ -1001,6 +1007,7 @@ __global__ void empty_header(TreeHeader *hdr, int dim)
     for (int d = 0; d < kMaxDim; ++d)
         hdr->qscale[d] = 0.0f;
     hdr->qinv = 0.0;
+    hdr->even = 1;
     hdr->crowded = 0;
     hdr->root = -1;
     hdr->height = 0;
@@ -1223,9 +1230,10 @@ __global__ void forest_headers(const int64_t *__restrict__ seg, int T, const uin
         h.qscale[d] = 0.0f;
     }
     h.qinv = 0.0;
+    h.even = 1;
     h.crowded = 0;
     if (n > 0)
-        quant_frame<D>(h.lo, h.hi, h.qscale, &h.qinv);
+        quant_frame<D>(h.lo, h.hi, h);
 }
 
 template <int D>

@@ -25,10 +25,10 @@ struct TreeHeader {
     float lo[kMaxDim];
     float hi[kMaxDim];
     float qscale[kMaxDim];  // quantized-node frame: coordinate = lo + code * qscale
-    // One step for every dimension, 1/qscale; 0 where the extents differ too
-    // much for that (quant_frame) or there is no extent: sphere walks then take
-    // the float nodes.
-    double qinv;
+    float qweight[kMaxDim];  // qscale over the largest one
+    double qinvs[kMaxDim];   // 1 over qscale
+    double qinv;      // 1 over the largest qscale; 0 where there is no extent
+    int32_t even;     // 1: one step for every dimension
     int32_t crowded;  // 1: points lie too close together for codes of that step (store_qnode)
 };
 

@@ -112,7 +112,10 @@ __global__ void k_pair_degree(const Node<D> *__restrict__ nodes, const QNode<D> 
                             f(0, at + 1, i1, 0.0f);
                     }
                 };
-                traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+                if (hdr->even)
+                    traverse_codes<D, 1, true, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+                else
+                    traverse_codes<D, 1, true, false>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
             } else {
                 traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);
             }
@@ -325,7 +328,10 @@ __global__ void k_dbscan_pairs(const Node<D> *__restrict__ nodes, const QNode<D>
                     if (__any(held > kPairQueue - 2))
                         settle();
                 };
-                traverse_codes<D, 1, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+                if (hdr->even)
+                    traverse_codes<D, 1, true, true>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
+                else
+                    traverse_codes<D, 1, true, false>(qnodes, *hdr, (int)(n - 1), pred, (int)p0, ts, f1);
                 settle();
             } else {
                 traverse_pairs_packet<D, W>(nodes, hdr->root, (int)(n - 1), (int)p0, pred, st, f);

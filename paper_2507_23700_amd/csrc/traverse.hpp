@@ -771,6 +771,98 @@ __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__rest
     }
 }
 
+// Distances in the codes of a tree's frame, in units of its largest step: the
+// sum of the squared gaps of the dimensions between a query's code words and a
+// child's words is at most the squared distance.  In a frame with one step the
+// sum is of whole numbers (a saturating pair subtraction and a dot product a
+// dimension); in one with a step for each dimension it is of floats, every gap
+// times its step (five instructions a dimension).
+template <int D, bool EVEN>
+struct CodeMetric {
+    typedef uint32_t Sum;
+    __device__ __forceinline__ explicit CodeMetric(const TreeHeader &) {}
+    __device__ __forceinline__ double inv(const TreeHeader &h, int) const { return h.qinv; }
+    __device__ __forceinline__ double weight(int) const { return 1.0; }
+    __device__ __forceinline__ Sum gap2(const uint32_t (&q)[D], const uint32_t (&w)[D]) const
+    {
+        return code_gap2<D>(q, w);
+    }
+    // a bound on the sum from one on the squared distance, at least as large
+    __device__ __forceinline__ static Sum bound(double r)
+    {
+        return r < 4294967295.0 ? (uint32_t)fmax(r, 0.0) : UINT32_MAX;
+    }
+};
+template <int D>
+struct CodeMetric<D, false> {
+    typedef float Sum;
+    float wt[D];
+    __device__ __forceinline__ explicit CodeMetric(const TreeHeader &h)
+    {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            wt[d] = h.qweight[d];
+    }
+    __device__ __forceinline__ double inv(const TreeHeader &h, int d) const { return h.qinvs[d]; }
+    __device__ __forceinline__ double weight(int d) const { return (double)wt[d]; }
+    __device__ __forceinline__ float gap(uint32_t q, uint32_t w, int d) const
+    {
+        const ushort2_t one = {1, 1};
+        return (float)__builtin_amdgcn_udot2(code_gap(q, w), one, 0u, false) * wt[d];
+    }
+    __device__ __forceinline__ Sum gap2(const uint32_t (&q)[D], const uint32_t (&w)[D]) const
+    {
+        float acc = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const float g = gap(q[d], w[d], d);
+            acc = fmaf(g, g, acc);
+        }
+        return acc;
+    }
+    __device__ __forceinline__ static Sum bound(double r)
+    {
+        return r < 3.0e38 ? (float)(fmax(r, 0.0) * (1.0 + 0x1p-22)) : INFINITY;
+    }
+};
+
+// A ball around a query in these codes: a box whose gaps sum to more than r2
+// holds no value within the radius.  A value matches when its float32 squared
+// distance, within a factor 1 +- 2^-20 and 16 * 2^-149 of the real one, is at
+// most the ball's; a float sum of gaps is off by a factor of 1 +- 2^-20 too.  A
+// query outside the frame takes the excess e past it off the gaps of that
+// dimension: (e + g)^2 = e^2 + g (2 e + g), so r2 lacks the sum of the e^2, and
+// a search whose radius is about e long also counts the middle terms
+// (CodeExcess).  A ball that does not reach the frame meets only boxes that
+// span it.
+template <int D, class Sum>
+struct CodeBall {
+    uint32_t q[D];
+    Sum r2;
+};
+template <int D, bool EVEN>
+__device__ __forceinline__ void code_ball(const float (&c)[D], float r2, const TreeHeader &h,
+                                          const CodeMetric<D, EVEN> &metric,
+                                          CodeBall<D, typename CodeMetric<D, EVEN>::Sum> &ball)
+{
+    double past = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        double e;
+        ball.q[d] = code_query(c[d], h.lo[d], h.hi[d], metric.inv(h, d), e);
+        e *= metric.weight(d) * (EVEN ? 1.0 : 1.0 - 0x1p-22);
+        past += e * e;
+    }
+    const double r = ((double)r2 * (1.0 + (EVEN ? 0x1p-18 : 0x1p-17)) + 0x1p-144) * h.qinv * h.qinv *
+                         (1.0 + 0x1p-30) + (EVEN ? 1.0 : 0.0) - fmin(past, 1.0e300);
+    ball.r2 = metric.bound(r);
+    if (r < 0.0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            ball.q[d] = 0;
+    }
+}
+
 // Depth-first walk of NQ neighbouring sphere queries over the quantized nodes
 // of a tree of points, in the codes of its frame: an internal child costs one
 // saturating pair subtraction and one dot product per dimension instead of
@@ -789,15 +881,16 @@ __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__rest
 // walk fell from 1.5e9 to 1.0e9 vector instructions and from 3.28 to 2.70 ms;
 // CSR with distances of 5*10^5 6D mixture points, build included, from 3.95
 // to 3.09 ms; DBSCAN of 5*10^6 points from 5.3 to 4.7 ms.
-template <int D, int NQ, bool PAIRS, class F, class S = NeverStop>
+template <int D, int NQ, bool PAIRS, bool EVEN, class F, class S = NeverStop>
 __device__ __forceinline__ void traverse_codes(const QNode<D> *__restrict__ nodes, const TreeHeader &h, int n_nodes,
                                                const Sphere<D> (&pred)[NQ], int lpos, TopStack<int> &st, F &f,
                                                const S &stop = S())
 {
-    CodeBall<D> ball[NQ];
+    const CodeMetric<D, EVEN> metric(h);
+    CodeBall<D, typename CodeMetric<D, EVEN>::Sum> ball[NQ];
 #pragma unroll
     for (int j = 0; j < NQ; ++j)
-        code_ball<D>(pred[j].c, pred[j].r2, h.lo, h.hi, h.qinv, ball[j]);
+        code_ball<D, EVEN>(pred[j].c, pred[j].r2, h, metric, ball[j]);
     const unsigned last = (unsigned)n_nodes - 1u;
     int cur = h.root;
     QNode<D> nd;
@@ -812,8 +905,8 @@ __device__ __forceinline__ void traverse_codes(const QNode<D> *__restrict__ node
         float d0[NQ], d1[NQ];
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-            g0 = g0 | (code_gap2<D>(ball[j].q, nd.w[0]) <= ball[j].r2);
-            g1 = g1 | (code_gap2<D>(ball[j].q, nd.w[1]) <= ball[j].r2);
+            g0 = g0 | (metric.gap2(ball[j].q, nd.w[0]) <= ball[j].r2);
+            g1 = g1 | (metric.gap2(ball[j].q, nd.w[1]) <= ball[j].r2);
             d0[j] = point_d2<D>(pred[j].c, nd.w[0]);
             d1[j] = point_d2<D>(pred[j].c, nd.w[1]);
             h0[j] = c0 < 0 && (!PAIRS || cur > lpos) && d0[j] <= pred[j].r2;
@@ -1414,13 +1507,53 @@ __device__ __forceinline__ void knn_search_wave(const Node<D> *__restrict__ node
     }
 }
 
+// The sums a kNN walk over codes orders and prunes by, as words whose order is
+// theirs, and the bound on them from k d^2 + a (a NaN, infinity times a k of zero,
+// bounds nothing): in a frame with one step, for a query inside it and for one
+// past it; in a frame with a step for each dimension, for both.
+template <int D>
+struct KnnGap {
+    const uint32_t (&q)[D];
+    __device__ __forceinline__ uint32_t sum(const uint32_t (&w)[D]) const { return code_gap2<D>(q, w); }
+    __device__ __forceinline__ uint32_t bound(float fb) const { return fb < 4.29e9f ? (uint32_t)fb : UINT32_MAX; }
+};
+template <int D>
+struct KnnGapPast {
+    const uint32_t (&q)[D];
+    CodeExcess<D> ex;
+    __device__ __forceinline__ uint32_t sum(const uint32_t (&w)[D]) const { return ex.gap2(q, w); }
+    __device__ __forceinline__ uint32_t bound(float fb) const
+    {
+        return fb < 4.29e9f ? (uint32_t)fmaxf(fb, 0.0f) : UINT32_MAX;
+    }
+};
+template <int D>
+struct KnnGapUneven {
+    const uint32_t (&q)[D];
+    CodeMetric<D, false> metric;
+    float e2[D];  // twice the excess, rounded down
+    __device__ __forceinline__ uint32_t sum(const uint32_t (&w)[D]) const
+    {
+        float acc = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const float g = metric.gap(q[d], w[d], d);
+            acc = fmaf(g, g + e2[d], acc);
+        }
+        return __float_as_uint(acc);
+    }
+    __device__ __forceinline__ uint32_t bound(float fb) const
+    {
+        return __float_as_uint(fb < 3.0e38f ? fmaxf(fb, 0.0f) : INFINITY);
+    }
+};
+
 // kNN over the quantized nodes of a tree of points in the codes of its frame
 // (see traverse_codes): as knn_search, seeded and software-pipelined, with
 // internal children ordered and pruned by their squared code gaps against the
 // bound in codes, and leaf children offered with their exact distances.  The
 // bound in codes, k d^2 + a, is rounded up in float32: k and a hold 1/s^2 with
-// the margins of code_ball and more (a frame's step keeps them in range, see
-// quant_frame).  A wavefront with a query outside the
+// the margins of code_ball and more.  A wavefront with a query outside the
 // frame counts the excesses past it (CodeExcess), or it would enter every node
 // near the projection on the frame: k = 1 between clouds of unlike extents
 // took 6.6 ms without them, 1.8 over float nodes.  Half the loads of the float nodes and no decoding:
@@ -1429,10 +1562,10 @@ __device__ __forceinline__ void knn_search_wave(const Node<D> *__restrict__ node
 // LDS and merging eight at a time with a sorting network took 13 % fewer
 // vector instructions at k = 16, none fewer at k = 8, and 6.5 and 6.7 ms: the
 // bound lags and the queue takes LDS.)
-template <int D, int K, bool PAST, class G>
+template <int D, int K, class G>
 __device__ __forceinline__ void knn_walk_codes(const QNode<D> *__restrict__ nodes, int n_nodes, const TreeHeader &hdr,
                                                const float (&q)[D], TopK<K> &best, TopStack<KnnCode> &st, float k,
-                                               float a, const G &gap2)
+                                               float a, const G &gap)
 {
     const unsigned last = (unsigned)n_nodes - 1u;
     int cur = hdr.root;
@@ -1443,13 +1576,12 @@ __device__ __forceinline__ void knn_walk_codes(const QNode<D> *__restrict__ node
             break;
         KnnCode deferred = st.top();
         const int c0 = nd.child[0], c1 = nd.child[1];
-        const uint32_t s0 = gap2(nd.w[0]), s1 = gap2(nd.w[1]);
+        const uint32_t s0 = gap.sum(nd.w[0]), s1 = gap.sum(nd.w[1]);
         // leaf children as keys, the other slots above every key
         const double none = TopK<K>::pack(__uint_as_float(0x7fc00000u), INT32_MAX);
         const double v0 = c0 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[0]), ~c0) : none;
         const double v1 = c1 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[1]), ~c1) : none;
-        const float fb = fmaf(best.bound(), k, a);
-        const uint32_t bound = fb < 4.29e9f ? (uint32_t)(PAST ? fmaxf(fb, 0.0f) : fb) : UINT32_MAX;
+        const uint32_t bound = gap.bound(fmaf(best.bound(), k, a));
         const bool k0 = c0 >= 0 && s0 <= bound;
         const bool k1 = c1 >= 0 && s1 <= bound;
         const bool near1 = k1 && (!k0 || s1 < s0);
@@ -1483,22 +1615,33 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
         seed_window<D, K>(leaves, kind, hdr, leaf_position<D>(keys, hdr, q), q, best, seed);
     uint32_t qc[D];
     double e[D], past = 0.0;
+    const double k = hdr.qinv * hdr.qinv * (1.0 + 0x1p-19), a = hdr.qinv * hdr.qinv * 0x1p-144;
+    if (hdr.even) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv, e[d]);
-        past += e[d] * e[d];
-    }
-    const double k = hdr.qinv * hdr.qinv * (1.0 + 0x1p-19), a = hdr.qinv * hdr.qinv * 0x1p-144 + 2.0;
-    if (!__any(past > 1.0)) {
-        knn_walk_codes<D, K, false>(nodes, n_nodes, hdr, q, best, st, (float)k, (float)a,
-                                    [&](const uint32_t(&w)[D]) { return code_gap2<D>(qc, w); });
+        for (int d = 0; d < D; ++d) {
+            qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv, e[d]);
+            past += e[d] * e[d];
+        }
+        if (!__any(past > 1.0)) {
+            knn_walk_codes<D, K>(nodes, n_nodes, hdr, q, best, st, (float)k, (float)(a + 2.0), KnnGap<D>{qc});
+            return;
+        }
+        const KnnGapPast<D> gap{qc, CodeExcess<D>(e)};
+        const double unit = ldexp(1.0, -(int)(gap.ex.shift & 15u));
+        const double rest = (a + 2.0 - past * (1.0 - 0x1p-22)) * unit;
+        knn_walk_codes<D, K>(nodes, n_nodes, hdr, q, best, st, (float)(k * unit), (float)fmax(rest + 1.0, -3.0e38), gap);
         return;
     }
-    const CodeExcess<D> ex(e);
-    const double unit = ldexp(1.0, -(int)(ex.shift & 15u));
-    const double rest = (a - past * (1.0 - 0x1p-22)) * unit;
-    knn_walk_codes<D, K, true>(nodes, n_nodes, hdr, q, best, st, (float)(k * unit), (float)fmax(rest + 1.0, -3.0e38),
-                               [&](const uint32_t(&w)[D]) { return ex.gap2(qc, w); });
+    KnnGapUneven<D> gap{qc, CodeMetric<D, false>(hdr)};
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], gap.metric.inv(hdr, d), e[d]);
+        e[d] *= gap.metric.weight(d) * (1.0 - 0x1p-22);
+        gap.e2[d] = (float)(2.0 * e[d] * (1.0 - 0x1p-23));
+        past += e[d] * e[d];
+    }
+    knn_walk_codes<D, K>(nodes, n_nodes, hdr, q, best, st, (float)(k * (1.0 + 0x1p-18)),
+                         (float)fmax(a + 0x1p-100 - past * (1.0 - 0x1p-22), -3.0e38), gap);
 }
 
 // kNN over quantized nodes: as knn_search (seeded, software-pipelined),
@@ -1597,15 +1740,20 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
 // Node slots of a single tree (one-value trees still have one node).
 __device__ __forceinline__ int node_count(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
 
-// Whether searches over points walk the codes of the tree's frame: it has one
-// step for every dimension, and no crowd of points that the codes cannot tell
-// apart (store_qnode).  A ball much wider than a code meets few more boxes in
+// Whether searches over points walk the codes of the tree's frame: no crowd of
+// points is there that the codes cannot tell apart (store_qnode).  A ball much wider than a code meets few more boxes in
 // codes than in floats: 10^6 uniform 3D points 4 codes apart, counts over codes
 // and over float nodes 537 and 506 us at a radius of 5 codes, 938 and 955 at 8,
 // 3622 and 4243 at 16; 2.2 codes apart 5626 and 5176 at 8, 26431 and 28397 at 16;
 // 3*10^5 2D points 1.1 codes apart 79 and 70 at 2, 122 and 126 at 4.
+// The nearest searches turn their bound into codes in float32, so 1/step^2 has
+// to lie in its range.
 template <int D> constexpr double kWideBall = D <= 2 ? 3.0 : 12.0;  // codes
-__device__ __forceinline__ bool codes_serve(const TreeHeader &h) { return h.qinv != 0.0 && !h.crowded; }
+constexpr double kLeastStep = 1e-19;
+__device__ __forceinline__ bool codes_serve(const TreeHeader &h)
+{
+    return h.qinv != 0.0 && !h.crowded && h.qinv <= 1.0 / kLeastStep;
+}
 template <int D>
 __device__ __forceinline__ bool codes_serve(const TreeHeader &h, float r2)
 {
@@ -1628,7 +1776,10 @@ __device__ __forceinline__ void walk_quantized(const Node<D> *__restrict__ nodes
                 auto g1 = [&](int, int idx, float d2) { f(idx, d2); };
                 auto g = each_hit(g1);
                 const P preds[1] = {pred};
-                traverse_codes<D, 1, false>(qnodes, h, n_nodes, preds, -1, st, g, stop);
+                if (h.even)
+                    traverse_codes<D, 1, false, true>(qnodes, h, n_nodes, preds, -1, st, g, stop);
+                else
+                    traverse_codes<D, 1, false, false>(qnodes, h, n_nodes, preds, -1, st, g, stop);
             } else {
                 ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
                 traverse_spatial<D>(nodes, h.root, n_nodes, pred, st, f, stop);
@@ -1655,7 +1806,10 @@ __device__ __forceinline__ void walk_quantized_packet(const Node<D> *__restrict_
     if (kind != ARBORX_BOXES && codes_serve<D>(h, r2)) {
         TopStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill, -1);
         auto g = each_hit(f);
-        traverse_codes<D, NQ, false>(qnodes, h, n_nodes, pred, -1, st, g);
+        if (h.even)
+            traverse_codes<D, NQ, false, true>(qnodes, h, n_nodes, pred, -1, st, g);
+        else
+            traverse_codes<D, NQ, false, false>(qnodes, h, n_nodes, pred, -1, st, g);
         return;
     }
     ShortStack<int> st(s_stack + threadIdx.x, blockDim.x, cap, spill);
