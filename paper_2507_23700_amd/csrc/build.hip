@@ -80,10 +80,10 @@ __device__ void quant_frame(const float *lo, const float *hi, TreeHeader &h)
 // most; `slop` is that in codes, and a hair for the arithmetic here.
 struct CodeAxis {
     double lo, inv, slop;
-    __device__ __forceinline__ void set(float l, float h, float scale)
+    __device__ __forceinline__ void set(float l, float h, double i)
     {
         lo = l;
-        inv = scale > 0.0f ? 1.0 / (double)scale : 0.0;
+        inv = i;
         slop = (fmax(fabs((double)l), fabs((double)h)) * 0x1.01p-24 + 0x1p-149) * inv + 0x1p-10;
     }
     __device__ __forceinline__ uint32_t down(float x) const
@@ -103,7 +103,7 @@ struct CodeFrame {
     {
 #pragma unroll
         for (int d = 0; d < D; ++d)
-            axis[d].set(h.lo[d], h.hi[d], h.qscale[d]);
+            axis[d].set(h.lo[d], h.hi[d], h.qinvs[d]);
     }
 };
 
@@ -422,26 +422,46 @@ __device__ __forceinline__ void load_value_box(const float *values, int kind, ui
     }
 }
 
+// A tree is crowded where its frame is coarse for its points: some subtree of
+// kCrowd or more values lies within kCrowdCodes codes, rounded outward, in
+// every dimension (and not all in one place, where no box can be left out).
+// In codes every box around there is next to every query, so a search leaves
+// nothing out and meets the whole crowd; float boxes have no such limit (see
+// codes_serve).  One stray point far from 10^6 uniform ones in 3D widens the
+// frame until a code is 1/S of the mean spacing; nearest 8 over codes and over
+// float nodes: S = 20 466 and 564 us, 7 621 and 703, 5 789 and 787, 4 899 and
+// 808, 2.2 1956 and 1063, 1.1 4063 and 1064, where the largest subtree within
+// four codes has 3, 6, 7, 9, 21 and 79 points.  With 10^4 of 10^6 points inside
+// two codes 4960 and 482 us.
+// It is looked for in the subtrees that lie in one chunk of the climb: some part
+// of a crowd over several chunks does, and the second phase, one chain of steps,
+// took 24.5 us instead of 21.2 at 2*10^4 points when it looked at every node.
+constexpr uint32_t kCrowdCodes = 5;
+constexpr int kCrowd = 8;
+template <int D>
+__device__ __forceinline__ bool is_crowd(const float *lo, const float *hi, uint32_t span, int values)
+{
+    bool apart = false;
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        apart = apart || lo[d] < hi[d];
+    return apart && span <= kCrowdCodes && values >= kCrowd;
+}
+template <int D>
+__device__ __forceinline__ bool is_crowd(const float *lo, const float *hi, const CodeFrame<D> &frame, int values)
+{
+    uint32_t span = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        span = max(span, frame.axis[d].up(hi[d]) - frame.axis[d].down(lo[d]));
+    return is_crowd<D>(lo, hi, span, values);
+}
+
 // Quantized form of float node p of a tree with the given frame.  A point tree's
 // leaf child keeps its point and reference unchanged (the point's float words
 // fill that child's code bytes); a box tree's leaf child becomes its sorted
 // leaf position: the left child of node p is leaf p, the right child leaf
-// p + 1.
-//
-// Returns whether a child of the node makes its tree crowded (whoever finds one
-// stores the same word in the header): the frame is coarse for its points, some
-// subtree of kCrowd or more values lies within kCrowdCodes codes, rounded
-// outward, in every dimension (and not all in one place, where no box can be
-// left out).  In codes every box around there is next to every query, so a
-// search leaves nothing out and meets the whole crowd; float boxes have no such
-// limit (see codes_serve).  One stray point far from 10^6 uniform ones in 3D
-// widens the frame until a code is 1/S of the mean spacing; nearest 8 over codes
-// and over float nodes: S = 20 466 and 564 us, 7 621 and 703, 5 789 and 787, 4
-// 899 and 808, 2.2 1956 and 1063, 1.1 4063 and 1064, where the largest subtree
-// within four codes has 3, 6, 7, 9, 21 and 79 points.  With 10^4 of 10^6 points
-// inside two codes 4960 and 482 us.
-constexpr uint32_t kCrowdCodes = 5;
-constexpr int kCrowd = 8;
+// p + 1.  Returns whether a child is a crowd.
 template <int D>
 __device__ __forceinline__ bool store_qnode(QNode<D> *__restrict__ dst, const Node<D> &nd, int p, int kind,
                                             const CodeFrame<D> &frame)
@@ -476,11 +496,7 @@ __device__ __forceinline__ bool store_qnode(QNode<D> *__restrict__ dst, const No
             qn.w[c][d] = lo | (((uint32_t)kQMax - hi) << 16);
             span = max(span, hi - lo);
         }
-        if (span <= kCrowdCodes && ref >= 0 && (c == 0 ? p - nd.range_l + 1 : nd.range_r - p) >= kCrowd) {
-#pragma unroll
-            for (int d = 0; d < D; ++d)
-                crowd = crowd || nd.lo[c][d] < nd.hi[c][d];
-        }
+        crowd = crowd || is_crowd<D>(nd.lo[c], nd.hi[c], span, c == 0 ? p - nd.range_l + 1 : nd.range_r - p);
         qn.child[c] = ref >= 0 ? ref : ~(p + c);
     }
     float4 *d4 = reinterpret_cast<float4 *>(dst);
@@ -779,6 +795,9 @@ __global__ __launch_bounds__(chunk_leaves<D>()) void hierarchy_chunk_kernel(cons
             segment_of(p, seg, nseg, n, sg, ts, te);
             put_wait_key(*np, side == 0 ? (bound == ts ? ~0ull : s_key[bound - cs]) :
                                           (bound == te ? ~0ull : s_key[bound - cs + 1]));
+            if (qnodes && is_crowd<D>(s_lo[lp][side], s_hi[lp][side], CodeFrame<D>(hdrs[sg]),
+                                      side == 0 ? p - bound + 1 : bound - p))
+                hdrs[sg].crowded = 1;
         }
     }
 }
@@ -845,7 +864,8 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
         const CodeFrame<D> frame(hdrs[sg]);
         // split keys at the subtree's two ends (none at an end of the tree)
         uint64_t kl = l == ts ? ~0ull : split_key(codes, l - 1), kr = r == te ? ~0ull : split_key(codes, r);
-        bool crowd = false;
+        if (qnodes && is_crowd<D>(lo, hi, frame, r - l + 1))
+            hdrs[sg].crowded = 1;
         // a climb visits at most n-1 splits
         for (int guard = 0; guard < n; ++guard) {
             if (p < 0 || p > n - 2)
@@ -941,7 +961,7 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
             nd.range_r = r;
             store_node(np, nd);
             if (qnodes)
-                crowd |= store_qnode<D>(qnodes + p, nd, p, kind, frame);
+                store_qnode<D>(qnodes + p, nd, p, kind, frame);
             ref = p;
             if (l == ts && r == te) {
                 hdrs[sg].root = p;
@@ -956,8 +976,6 @@ __global__ __launch_bounds__(kTopBlock) void hierarchy_top_kernel(const uint64_t
                 side = 1;
             }
         }
-        if (crowd)
-            hdrs[sg].crowded = 1;
     }
     __syncthreads();
     const unsigned long long w = s_word[tid];

@@ -22,14 +22,15 @@ struct TreeHeader {
     int32_t height;  // edges on the longest root-to-leaf path
     int32_t n;       // values in the tree
     int32_t start;   // position of the tree's first leaf in the sorted leaf array
-    float lo[kMaxDim];
-    float hi[kMaxDim];
-    float qscale[kMaxDim];  // quantized-node frame: coordinate = lo + code * qscale
-    float qweight[kMaxDim];  // qscale over the largest one
-    double qinvs[kMaxDim];   // 1 over qscale
+    // what decides the walk, in the cache line of the root
     double qinv;      // 1 over the largest qscale; 0 where there is no extent
     int32_t even;     // 1: one step for every dimension
-    int32_t crowded;  // 1: points lie too close together for codes of that step (store_qnode)
+    int32_t crowded;  // 1: points lie too close together for codes of these steps (store_qnode)
+    float lo[kMaxDim];
+    float hi[kMaxDim];
+    float qscale[kMaxDim];   // quantized-node frame: coordinate = lo + code * qscale
+    float qweight[kMaxDim];  // qscale over the largest one
+    double qinvs[kMaxDim];   // 1 over qscale
 };
 
 // Device-resident per-call header of a CSR query, written by the scan.
