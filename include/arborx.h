@@ -82,10 +82,10 @@ typedef struct arborx_tuning {
                              and a box tree's decided on their exact records; 2 = four-wide nodes (two levels
                              per fetch).  Every format gives identical results.  Formats 1 and 2 are built only
                              while some operation asks for them when the tree is built; asking later is
-                             ARBORX_E_INVALID.  The defaults (arborx_set_tuning(NULL)): 1 for ARBORX_OP_SPATIAL
-                             and ARBORX_OP_REDUCE, 0 for ARBORX_OP_KNN, over trees and forests of points; under
-                             them a kNN over points also walks format 1, while trees and forests of boxes, and
-                             ones built without format 1, are walked on format 0 */
+                             ARBORX_E_INVALID.  The defaults (arborx_set_tuning(NULL)): 1 over trees and forests
+                             of points; trees and forests of boxes, and ones built without format 1, are walked
+                             on format 0.  In format 1 a nearest search, or one of a radius near the width of a
+                             code, takes the float boxes where points lie too close together for the codes */
     int32_t queries_per_thread; /* radius searches (CSR count pass of sphere queries, fused reductions) with
                                    the thread schedule on binary nodes: 1, 2 or 4 neighbouring queries
                                    answered by one thread in one walk over the union of their paths; 0 = by
@@ -137,7 +137,9 @@ arborx_status arborx_set_tuning(const arborx_tuning *tuning);
 /* Current traversal schedule (of ARBORX_OP_SPATIAL). [host] */
 arborx_status arborx_get_tuning(arborx_tuning *tuning);
 
-/* Per-operation forms: op is an arborx_op; NULL restores that operation's defaults. [host] */
+/* Per-operation forms: op is an arborx_op; NULL restores that operation's defaults.  The defaults are reported
+ * as they come to up to 3D over points; they also follow the dimension (in 6D workgroups of 64, 16 stack entries
+ * for a nearest search) and take smaller workgroups for few queries. [host] */
 arborx_status arborx_set_tuning_op(int32_t op, const arborx_tuning *tuning);
 arborx_status arborx_get_tuning_op(int32_t op, arborx_tuning *tuning);
 
@@ -151,7 +153,8 @@ arborx_status arborx_get_tuning_op(int32_t op, arborx_tuning *tuning);
  * used for ARBORX_OP_SPATIAL / ARBORX_OP_REDUCE, k for ARBORX_OP_KNN.  If the
  * environment variable ARBORX_TUNING_CACHE names a file, a choice recorded
  * there for the same operation, dimension, kind, k and size classes is reused
- * (*best_ms = -1) and new choices are appended.  Synchronises.
+ * as it was recorded, on float nodes where a structure was built without its
+ * format 1 (*best_ms = -1), and new choices are appended.  Synchronises.
  *   best [host, may be NULL] receives the chosen schedule; best_ms [host, may be NULL] its time.
  */
 arborx_status arborx_autotune(arborx_tree tree, int32_t op, const float *queries, int64_t m, float radius, int32_t k,

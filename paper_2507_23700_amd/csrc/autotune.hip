@@ -77,7 +77,11 @@ std::string cache_key(int op, int dim, int kind, int k, int64_t n, int64_t m)
     return buf;
 }
 
-bool cache_lookup(const std::string &key, Tuning &t)
+// A line holds what was launched: "defaults" 1 where the library's defaults
+// won, whose shape follows the launch.  Lines without that word are of versions
+// that recorded the defaults' fields as they stood and walked 6D trees by
+// values of their own; they still do.
+bool cache_lookup(const std::string &key, int op, int dim, Tuning &t)
 {
     const char *path = std::getenv("ARBORX_TUNING_CACHE");
     if (!path || !*path)
@@ -89,11 +93,24 @@ bool cache_lookup(const std::string &key, Tuning &t)
     bool found = false;
     while (std::fgets(line, sizeof(line), f)) {
         char k[200];
-        int block, order, stack, schedule, seed, nodes, packet;
+        int block, order, stack, schedule, seed, nodes, packet, defaults = -1;
         if (std::sscanf(line, "{\"key\": \"%199[^\"]\", \"block\": %d, \"order\": %d, \"stack\": %d, \"schedule\": %d, "
-                              "\"seed\": %d, \"nodes\": %d, \"packet\": %d",
-                        k, &block, &order, &stack, &schedule, &seed, &nodes, &packet) == 8 &&
+                              "\"seed\": %d, \"nodes\": %d, \"packet\": %d, \"defaults\": %d",
+                        k, &block, &order, &stack, &schedule, &seed, &nodes, &packet, &defaults) >= 8 &&
             key == k) {
+            found = true;
+            if (defaults == 1) {
+                t = default_tuning(op);
+                continue;
+            }
+            if (defaults < 0 && dim >= 6 && t.by_dim) {
+                if (op != OP_REDUCE)
+                    block = 64;
+                if (op == OP_KNN) {
+                    stack = 16;
+                    nodes = 1;
+                }
+            }
             t.block = block;
             t.order = order;
             t.stack = stack;
@@ -101,14 +118,14 @@ bool cache_lookup(const std::string &key, Tuning &t)
             t.seed = seed;
             t.nodes = nodes;
             t.packet = packet;
-            found = true;
+            t.saved = true;
         }
     }
     std::fclose(f);
     return found;
 }
 
-void cache_store(const std::string &key, const Tuning &t, double ms)
+void cache_store(const std::string &key, const arborx_tuning &t, bool defaults, double ms)
 {
     const char *path = std::getenv("ARBORX_TUNING_CACHE");
     if (!path || !*path)
@@ -118,9 +135,24 @@ void cache_store(const std::string &key, const Tuning &t, double ms)
         return;
     std::fprintf(f,
                  "{\"key\": \"%s\", \"block\": %d, \"order\": %d, \"stack\": %d, \"schedule\": %d, \"seed\": %d, "
-                 "\"nodes\": %d, \"packet\": %d, \"ms\": %.4f}\n",
-                 key.c_str(), t.block, t.order, t.stack, t.schedule, t.seed, t.nodes, t.packet, ms);
+                 "\"nodes\": %d, \"packet\": %d, \"defaults\": %d, \"ms\": %.4f}\n",
+                 key.c_str(), t.block, t.order, t.stack, t.schedule, t.seed_mode, t.node_format, t.queries_per_thread,
+                 defaults ? 1 : 0, ms);
     std::fclose(f);
+}
+
+// Make the winner the tuning of `op`.  The library's defaults on a structure
+// that lacks their node format are kept as the choice of what ran.
+void install(int op, Tuning &t, int dim, int usual, int ran, arborx_tuning *report)
+{
+    report_tuning(op, t, dim, ran, report);
+    if (is_default(t) && ran != usual) {
+        t.block = report->block;
+        t.stack = report->stack;
+        t.nodes = ran;
+        t.saved = true;
+    }
+    set_tuning_op(op, t);
 }
 
 }  // namespace
@@ -149,18 +181,10 @@ extern "C" arborx_status arborx_autotune(arborx_tree tree, int32_t op, const flo
         return st;
     const std::string key = cache_key(op, dim, kind, k, n, m);
     Tuning cached = tuning(op);
-    if (cache_lookup(key, cached)) {
+    if (cache_lookup(key, op, dim, cached)) {
         set_tuning_op(op, cached);
-        if (best) {
-            best->block = cached.block;
-            best->order = cached.order;
-            best->stack = cached.stack;
-            best->schedule = cached.schedule;
-            best->build = cached.build;
-            best->seed_mode = cached.seed;
-            best->queries_per_thread = cached.packet;
-            best->node_format = node_format_of(cached, op, dim, kind, false);
-        }
+        if (best)
+            report_tuning(op, cached, dim, node_format_of(cached, op, dim, kind, false), best);
         if (best_ms)
             *best_ms = -1.0;
         return ARBORX_OK;
@@ -324,20 +348,12 @@ extern "C" arborx_status arborx_autotune(arborx_tree tree, int32_t op, const flo
     }
     besti = keep_unless_faster(cands, besti);
     Tuning &b = cands[besti].t;
-    if (op == OP_KNN)  // the defaults choose kNN's format themselves: record the one that ran
-        b.nodes = node_format_of(b, op, dim, kind, false);
-    set_tuning_op(op, b);
-    cache_store(key, b, cands[besti].ms);
-    if (best) {
-        best->block = b.block;
-        best->order = b.order;
-        best->stack = b.stack;
-        best->schedule = b.schedule;
-        best->build = b.build;
-        best->seed_mode = b.seed;
-        best->queries_per_thread = b.packet;
-        best->node_format = node_format_of(b, op, dim, kind, false);
-    }
+    const int usual = node_format_of(b, op, dim, kind, false);
+    arborx_tuning report;
+    install(op, b, dim, usual, is_default(b) && !tree_has_format(tree, usual) ? 0 : usual, &report);
+    cache_store(key, report, is_default(b), cands[besti].ms);
+    if (best)
+        *best = report;
     if (best_ms)
         *best_ms = cands[besti].ms;
     return ARBORX_OK;
@@ -370,18 +386,10 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
     const std::string key = "forest " + cache_key(op, dim, 0, k, n, m);
     const Tuning base = tuning(op);
     Tuning cached = base;
-    if (cache_lookup(key, cached)) {
+    if (cache_lookup(key, op, dim, cached)) {
         set_tuning_op(op, cached);
-        if (best) {
-            best->block = cached.block;
-            best->order = cached.order;
-            best->stack = cached.stack;
-            best->schedule = cached.schedule;
-            best->build = cached.build;
-            best->seed_mode = cached.seed;
-            best->queries_per_thread = cached.packet;
-            best->node_format = forest_format(cached, op, forest);
-        }
+        if (best)
+            report_tuning(op, cached, dim, forest_format(cached, op, forest), best);
         if (best_ms)
             *best_ms = -1.0;
         return ARBORX_OK;
@@ -489,19 +497,11 @@ extern "C" arborx_status arborx_autotune_forest(arborx_forest forest, int32_t op
     }
     besti = keep_unless_faster(cands, besti);
     Tuning &b = cands[besti].t;
-    b.nodes = forest_format(b, op, forest);  // the defaults choose the format themselves: record the one that ran
-    set_tuning_op(op, b);
-    cache_store(key, b, cands[besti].ms);
-    if (best) {
-        best->block = b.block;
-        best->order = b.order;
-        best->stack = b.stack;
-        best->schedule = b.schedule;
-        best->build = b.build;
-        best->seed_mode = b.seed;
-        best->queries_per_thread = b.packet;
-        best->node_format = b.nodes;
-    }
+    arborx_tuning report;
+    install(op, b, dim, forest_default_format(op, forest), forest_format(b, op, forest), &report);
+    cache_store(key, report, is_default(b), cands[besti].ms);
+    if (best)
+        *best = report;
     if (best_ms)
         *best_ms = cands[besti].ms;
     return ARBORX_OK;

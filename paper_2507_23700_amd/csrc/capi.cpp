@@ -155,7 +155,7 @@ static thread_local std::string g_error;
 // and kNN run over quantized nodes (half the node loads; a point's leaf is
 // exact in its parent; node_format_of below), the CSR count one query per
 // thread.
-static Tuning default_tuning(int op)
+Tuning default_tuning(int op)
 {
     Tuning t;
     if (op == OP_KNN) {
@@ -170,22 +170,19 @@ static Tuning default_tuning(int op)
     return t;
 }
 
-bool default_shape(int op)
-{
-    const Tuning &t = tuning(op), d = default_tuning(op);
-    return t.by_dim && t.block == d.block && t.stack == d.stack;
-}
+bool is_default(const Tuning &t) { return t.by_dim && !t.saved; }
 
-void launch_shape(int op, int dim, int &block, int &stack)
+static void shape_of(const Tuning &t, int op, int dim, int &block, int &stack)
 {
-    const Tuning &t = tuning(op);
     block = t.block;
     stack = t.stack;
+    if (!is_default(t))
+        return;
     // kNN over codes up to 3D: 256 threads, whose neighbouring wavefronts share a compute unit's cache (k = 16 at
     // 10^7 points 5.71 ms, 5.84 with 64); in 6D 64 (k = 8 5.51 ms, 5.67 with 256) with 16 entries (7.87 with 8)
-    if (default_shape(op) && dim < 6 && op == OP_KNN)
+    if (dim < 6 && op == OP_KNN)
         block = 256;
-    if (t.by_dim && dim >= 6) {
+    if (dim >= 6) {
         if (op == OP_KNN) {
             block = 64;
             stack = 16;
@@ -194,6 +191,23 @@ void launch_shape(int op, int dim, int &block, int &stack)
         }
     }
 }
+
+void launch_shape(int op, int dim, int &block, int &stack) { shape_of(tuning(op), op, dim, block, stack); }
+
+void report_tuning(int op, const Tuning &t, int dim, int format, arborx_tuning *out)
+{
+    int block = 0, stack = 0;
+    shape_of(t, op, dim, block, stack);
+    out->block = block;
+    out->order = t.order;
+    out->stack = stack;
+    out->schedule = t.schedule;
+    out->build = t.build;
+    out->seed_mode = t.seed;
+    out->node_format = format;
+    out->queries_per_thread = t.packet;
+}
+
 static Tuning g_tuning[OP_KINDS] = {default_tuning(OP_SPATIAL), default_tuning(OP_REDUCE), default_tuning(OP_KNN)};
 
 const Tuning &tuning(int op) { return g_tuning[op >= 0 && op < OP_KINDS ? op : 0]; }
@@ -204,11 +218,7 @@ int node_format_of(const Tuning &t, int op, int dim, int kind, bool forest)
         return t.nodes;
     if (kind == ARBORX_BOXES)  // a box leaf is not exact in the node: its record is fetched again
         return 0;
-    if (forest)  // quantized unless a saved choice for the reductions names another format
-        return op == OP_KNN || t.nodes == 1 ? 1 : 0;
-    if (op == OP_KNN)  // four-wide nodes only where a saved choice of the autotuner names them
-        return t.nodes == 2 && dim < 6 ? 2 : 1;
-    return t.nodes;
+    return t.saved ? t.nodes : 1;
 }
 
 int node_format(int op, int dim, int kind, bool forest) { return node_format_of(tuning(op), op, dim, kind, forest); }
@@ -247,12 +257,17 @@ int tree_format(int op, const TreeDev &t)
 static int forest_format_of(const Tuning &t, int op, const ForestDev &f)
 {
     const int fmt = node_format_of(t, op, f.dim, f.kind, true);
-    return (fmt == 1 && !f.qnodes && t.by_dim) ? 0 : fmt;
+    return t.by_dim && ((fmt == 1 && !f.qnodes) || (fmt == 2 && !f.wnodes)) ? 0 : fmt;
 }
 
 int forest_format(int op, const ForestDev &f) { return forest_format_of(tuning(op), op, f); }
 
 int forest_format(const Tuning &t, int op, arborx_forest forest) { return forest_format_of(t, op, forest->dev); }
+
+int forest_default_format(int op, arborx_forest forest)
+{
+    return node_format_of(default_tuning(op), op, forest->dev.dim, forest->dev.kind, true);
+}
 
 arborx_status check_nodes(const void *qnodes, const void *wnodes, int64_t n, int fmt)
 {
@@ -839,7 +854,7 @@ const char *arborx_last_error(void) { return g_error.c_str(); }
 static arborx_status to_tuning(const arborx_tuning *t, const Tuning &base, Tuning &n)
 {
     n = base;
-    n.by_dim = false;  // a caller's tuning is used as given
+    n.by_dim = n.saved = false;  // a caller's tuning is used as given
     if (t->block) {
         if (t->block != 64 && t->block != 128 && t->block != 256)
             return fail(ARBORX_E_INVALID, "block must be 64, 128 or 256");
@@ -872,16 +887,10 @@ static arborx_status to_tuning(const arborx_tuning *t, const Tuning &base, Tunin
     return ARBORX_OK;
 }
 
-static void from_tuning(const Tuning &g, arborx_tuning *t)
+// As it comes to up to 3D over points.
+static void from_tuning(int op, const Tuning &g, arborx_tuning *t)
 {
-    t->block = g.block;
-    t->order = g.order;
-    t->stack = g.stack;
-    t->schedule = g.schedule;
-    t->build = g.build;
-    t->seed_mode = g.seed;
-    t->node_format = g.nodes;
-    t->queries_per_thread = g.packet;
+    report_tuning(op, g, 3, node_format_of(g, op, 3, ARBORX_POINTS, false), t);
 }
 
 arborx_status arborx_set_allocator(arborx_alloc_fn alloc_fn, arborx_free_fn free_fn, void *ctx)
@@ -935,7 +944,7 @@ arborx_status arborx_get_tuning(arborx_tuning *t)
 {
     if (!t)
         return fail(ARBORX_E_INVALID, "tuning is NULL");
-    from_tuning(g_tuning[0], t);
+    from_tuning(0, g_tuning[0], t);
     return ARBORX_OK;
 }
 
@@ -945,7 +954,7 @@ arborx_status arborx_get_tuning_op(int32_t op, arborx_tuning *t)
         return fail(ARBORX_E_INVALID, "tuning is NULL");
     if (op < 0 || op >= OP_KINDS)
         return fail(ARBORX_E_INVALID, "unknown operation");
-    from_tuning(g_tuning[op], t);
+    from_tuning(op, g_tuning[op], t);
     return ARBORX_OK;
 }
 

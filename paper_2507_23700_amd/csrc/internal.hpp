@@ -53,10 +53,13 @@ struct Tuning {
                     // operation, dimension and format (up to 3D, where neighbouring paths overlap most: for
                     // the fused reductions 4 on float nodes, 1 on quantized ones; 2 for the CSR count; 1 in
                     // 6D)
-    bool by_dim = false;  // the library's defaults: block and stack also follow the dimension (launch_shape)
+    bool by_dim = false;  // not a caller's: node formats a structure was built without are passed over
+    bool saved = false;   // with by_dim: a choice of the autotuner's file, launched as recorded; else the library's
+                          // defaults, whose block, stack and format also follow the dimension and the launch
 };
-// The block and stack of `op` are the library's defaults, not a saved choice's.
-bool default_shape(int op);
+Tuning default_tuning(int op);
+// The tuning of `op` is the library's defaults, not a caller's or a saved choice.
+bool is_default(const Tuning &t);
 // Block size and short-stack depth a launch of `op` in dimension `dim` uses:
 // the tuning's, except that the library's defaults in 6D take the shapes
 // measured best on the 6D Gaussian mixture at 2*10^6 points over quantized
@@ -67,6 +70,9 @@ void launch_shape(int op, int dim, int &block, int &stack);
 enum Op { OP_SPATIAL = 0, OP_REDUCE = 1, OP_KNN = 2, OP_KINDS = 3 };
 const Tuning &tuning(int op = OP_SPATIAL);
 void set_tuning_op(int op, const Tuning &t);
+// What a tuning of `op` comes to in dimension `dim`, for reporting: the block and stack of launch_shape and the
+// node format `format`.
+void report_tuning(int op, const Tuning &t, int dim, int format, arborx_tuning *out);
 // Node format the thread schedule of `op` walks on a tree (or forest) of
 // dimension `dim` over values of `kind`: the tuning's; under the library's
 // defaults 1 over points and 0 for every other walk (box values, forests).
@@ -223,6 +229,7 @@ struct ForestDev {
 // As tree_format, for the walks over a forest.
 int forest_format(int op, const ForestDev &f);
 int forest_format(const Tuning &t, int op, arborx_forest forest);
+int forest_default_format(int op, arborx_forest forest);  // of the library's defaults over such values
 arborx_status build_forest(const float *values, const int64_t *seg_host, int T, int dim, int kind, ForestDev &f,
                            hipStream_t s);
 // Every allocation of a forest of n values in T trees (structure and build

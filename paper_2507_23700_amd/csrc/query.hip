@@ -1109,7 +1109,7 @@ Launch traversal_launch(int64_t m, size_t entry_bytes, int op, int dim, bool wav
 {
     Launch L;
     launch_shape(op, dim, L.block, L.cap);
-    if (default_shape(op) && !wave && (m + kWave - 1) / kWave < kFillBlocks) {
+    if (is_default(tuning(op)) && !wave && (m + kWave - 1) / kWave < kFillBlocks) {
         L.cap = kSmallStack;
         while (L.block > kSmallBlock && (m + L.block - 1) / L.block < kFillBlocks)
             L.block >>= 1;
