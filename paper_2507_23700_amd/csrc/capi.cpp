@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "device_util.hpp"
+#include "block_cache.hpp"
 #include "internal.hpp"
 #include "profile.hpp"
 
@@ -354,174 +355,6 @@ static void drain_pending(bool wait)
     }
 }
 
-// Blocks of the default allocator that are free, kept for later calls.  A
-// build and a query take and give back some thirty blocks, up to gigabytes;
-// left to hipMallocAsync and hipFreeAsync, whose memory went back to the
-// device and was mapped again, a build and CSR query at 10^7 points took
-// 84 ms for 7 ms of kernels, and 10^6 box overlaps 5.3 ms for 0.8 ms.
-//
-// A block is freed with an event on the stream that had its last use (one
-// event for all the blocks of a call).  It goes to a later allocation for the
-// stream it was taken for, which waits for that event on the device, or for any
-// stream once the event has completed; never to work that could overlap its
-// last use.  What is kept is bounded by a quarter of the device's memory, the
-// longest unused given back first, and all of it is given back when an
-// allocation fails or the caller installs an allocator.  While a stream is
-// being captured its allocations and releases pass the cache by.
-struct FreeGroup {
-    hipEvent_t done = nullptr;  // NULL: complete
-    int blocks = 0;             // free blocks that refer to the group
-};
-struct CachedBlock {
-    void *p = nullptr;
-    size_t bytes = 0;
-    int dev = 0;
-    hipStream_t owner = nullptr;  // the stream it was last allocated for
-    FreeGroup *group = nullptr;
-    uint64_t age = 0;
-};
-static std::mutex g_cache_mu;
-static std::unordered_map<void *, CachedBlock> g_live_blocks;
-static std::multimap<size_t, CachedBlock> g_free_blocks[64];
-static size_t g_free_bytes[64] = {};
-static size_t g_cache_limit[64] = {};
-static uint64_t g_cache_age = 0;
-static std::vector<hipEvent_t> g_event_pool;
-
-static hipStream_t release_stream();
-
-static bool is_capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
-}
-
-// Lets this thread query events while another thread captures a graph.
-struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
-
-static bool group_complete(FreeGroup *g)
-{
-    if (!g->done)
-        return true;
-    RelaxedCapture relaxed;
-    if (hipEventQuery(g->done) != hipSuccess) {
-        (void)hipGetLastError();  // "not ready" must not surface as a later call's error
-        return false;
-    }
-    g_event_pool.push_back(g->done);
-    g->done = nullptr;
-    return true;
-}
-
-static void group_leave(FreeGroup *g)
-{
-    if (--g->blocks == 0) {
-        if (g->done)  // an event may be recorded again while waits on its earlier record are queued
-            g_event_pool.push_back(g->done);
-        delete g;
-    }
-}
-
-// Give a cached block back to the device, after its last use.
-static void give_back(CachedBlock &b, bool wait)
-{
-    hipStream_t rs = release_stream();
-    if (b.group->done) {
-        if (wait || !rs)
-            (void)hipEventSynchronize(b.group->done);
-        else
-            (void)hipStreamWaitEvent(rs, b.group->done, 0);
-    }
-    (void)hipFreeAsync(b.p, rs);
-    group_leave(b.group);
-}
-
-// Give back the longest unused blocks of a device until at most `keep` bytes
-// stay (g_cache_mu held, dev the current device).
-static void trim_cache(int dev, size_t keep, bool wait)
-{
-    auto &blocks = g_free_blocks[dev];
-    while (g_free_bytes[dev] > keep && !blocks.empty()) {
-        auto oldest = blocks.begin();
-        for (auto it = blocks.begin(); it != blocks.end(); ++it)
-            if (it->second.age < oldest->second.age)
-                oldest = it;
-        g_free_bytes[dev] -= oldest->second.bytes;
-        give_back(oldest->second, wait);
-        blocks.erase(oldest);
-    }
-    if (wait) {
-        hipStream_t rs = release_stream();
-        (void)hipStreamSynchronize(rs);
-        hipMemPool_t pool;
-        if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess)
-            (void)hipMemPoolTrimTo(pool, 0);
-        (void)hipGetLastError();
-    }
-}
-
-// A free block of at least `bytes` (and not much more) for work on s, or NULL.
-static void *cache_take(int dev, size_t bytes, hipStream_t s)
-{
-    auto &blocks = g_free_blocks[dev];
-    const size_t most = bytes + bytes / 4 + 4096;
-    auto found = blocks.end();
-    for (int pass = 0; pass < 2 && found == blocks.end(); ++pass)
-        for (auto it = blocks.lower_bound(bytes); it != blocks.end() && it->first <= most; ++it) {
-            CachedBlock &b = it->second;
-            if (pass == 0 ? b.owner == s : group_complete(b.group)) {
-                found = it;
-                break;
-            }
-        }
-    if (found == blocks.end())
-        return nullptr;
-    CachedBlock b = found->second;
-    // on the stream that recorded it this costs nothing; it is never left out,
-    // because a stream's handle may be given to a new stream
-    if (b.group->done && hipStreamWaitEvent(s, b.group->done, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    blocks.erase(found);
-    g_free_bytes[dev] -= b.bytes;
-    group_leave(b.group);
-    b.group = nullptr;
-    b.owner = s;
-    g_live_blocks[b.p] = b;
-    return b.p;
-}
-
-static size_t cache_limit(int dev)
-{
-    if (!g_cache_limit[dev]) {
-        RelaxedCapture relaxed;
-        size_t avail = 0, total = 0;
-        if (hipMemGetInfo(&avail, &total) != hipSuccess) {
-            (void)hipGetLastError();
-            total = (size_t)4 << 30;
-        }
-        g_cache_limit[dev] = total / 4 + 1;
-    }
-    return g_cache_limit[dev];
-}
-
-static void flush_cache()
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess)
-        return;
-    std::lock_guard<std::mutex> lock(g_cache_mu);
-    for (int d = 0; d < 64; ++d)
-        if (!g_free_blocks[d].empty() && hipSetDevice(d) == hipSuccess)
-            trim_cache(d, 0, true);
-    (void)hipSetDevice(dev);
-}
-
 static std::mutex g_header_mu;
 static std::vector<QueryHeader *> g_headers;
 
@@ -580,12 +413,9 @@ arborx_status dalloc(void **p, size_t bytes, hipStream_t s)
     const size_t want = bytes ? (bytes + step - 1) / step * step : step;
     int dev = -1;
     const bool cached = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !is_capturing(s);
-    if (cached) {
-        std::lock_guard<std::mutex> lock(g_cache_mu);
-        if ((*p = cache_take(dev, want, s))) {
-            ++g_default_live;
-            return ARBORX_OK;
-        }
+    if (cached && (*p = cache_take(dev, want, s))) {
+        ++g_default_live;
+        return ARBORX_OK;
     }
     hipError_t e = hipMallocAsync(p, want, s);
     if (e != hipSuccess && cached) {  // give every free block back and try once more
@@ -598,15 +428,8 @@ arborx_status dalloc(void **p, size_t bytes, hipStream_t s)
         (void)hipGetLastError();
         return fail(ARBORX_E_NOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
     }
-    if (cached) {
-        std::lock_guard<std::mutex> lock(g_cache_mu);
-        CachedBlock b;
-        b.p = *p;
-        b.bytes = want;
-        b.dev = dev;
-        b.owner = s;
-        g_live_blocks[*p] = b;
-    }
+    if (cached)
+        cache_note(*p, want, dev, s);
     ++g_default_live;
     return ARBORX_OK;
 }
@@ -648,63 +471,13 @@ static bool user_free(void *p, hipStream_t s)
 // an event no call is made on s, which may be gone by then.
 static void release_blocks(void *const *ptrs, int n, hipStream_t s, hipEvent_t done)
 {
-    std::vector<CachedBlock> mine;
-    const bool capturing = n > 0 && !done && is_capturing(s);
-    for (int i = 0; i < n; ++i) {
-        void *p = ptrs[i];
-        if (!p || user_free(p, s))
-            continue;
-        --g_default_live;
-        CachedBlock b;
-        {
-            std::lock_guard<std::mutex> lock(g_cache_mu);
-            auto it = g_live_blocks.find(p);
-            if (it != g_live_blocks.end()) {
-                b = it->second;
-                g_live_blocks.erase(it);
-            }
+    std::vector<void *> mine;
+    for (int i = 0; i < n; ++i)
+        if (ptrs[i] && !user_free(ptrs[i], s)) {
+            --g_default_live;
+            mine.push_back(ptrs[i]);
         }
-        if (!b.p || capturing)
-            (void)hipFreeAsync(p, s);
-        else
-            mine.push_back(b);
-    }
-    std::lock_guard<std::mutex> lock(g_cache_mu);
-    if (mine.empty()) {
-        if (done)
-            g_event_pool.push_back(done);
-        return;
-    }
-    FreeGroup *g = new FreeGroup();
-    hipEvent_t e = done;
-    if (!e && !g_event_pool.empty()) {
-        e = g_event_pool.back();
-        g_event_pool.pop_back();
-    } else if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        e = nullptr;
-    }
-    if (e && (done || hipEventRecord(e, s) == hipSuccess)) {
-        g->done = e;
-    } else {
-        (void)hipGetLastError();
-        if (e)
-            g_event_pool.push_back(e);
-        (void)hipStreamSynchronize(s);
-    }
-    int cur = -1;
-    (void)hipGetDevice(&cur);
-    bool touched[64] = {};
-    for (CachedBlock &b : mine) {
-        b.group = g;
-        b.age = ++g_cache_age;
-        ++g->blocks;
-        g_free_bytes[b.dev] += b.bytes;
-        g_free_blocks[b.dev].emplace(b.bytes, b);
-        touched[b.dev] = true;
-    }
-    if (cur >= 0 && cur < 64 && touched[cur])
-        trim_cache(cur, cache_limit(cur), false);
+    cache_release(mine, s, done);
 }
 
 void dfree_many(void *const *ptrs, int n, hipStream_t s) { release_blocks(ptrs, n, s, nullptr); }
@@ -730,23 +503,6 @@ static arborx_status check_tree(arborx_tree t)
     if (!t)
         return fail(ARBORX_E_INVALID, "tree is NULL");
     return ARBORX_OK;
-}
-
-// Stream of the calling device on which destroyed structures release their
-// memory, after waiting for the build and every recorded use.
-static hipStream_t release_stream()
-{
-    static std::mutex mu;
-    static hipStream_t streams[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return nullptr;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!streams[dev] && hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking) != hipSuccess) {
-        (void)hipGetLastError();
-        streams[dev] = nullptr;
-    }
-    return streams[dev];
 }
 
 static void release_tree(arborx_tree t)
