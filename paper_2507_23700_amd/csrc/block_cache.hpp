@@ -38,23 +38,23 @@ hipStream_t release_stream()
 // 84 ms for 7 ms of kernels, and 10^6 box overlaps 5.3 ms for 0.8 ms.
 //
 // A block is freed with an event on the stream that had its last use (one
-// event for all the blocks of a call).  It goes to a later allocation for the
-// stream it was taken for, which waits for that event on the device, or for any
-// stream once the event has completed; never to work that could overlap its
-// last use.  What is kept is bounded by a quarter of the device's memory, the
+// event for all the blocks of a call).  It goes to a later allocation for that
+// stream, which waits for the event on the device, or for any stream once the
+// event has completed; never to work that could overlap its last use, and
+// nothing waits for another stream's work where memory is left.  What is kept is bounded by a quarter of the device's memory, the
 // longest unused given back first, and all of it is given back when an
 // allocation fails or the caller installs an allocator.  While a stream is
 // being captured its allocations and releases pass the cache by.
 struct FreeGroup {
     hipEvent_t done = nullptr;  // NULL: complete
     int dev = 0;                // the event's device
+    hipStream_t on = nullptr;   // the stream that recorded it
     int blocks = 0;             // free blocks that refer to the group
 };
 struct CachedBlock {
     void *p = nullptr;
     size_t bytes = 0;
     int dev = 0;
-    hipStream_t owner = nullptr;  // the stream it was last allocated for
     FreeGroup *group = nullptr;
     uint64_t age = 0;
 };
@@ -149,8 +149,8 @@ void *cache_take(int dev, size_t bytes, hipStream_t s)
     auto found = blocks.end();
     for (int pass = 0; pass < 2 && found == blocks.end(); ++pass)
         for (auto it = blocks.lower_bound(bytes); it != blocks.end() && it->first <= most; ++it) {
-            CachedBlock &b = it->second;
-            if (pass == 0 ? b.owner == s : group_complete(b.group)) {
+            FreeGroup *g = it->second.group;
+            if (pass == 0 ? g->on == s : group_complete(g)) {
                 found = it;
                 break;
             }
@@ -168,7 +168,6 @@ void *cache_take(int dev, size_t bytes, hipStream_t s)
     g_free_bytes[dev] -= b.bytes;
     group_leave(b.group);
     b.group = nullptr;
-    b.owner = s;
     g_live_blocks[b.p] = b;
     return b.p;
 }
@@ -199,15 +198,14 @@ void flush_cache()
     (void)hipSetDevice(dev);
 }
 
-// Remember a block of the device, allocated for s.
-void cache_note(void *p, size_t bytes, int dev, hipStream_t s)
+// Remember a block of the device.
+void cache_note(void *p, size_t bytes, int dev)
 {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     CachedBlock b;
     b.p = p;
     b.bytes = bytes;
     b.dev = dev;
-    b.owner = s;
     g_live_blocks[p] = b;
 }
 
@@ -240,6 +238,7 @@ void cache_release(const std::vector<void *> &ptrs, hipStream_t s, hipEvent_t do
         cur = 0;
     FreeGroup *g = new FreeGroup();
     g->dev = done ? mine[0].dev : cur;
+    g->on = s;
     hipEvent_t e = done;
     if (!e && !g_event_pool[cur].empty()) {
         e = g_event_pool[cur].back();

@@ -45,6 +45,12 @@ struct StreamUses {
             (void)hipStreamSynchronize(s);
         }
     }
+    // True if every recorded use was on s.
+    bool only(hipStream_t s)
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        return ev.empty() || (ev.size() == 1 && ev[0].first == s);
+    }
     // Make `to` wait for every recorded use so far.
     void wait(hipStream_t to)
     {
@@ -429,7 +435,7 @@ arborx_status dalloc(void **p, size_t bytes, hipStream_t s)
         return fail(ARBORX_E_NOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
     }
     if (cached)
-        cache_note(*p, want, dev, s);
+        cache_note(*p, want, dev);
     ++g_default_live;
     return ARBORX_OK;
 }
@@ -569,6 +575,11 @@ static arborx_status tree_order(arborx_tree t, const float *queries, int64_t m, 
     oc.m = m;
     oc.pred = (int)pred;
     oc.mode = mode;
+    if (oc.last && oc.last.use_count() == 1 && t->uses.only(s)) {  // used on this stream alone: its to take again
+        t->uses.wait(s);  // or on a destroyed one that had its handle
+        dfree(oc.last->perm, s);
+        oc.last->perm = nullptr;
+    }
     oc.last = keep;  // the replaced order goes when the last call that walks by it lets go
     *order = keep;
     return ARBORX_OK;

@@ -97,10 +97,10 @@ hipStream_t stream_on(int dev)
     t_dev = before;
     return s;
 }
-void *block(size_t bytes, int dev, hipStream_t s)
+void *block(size_t bytes, int dev)
 {
     void *p = std::malloc(1);
-    cache_note(p, bytes, dev, s);
+    cache_note(p, bytes, dev);
     return p;
 }
 
@@ -115,7 +115,7 @@ void events_by_device()
             t_dev = d;
             p[d] = cache_take(d, 4096, s[d]);
             if (!p[d])
-                p[d] = block(4096, d, s[d]);
+                p[d] = block(4096, d);
         }
         for (int d = 0; d < 2; ++d) {
             t_dev = d;
@@ -126,6 +126,26 @@ void events_by_device()
     CHECK(g_synced == 0);
     CHECK(g_freed.empty());
 }
+
+// A block whose last use is still to come on another stream makes no one wait
+// while there is a finished one, or other memory.
+void unfinished_elsewhere()
+{
+    hipStream_t a = stream_on(0), b = stream_on(0);
+    void *p = block(8192, 0);
+    cache_release({p}, b, nullptr);  // taken for a, read last by work on b that goes on
+    CHECK(cache_take(0, 8192, a) == nullptr);
+    CHECK(a->waits.empty());
+    void *q = block(8192, 0);
+    cache_release({q}, b, nullptr);
+    b->done = b->queued - 1;  // p's use has ended, q's has not
+    CHECK(cache_take(0, 8192, a) == p);
+    CHECK(cache_take(0, 8192, a) == nullptr);
+    CHECK(cache_take(0, 8192, b) == q);  // b's own work is in order
+    CHECK(a->waits.empty());
+    CHECK(b->waits.size() == 1);
+    CHECK(g_synced == 0 && g_freed.empty());
+}
 }  // namespace
 
 int main(int argc, char **argv)
@@ -133,6 +153,8 @@ int main(int argc, char **argv)
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "events_by_device")
         events_by_device();
+    else if (name == "unfinished_elsewhere")
+        unfinished_elsewhere();
     else
         return 2;
     return g_failed ? 1 : 0;
