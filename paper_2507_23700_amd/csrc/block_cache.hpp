@@ -172,6 +172,7 @@ void *cache_take(int dev, size_t bytes, hipStream_t s)
     return b.p;
 }
 
+// What may be kept on the current device.
 size_t cache_limit(int dev)
 {
     if (!g_cache_limit[dev]) {
@@ -264,8 +265,12 @@ void cache_release(const std::vector<void *> &ptrs, hipStream_t s, hipEvent_t do
         g_free_blocks[b.dev].emplace(b.bytes, b);
         touched[b.dev] = true;
     }
-    if (touched[cur])
-        trim_cache(cur, cache_limit(cur), false);
+    for (int d = 0; d < 64; ++d)  // blocks may be of another device than the current one
+        if (touched[d] && (d == cur || hipSetDevice(d) == hipSuccess)) {
+            trim_cache(d, cache_limit(d), false);
+            if (d != cur)
+                (void)hipSetDevice(cur);
+        }
 }
 
 }  // namespace

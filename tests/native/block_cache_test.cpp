@@ -146,6 +146,22 @@ void unfinished_elsewhere()
     CHECK(b->waits.size() == 1);
     CHECK(g_synced == 0 && g_freed.empty());
 }
+
+// Blocks of a device that is not the current one when they are freed keep that
+// device's bound, and go back on a stream of theirs.
+void other_device_is_trimmed()
+{
+    hipStream_t s = stream_on(0);
+    t_dev = 0;
+    const size_t bytes = (size_t)25 << 20;  // device 1 has 500 MiB: 125 may stay
+    for (int i = 0; i < 8; ++i)
+        cache_release({block(bytes, 1)}, s, nullptr);
+    CHECK(t_dev == 0);
+    CHECK(g_free_bytes[1] <= (size_t)126 << 20 && g_free_bytes[1] >= (size_t)100 << 20);
+    CHECK(g_freed.size() >= 3);
+    for (const Freed &f : g_freed)
+        CHECK(f.dev == 1);
+}
 }  // namespace
 
 int main(int argc, char **argv)
@@ -155,6 +171,8 @@ int main(int argc, char **argv)
         events_by_device();
     else if (name == "unfinished_elsewhere")
         unfinished_elsewhere();
+    else if (name == "other_device_is_trimmed")
+        other_device_is_trimmed();
     else
         return 2;
     return g_failed ? 1 : 0;

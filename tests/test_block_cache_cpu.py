@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["events_by_device", "unfinished_elsewhere"])
+@pytest.mark.parametrize("case", ["events_by_device", "unfinished_elsewhere", "other_device_is_trimmed"])
 def test_block_cache(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
