@@ -108,8 +108,10 @@ const char *arborx_last_error(void);
  * forest storage, per-call temporaries, CSR plans) from alloc_fn and returns it
  * to free_fn, for example to share a framework's caching allocator; by
  * default it uses stream-ordered allocations from the device's pool and keeps
- * freed blocks for its later calls (at most a quarter of the device's memory;
- * given back when an allocation fails or a hook is installed).
+ * freed blocks for its later calls (at most a quarter of the device's memory).
+ * They are given back when an allocation fails and by every call of this
+ * function, also by one that ends in ARBORX_E_INVALID because structures live:
+ * a program that runs out of memory beside the library calls it with NULLs.
  *   alloc_fn(bytes, stream, ctx) returns device memory for work queued on
  *     `stream`, or NULL (the call then fails with ARBORX_E_NOMEM).
  *   free_fn(ptr, stream, ctx) hands a block back.  `stream` is the stream the

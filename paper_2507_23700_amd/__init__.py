@@ -70,7 +70,9 @@ _allocator = None  # the installed ctypes callbacks, kept alive while the librar
 def arborx_set_allocator(alloc=None, free=None) -> None:
     """Take the library's device memory from ``alloc(nbytes, stream) -> int`` and return it to
     ``free(ptr, stream)`` (``stream`` is the raw stream handle as an int, 0 for the default
-    stream); with no arguments the library's own stream-ordered pool is used again."""
+    stream); with no arguments the library's own stream-ordered pool is used again.  Every
+    call gives the free blocks that the library keeps back to the device, also one that is refused
+    because trees, forests or plans live."""
     global _allocator
     if (alloc is None) != (free is None):
         raise ValueError("give both alloc and free, or neither")

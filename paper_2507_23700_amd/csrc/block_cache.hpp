@@ -43,7 +43,7 @@ hipStream_t release_stream()
 // event has completed; never to work that could overlap its last use, and
 // nothing waits for another stream's work where memory is left.  What is kept is bounded by a quarter of the device's memory, the
 // longest unused given back first, and all of it is given back when an
-// allocation fails or the caller installs an allocator.  While a stream is
+// allocation fails or the caller installs an allocator or names the default.  While a stream is
 // being captured its allocations and releases pass the cache by.
 struct FreeGroup {
     hipEvent_t done = nullptr;  // NULL: complete

@@ -665,8 +665,7 @@ arborx_status arborx_set_allocator(arborx_alloc_fn alloc_fn, arborx_free_fn free
     if (!alloc_fn != !free_fn)
         return fail(ARBORX_E_INVALID, "alloc_fn and free_fn must both be given or both be NULL");
     drain_pending(true);
-    if (alloc_fn)
-        flush_cache();
+    flush_cache();
     std::lock_guard<std::mutex> lock(g_alloc_mu);
     if (!g_user_blocks.empty() || !g_pending.empty() || g_default_live.load() != 0)
         return fail(ARBORX_E_INVALID, "the library still holds device memory (a live tree, forest or plan)");
