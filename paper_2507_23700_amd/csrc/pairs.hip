@@ -431,7 +431,7 @@ PairLaunch pair_launch(const TreeDev &t)
     L.nq = tu.schedule == 2 ? 0 : (tu.packet ? tu.packet : (dim <= 3 && !qf ? 2 : 1));
     L.q = L.nq == 1 && qf;
     launch_shape(OP_REDUCE, dim, L.block, L.cap);
-    while (L.cap > 1 && (size_t)(L.cap + (L.q ? kPairQueue : 0)) * L.block * sizeof(int) > 65536)
+    while (L.cap > 1 && (size_t)L.cap * L.block * sizeof(int) > 65536)
         L.cap >>= 1;
     L.lds = L.nq ? (size_t)(L.cap > 2 ? L.cap : 2) * L.block * sizeof(int) : 0;  // a TopStack has at least two slots
     const int64_t per = L.nq ? L.nq : 1;

@@ -1174,12 +1174,8 @@ arborx_status count_impl(const TreeDev &t, Pred pred, const float *q, int64_t m,
         return ARBORX_OK;
     }
     Launch L = traversal_launch(m, sizeof(int), OP_SPATIAL, D, sched == 1);
-    if (sched == 3) {  // the rings of StashRing behind the stacks
-        const int ring = kRing * (out ? 2 : 1);
-        while (L.cap > 2 && (size_t)(L.cap + ring) * L.block * sizeof(int) > 65536)
-            L.cap >>= 1;
-        L.lds = (size_t)((L.cap > 2 ? L.cap : 2) + ring) * L.block * sizeof(int);
-    }
+    if (sched == 3)  // the rings of StashRing behind the stacks: at most 80 of a workgroup's 160 KiB
+        L.lds += (size_t)kRing * (out ? 2 : 1) * L.block * sizeof(int);
     const Node<D> *nodes = static_cast<const Node<D> *>(t.nodes);
     const QNode<D> *qnodes = static_cast<const QNode<D> *>(t.qnodes);
     const Node4<D> *wnodes = static_cast<const Node4<D> *>(t.wnodes);
