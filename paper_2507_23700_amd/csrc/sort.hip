@@ -37,10 +37,16 @@ constexpr int kRadix = 1 << kRadixBits;
 static_assert(kSortBlock == kRadix, "one thread per digit in the per-tile steps");
 
 // Keys per thread of a radix tile.  A tile of 16 per thread writes digit runs
-// of 16 keys on average, but 10^6 keys then make 245 tiles for 256 compute
-// units, each alone with its latency; fewer per thread fill the chip there.
-constexpr int64_t kItems4Most = (int64_t)1 << 19, kItems8Most = 2000000;
-inline int sort_items(int64_t n) { return n <= kItems4Most ? 4 : (n <= kItems8Most ? 8 : 16); }
+// of 16 keys on average, but few tiles leave compute units idle (256 of them), or
+// each alone with its latency.  63 and 24 bits with 4, 8 and 16 per thread, us:
+// 600000 keys 146 152 188 and 67 68 81; 786432 157 154 192 and 72 69 83; 2^20 189
+// 166 188 and 83 74 85; 1.9*10^6 281 212 218 and 118 91 95; 2*10^6 290 221 220 and
+// 122 94 96; 2.05*10^6 316 236 226 and 131 99 97; 2^22 525 394 356 and 203 155 129.
+// So 8 from 1.5 tiles of 8 a compute unit on, 16 from 1.94 tiles of 16; the 992
+// tiles of 8 below that fit the allocation-free nearest search's workspace of 1
+// MiB, which holds 1015.
+constexpr int64_t kItems8Least = 3 << 18, kItems16Least = 31 << 16;
+inline int sort_items(int64_t n) { return n < kItems8Least ? 4 : (n < kItems16Least ? 8 : 16); }
 inline int64_t sort_tiles(int64_t n, int items) { return (n + kSortBlock * items - 1) / (kSortBlock * items); }
 
 template <typename K, int ITEMS>
@@ -353,10 +359,10 @@ void radix_pass(const K *kin, const uint32_t *vin, K *kout, uint32_t *vout, int6
 size_t radix_workspace_bytes(int64_t n)
 {
     // enough for any smaller n too: a workspace is reserved for the largest call
-    int64_t tiles = sort_tiles(n < kItems4Most ? n : kItems4Most, 4);
-    if (n > kItems4Most)
-        tiles = std::max(tiles, sort_tiles(n < kItems8Most ? n : kItems8Most, 8));
-    if (n > kItems8Most)
+    int64_t tiles = sort_tiles(std::min(n, kItems8Least), 4);
+    if (n >= kItems8Least)
+        tiles = std::max(tiles, sort_tiles(std::min(n, kItems16Least), 8));
+    if (n >= kItems16Least)
         tiles = std::max(tiles, sort_tiles(n, 16));
     return (size_t)(tiles * kRadix + 8 * kRadix) * sizeof(uint32_t) + 256;
 }
