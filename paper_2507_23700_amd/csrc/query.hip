@@ -884,6 +884,17 @@ __global__ void k_spatial_reduce_packet(const Node<D> *__restrict__ nodes, const
 // shapes are left to the compiler.  The 3D k = 16 walk over codes is held from
 // 78 registers to 72 (7 waves; the four spilled are of queries outside the
 // frame): 7.81 instead of 7.97 ms for build and search at 10^7 points.
+// A kernel that may be launched with 1024 threads gets 128 registers at most; the
+// 64 keys of a long list take them all, and the walk spilled up to a thousand
+// words.  With 256 threads, the largest workgroup there is, it keeps them: k = 64
+// of 10^6 cube points 22.3 -> 4.1 ms, of 2*10^5 6D points 12.1 -> 3.3 (45 and 17.6
+// with the walk over uneven frames beside the others).
+template <int K>
+constexpr int knn_block()
+{
+    return K > 32 ? 256 : 1024;
+}
+
 template <int D, int K, bool WAVE, int FMT>
 constexpr int knn_waves()
 {
@@ -891,7 +902,8 @@ constexpr int knn_waves()
 }
 
 template <int D, int K, bool WAVE, int FMT>
-__global__ __attribute__((amdgpu_waves_per_eu(knn_waves<D, K, WAVE, FMT>()))) void k_knn(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
+__global__ __attribute__((amdgpu_waves_per_eu(knn_waves<D, K, WAVE, FMT>()),
+                          amdgpu_flat_work_group_size(1, knn_block<K>()))) void k_knn(const Node<D> *__restrict__ nodes, const QNode<D> *__restrict__ qnodes,
                       const Node4<D> *__restrict__ wnodes, const uint64_t *__restrict__ codes, int n_nodes,
                       const float *__restrict__ leaves, int kind,
                       const TreeHeader *__restrict__ hdr, const float *__restrict__ queries, int64_t m, int k_out,

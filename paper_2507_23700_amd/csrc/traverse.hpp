@@ -989,19 +989,20 @@ __device__ __forceinline__ void sort_network(T (&v)[C])
             }
 }
 
-struct KnnEntry {
+struct alignas(8) KnnEntry {  // read and written as one word, also as a KnnCode
     int32_t ref;
     float d2;
 };
 // A deferred subtree of a kNN walk over codes: its squared gap above its
 // reference, one word of a TopStack.
 typedef uint64_t KnnCode;
-static_assert(sizeof(KnnCode) == sizeof(KnnEntry), "the two share a stack area");
+static_assert(sizeof(KnnCode) == sizeof(KnnEntry) && alignof(KnnCode) == alignof(KnnEntry),
+              "the two share a stack area");
 __device__ __forceinline__ KnnCode knn_code(int32_t ref, uint32_t gap2) { return ((uint64_t)gap2 << 32) | (uint32_t)ref; }
 
 // Minimum and maximum of two top-k keys held as doubles.  The bit pattern of
-// a float32 distance >= 0 (up to +inf, and NaN) in the high word makes a
-// positive finite double (its exponent field is at most 0x7ff - 1), so the
+// a float32 distance >= 0, up to +inf and the NaN 0x7fc00000, in the high word
+// makes a positive finite double (its exponent field is at most 0x7fc), so the
 // double order is the order of the 64-bit words, and one instruction each
 // replaces a 64-bit compare and two selects.  A denormal (distance 0) keeps
 // its bits: double denormals are always on.  Written as instructions because
@@ -1577,7 +1578,8 @@ __device__ __forceinline__ void knn_walk_codes(const QNode<D> *__restrict__ node
         KnnCode deferred = st.top();
         const int c0 = nd.child[0], c1 = nd.child[1];
         const uint32_t s0 = gap.sum(nd.w[0]), s1 = gap.sum(nd.w[1]);
-        // leaf children as keys, the other slots above every key
+        // leaf children as keys, the other slots above every key; no slot is empty (its words are a NaN with an
+        // exponent of 0x7ff, for which the key order fails): a frame with an extent holds two values at least
         const double none = TopK<K>::pack(__uint_as_float(0x7fc00000u), INT32_MAX);
         const double v0 = c0 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[0]), ~c0) : none;
         const double v1 = c1 < 0 ? TopK<K>::pack(point_d2<D>(q, nd.w[1]), ~c1) : none;
