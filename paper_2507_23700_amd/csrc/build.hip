@@ -362,8 +362,9 @@ __global__ __launch_bounds__(kBuildBlock) void hierarchy_kernel(const uint64_t *
 // climb that reaches split cs-1 or ce-1 (the chunk's borders) stops and is
 // recorded as one of at most two escapes of the chunk.
 // Phase 2: one thread per escape continues the climb over the splits whose
-// subtrees span chunks, handing off through global memory; one workgroup takes
-// the escapes of 512 neighbouring chunks, and another what leaves those.
+// subtrees span chunks; a workgroup takes the escapes of kGroupChunks
+// neighbouring chunks, whose climbs meet in LDS, and the next level takes what
+// leaves the groups, until one group is left.
 // ---------------------------------------------------------------------------
 
 template <int D>

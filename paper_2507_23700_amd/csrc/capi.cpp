@@ -628,7 +628,7 @@ static arborx_status to_tuning(const arborx_tuning *t, const Tuning &base, Tunin
         n.block = t->block;
     }
     if (t->order < 0 || t->order > 2)
-        return fail(ARBORX_E_INVALID, "order must be 0 (none), 1 (24-bit Morton) or 2 (16-bit Morton)");
+        return fail(ARBORX_E_INVALID, "order must be 0 (none), 1 (24-bit grid) or 2 (16-bit grid)");
     n.order = t->order;
     if (t->stack) {
         if (t->stack < 1 || t->stack > 64 || (t->stack & (t->stack - 1)))

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kForestBlock) void k_forest_knn(
                                  reinterpret_cast<KnnCode *>(spill), knn_code(-1, 0u));
             knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, h, q, best, ts, seed, sk);
         } else if (FMT == 1 && kind == ARBORX_BOXES)
-            knn_search_q<D, K>(qnodes, n_nodes, leaves, kind, h, q, best, st, seed, sk);
+            knn_search_q<D, K>(qnodes, n_nodes, leaves, h, q, best, st, seed, sk);
         else if (FMT == 2)
             knn_search4<D, K>(nodes, wnodes, n_nodes, leaves, kind, h, q, best, st, seed, sk);
         else

@@ -61,10 +61,10 @@ Tuning default_tuning(int op);
 // The tuning of `op` is the library's defaults, not a caller's or a saved choice.
 bool is_default(const Tuning &t);
 // Block size and short-stack depth a launch of `op` in dimension `dim` uses:
-// the tuning's, except that the library's defaults in 6D take the shapes
-// measured best on the 6D Gaussian mixture at 2*10^6 points over quantized
-// nodes (kNN: 64-thread blocks, 16-entry ring, 7.4 -> 6.7 ms; CSR count:
-// 64-thread blocks, 10.8 -> 10.2 ms; reductions keep the 3D shape).
+// the tuning's, except that the library's defaults take the shapes measured
+// best: kNN up to 3D workgroups of 256; in 6D, on the Gaussian mixture at 2*10^6
+// points over quantized nodes, kNN 64 threads and 16 entries (7.4 -> 6.7 ms) and
+// the CSR count 64 threads (10.8 -> 10.2 ms).
 void launch_shape(int op, int dim, int &block, int &stack);
 // Tuning is kept per operation kind so the autotuner can pick each separately.
 enum Op { OP_SPATIAL = 0, OP_REDUCE = 1, OP_KNN = 2, OP_KINDS = 3 };
@@ -75,7 +75,8 @@ void set_tuning_op(int op, const Tuning &t);
 void report_tuning(int op, const Tuning &t, int dim, int format, arborx_tuning *out);
 // Node format the thread schedule of `op` walks on a tree (or forest) of
 // dimension `dim` over values of `kind`: the tuning's; under the library's
-// defaults 1 over points and 0 for every other walk (box values, forests).
+// defaults 1 over points and 0 over boxes.  A structure built without format 1
+// is walked on format 0 then (tree_format, forest_format).
 int node_format(int op, int dim, int kind, bool forest);
 int node_format_of(const Tuning &t, int op, int dim, int kind, bool forest);
 // Quantized (1) and four-wide (2) nodes are built only while some operation

@@ -935,7 +935,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(knn_waves<D, K, WAVE, FMT>()),
             knn_search_codes<D, K>(qnodes, n_nodes, leaves, kind, *hdr, q, best, ts, seed,
                                    SeedKeys{codes, 0, 63 / D});
         } else if (FMT == 1 && kind == ARBORX_BOXES)
-            knn_search_q<D, K>(qnodes, n_nodes, leaves, kind, *hdr, q, best, st, seed, SeedKeys{codes, 0, 63 / D});
+            knn_search_q<D, K>(qnodes, n_nodes, leaves, *hdr, q, best, st, seed, SeedKeys{codes, 0, 63 / D});
         else if (FMT == 2)
             knn_search4<D, K>(nodes, wnodes, n_nodes, leaves, kind, *hdr, q, best, st, seed, SeedKeys{codes, 0, 63 / D});
         else

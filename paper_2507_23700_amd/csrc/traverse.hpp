@@ -709,15 +709,14 @@ __device__ __forceinline__ void traverse_spatial_q(const QNode<D> *__restrict__ 
     }
 }
 
-// Packet walk over quantized nodes: as traverse_spatial_packet, one decode
-// of the node's child boxes serving all NQ queries; leaves as in
-// traverse_spatial_q.
+// Packet walk over the quantized nodes of a tree of boxes: as
+// traverse_spatial_packet, one decode of the node's child boxes serving all NQ
+// queries; leaves whose decoded box passes are decided on their records.
 template <int D, int NQ, class P, class F>
 __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__restrict__ nodes, const TreeHeader &h,
-                                                          int n_nodes, const float *__restrict__ leaves, int kind,
+                                                          int n_nodes, const float *__restrict__ leaves,
                                                           const P (&pred)[NQ], ShortStack<int> &st, F &f)
 {
-    const bool points = kind != ARBORX_BOXES;
     float flo[D], fsc[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -731,7 +730,7 @@ __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__rest
         QNode<D> nd;
         load_qnode(nodes, cur, nd);
         float lo[2][D], hi[2][D];
-        qboxes<D>(nd, points, flo, fsc, lo, hi);
+        qboxes<D>(nd, false, flo, fsc, lo, hi);
         const int c0 = nd.child[0], c1 = nd.child[1];
         bool g0 = false, g1 = false;
 #pragma unroll
@@ -740,18 +739,10 @@ __device__ __forceinline__ void traverse_spatial_packet_q(const QNode<D> *__rest
             const bool h0 = pred[j].hit(lo[0], hi[0], d0);
             const bool h1 = pred[j].hit(lo[1], hi[1], d1);
             auto fj = [&](int idx, float d) { f(j, idx, d); };
-            if (h0 && c0 < 0 && c0 != kEmptyRef) {
-                if (points)
-                    f(j, ~c0, d0);
-                else
-                    leaf_exact<D>(leaves, kind, ~c0, pred[j], fj);
-            }
-            if (h1 && c1 < 0 && c1 != kEmptyRef) {
-                if (points)
-                    f(j, ~c1, d1);
-                else
-                    leaf_exact<D>(leaves, kind, ~c1, pred[j], fj);
-            }
+            if (h0 && c0 < 0 && c0 != kEmptyRef)
+                leaf_exact<D>(leaves, ARBORX_BOXES, ~c0, pred[j], fj);
+            if (h1 && c1 < 0 && c1 != kEmptyRef)
+                leaf_exact<D>(leaves, ARBORX_BOXES, ~c1, pred[j], fj);
             g0 = g0 | h0;
             g1 = g1 | h1;
         }
@@ -1646,21 +1637,19 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
                          (float)fmax(a + 0x1p-100 - past * (1.0 - 0x1p-22), -3.0e38), gap);
 }
 
-// kNN over quantized nodes: as knn_search (seeded, software-pipelined),
-// pruning with the decoded (larger) internal boxes.  A point tree's leaves are
-// offered with their exact distances from the node; a box tree's leaves that
+// kNN over the quantized nodes of a tree of boxes: as knn_search (seeded,
+// software-pipelined), pruning with the decoded (larger) boxes; leaves that
 // pass the bound are offered from their records.
 template <int D, int K>
 __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes, int n_nodes,
-                                             const float *__restrict__ leaves, int kind, const TreeHeader &hdr,
-                                             const float *q, TopK<K> &best, ShortStack<KnnEntry> &st,
-                                             int seed, const SeedKeys &keys)
+                                             const float *__restrict__ leaves, const TreeHeader &hdr, const float *q,
+                                             TopK<K> &best, ShortStack<KnnEntry> &st, int seed, const SeedKeys &keys)
 {
     const int n = hdr.n;
     best.reset(INFINITY);
     if (n <= 0)
         return;
-    const bool points = kind != ARBORX_BOXES;
+    constexpr int kind = ARBORX_BOXES;
     float flo[D], fsc[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -1675,7 +1664,7 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
             QNode<D> nd;
             load_qnode(nodes, cur, nd);
             float lo[2][D], hi[2][D];
-            qboxes<D>(nd, points, flo, fsc, lo, hi);
+            qboxes<D>(nd, false, flo, fsc, lo, hi);
             const float d0 = box_d2<D>(q, lo[0], hi[0]);
             const float d1 = box_d2<D>(q, lo[1], hi[1]);
             const int go = (d1 < d0 && nd.child[1] != kEmptyRef) ? 1 : 0;
@@ -1696,7 +1685,7 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
         if ((unsigned)cur >= (unsigned)n_nodes)
             break;
         float lo[2][D], hi[2][D];
-        qboxes<D>(nd, points, flo, fsc, lo, hi);
+        qboxes<D>(nd, false, flo, fsc, lo, hi);
         const float d0 = box_d2<D>(q, lo[0], hi[0]);
         const float d1 = box_d2<D>(q, lo[1], hi[1]);
         const int c0 = nd.child[0], c1 = nd.child[1];
@@ -1723,18 +1712,11 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
         }
         if ((unsigned)next < (unsigned)n_nodes)
             load_qnode(nodes, next, nd);  // in flight during the insertions below
-        if (points) {
-            if (c0 < 0 && c0 != kEmptyRef)
-                best.offer(d0, ~c0);
-            if (c1 < 0 && c1 != kEmptyRef)
-                best.offer(d1, ~c1);
-        } else {
-            const int lf = leaf_floats(D, kind);
-            if (c0 < 0 && c0 != kEmptyRef && !(d0 > best.bound()))
-                best.offer(leaf_d2<D>(leaves, kind, ~c0, q), __float_as_int(leaves[(int64_t)(~c0) * lf + 2 * D]));
-            if (c1 < 0 && c1 != kEmptyRef && !(d1 > best.bound()))
-                best.offer(leaf_d2<D>(leaves, kind, ~c1, q), __float_as_int(leaves[(int64_t)(~c1) * lf + 2 * D]));
-        }
+        const int lf = leaf_floats(D, kind);
+        if (c0 < 0 && c0 != kEmptyRef && !(d0 > best.bound()))
+            best.offer(leaf_d2<D>(leaves, kind, ~c0, q), __float_as_int(leaves[(int64_t)(~c0) * lf + 2 * D]));
+        if (c1 < 0 && c1 != kEmptyRef && !(d1 > best.bound()))
+            best.offer(leaf_d2<D>(leaves, kind, ~c1, q), __float_as_int(leaves[(int64_t)(~c1) * lf + 2 * D]));
         cur = next;
     }
 }
@@ -1743,13 +1725,13 @@ __device__ __forceinline__ void knn_search_q(const QNode<D> *__restrict__ nodes,
 __device__ __forceinline__ int node_count(const TreeHeader *hdr) { return hdr->n > 1 ? hdr->n - 1 : 1; }
 
 // Whether searches over points walk the codes of the tree's frame: no crowd of
-// points is there that the codes cannot tell apart (store_qnode).  A ball much wider than a code meets few more boxes in
-// codes than in floats: 10^6 uniform 3D points 4 codes apart, counts over codes
-// and over float nodes 537 and 506 us at a radius of 5 codes, 938 and 955 at 8,
-// 3622 and 4243 at 16; 2.2 codes apart 5626 and 5176 at 8, 26431 and 28397 at 16;
-// 3*10^5 2D points 1.1 codes apart 79 and 70 at 2, 122 and 126 at 4.
-// The nearest searches turn their bound into codes in float32, so 1/step^2 has
-// to lie in its range.
+// points is there that the codes cannot tell apart (store_qnode).  A ball much
+// wider than a code meets few more boxes in codes than in floats: 10^6 uniform
+// 3D points 4 codes apart, counts over codes and over float nodes 537 and 506 us
+// at a radius of 5 codes, 938 and 955 at 8, 3622 and 4243 at 16; 2.2 codes apart
+// 5626 and 5176 at 8, 26431 and 28397 at 16; 3*10^5 2D points 1.1 codes apart 79
+// and 70 at 2, 122 and 126 at 4.  The nearest searches turn their bound into
+// codes in float32, so 1/step^2 has to lie in its range.
 template <int D> constexpr double kWideBall = D <= 2 ? 3.0 : 12.0;  // codes
 constexpr double kLeastStep = 1e-19;
 __device__ __forceinline__ bool codes_serve(const TreeHeader &h)
@@ -1818,7 +1800,7 @@ __device__ __forceinline__ void walk_quantized_packet(const Node<D> *__restrict_
     if (kind != ARBORX_BOXES)
         traverse_spatial_packet<D, NQ>(nodes, h.root, n_nodes, pred, st, f);
     else
-        traverse_spatial_packet_q<D, NQ>(qnodes, h, n_nodes, leaves, kind, pred, st, f);
+        traverse_spatial_packet_q<D, NQ>(qnodes, h, n_nodes, leaves, pred, st, f);
 }
 
 }  // namespace
