@@ -31,20 +31,15 @@ namespace {
 
 constexpr int kBuildBlock = 256;
 
-// Step of the 16-bit frame of [lo, hi]: a hair above (hi - lo) / 65535 so that
-// code 65535 decodes at or beyond hi.
-// Step of the 16-bit frame [lo, hi]: the smallest float found upward from
-// about (hi - lo) / kQMax whose top code decodes to at least hi.  The two
-// products are taken before the difference so that an extent beyond the float
-// range stays finite; the check makes the guarantee independent of rounding
-// and of underflow for tiny extents.
+// Step of the 16-bit frame [lo, hi]: a hair above (hi - lo) / kQMax, so that the
+// frame's end lo + kQMax * step is not below hi.
 __device__ __forceinline__ float quant_scale(float lo, float hi)
 {
     if (!(hi > lo))
         return 0.0f;
-    constexpr float k = 1.0f / (float)kQMax;
-    float s = (hi * k - lo * k) * (1.0f + 0x1p-18f);
-    while (qdecode((uint32_t)kQMax, lo, s) < hi)
+    const double extent = (double)hi - (double)lo;
+    float s = (float)(extent * ((1.0 + 0x1p-18) / kQMax));
+    while ((double)s * kQMax < extent * (1.0 + 0x1p-40))  // rounding of a tiny step
         s = nextafterf(s, INFINITY);
     return s;
 }
@@ -75,24 +70,24 @@ __device__ void quant_frame(const float *lo, const float *hi, TreeHeader &h)
     }
 }
 
-// One dimension of a frame: codes rounded outward, so that the decoded box
-// contains the true one.  Decoding is off by half an ulp of a coordinate at
-// most; `slop` is that in codes, and a hair for the arithmetic here.
+// One dimension of a frame: codes rounded outward, with a hair for the
+// arithmetic here.  Where lo + code * step is at most x, so is its rounding to a
+// float, x being one: the decoded box contains the true one as well, and no more
+// is needed where a code is far below the spacing of floats.
 struct CodeAxis {
-    double lo, inv, slop;
-    __device__ __forceinline__ void set(float l, float h, double i)
+    double lo, inv;
+    __device__ __forceinline__ void set(float l, double i)
     {
         lo = l;
         inv = i;
-        slop = (fmax(fabs((double)l), fabs((double)h)) * 0x1.01p-24 + 0x1p-149) * inv + 0x1p-10;
     }
     __device__ __forceinline__ uint32_t down(float x) const
     {
-        return (uint32_t)fmin(fmax(((double)x - lo) * inv - slop, 0.0), (double)kQMax);
+        return (uint32_t)fmin(fmax(((double)x - lo) * inv - 0x1p-10, 0.0), (double)kQMax);
     }
     __device__ __forceinline__ uint32_t up(float x) const
     {
-        return (double)x > lo ? (uint32_t)fmin(ceil(((double)x - lo) * inv + slop), (double)kQMax) : 0u;
+        return (double)x > lo ? (uint32_t)fmin(ceil(((double)x - lo) * inv + 0x1p-10), (double)kQMax) : 0u;
     }
 };
 
@@ -103,7 +98,7 @@ struct CodeFrame {
     {
 #pragma unroll
         for (int d = 0; d < D; ++d)
-            axis[d].set(h.lo[d], h.hi[d], h.qinvs[d]);
+            axis[d].set(h.lo[d], h.qinvs[d]);
     }
 };
 

@@ -207,15 +207,14 @@ struct CodeExcess {
 
 // Coordinate c of a query in the codes of one dimension: (smallest code at or
 // above it) | (65535 - largest code at or below it) << 16, both moved outward
-// by the error of decoding, so that for a box [lo, hi] with word w the halves
-// of w - code, saturated at zero, are at most the box's gaps (lo - c)/step and
-// (c - hi)/step.  e: how far past the frame it is, rounded down; such a query
-// is clamped to the border.  inv = 1/step; lo, hi: the frame.
-__device__ __forceinline__ uint32_t code_query(float c, float lo, float hi, double inv, double &e)
+// by a hair for the arithmetic here, so that for a box [lo, hi] with word w the
+// halves of w - code, saturated at zero, are at most the box's gaps (lo - c)/step
+// and (c - hi)/step (the box's codes are outside its true faces, see CodeAxis).
+// e: how far past the frame it is, rounded down; such a query is clamped to the
+// border.  inv = 1/step; lo: where the frame starts.
+__device__ __forceinline__ uint32_t code_query(float c, float lo, double inv, double &e)
 {
-    // decode(code) is off by half an ulp of a coordinate at most; the last term covers the arithmetic here
-    const double m = fmax(fabs((double)lo), fabs((double)hi));
-    const double slop = (m * 0x1p-23 + 0x1p-148) * inv + 0x1p-8;
+    constexpr double slop = 0x1p-8;
     const double u = ((double)c - (double)lo) * inv;
     const double up = ceil(u + slop), dn = floor(u - slop);
     const uint32_t qhi = up >= (double)kQMax ? (uint32_t)kQMax : (up > 0.0 ? (uint32_t)up : 0u);

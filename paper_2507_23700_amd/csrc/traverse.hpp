@@ -840,7 +840,7 @@ __device__ __forceinline__ void code_ball(const float (&c)[D], float r2, const T
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         double e;
-        ball.q[d] = code_query(c[d], h.lo[d], h.hi[d], metric.inv(h, d), e);
+        ball.q[d] = code_query(c[d], h.lo[d], metric.inv(h, d), e);
         e *= metric.weight(d) * (EVEN ? 1.0 : 1.0 - 0x1p-22);
         past += e * e;
     }
@@ -1612,7 +1612,7 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
     if (hdr.even) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], hdr.qinv, e[d]);
+            qc[d] = code_query(q[d], hdr.lo[d], hdr.qinv, e[d]);
             past += e[d] * e[d];
         }
         if (!__any(past > 1.0)) {
@@ -1628,7 +1628,7 @@ __device__ __forceinline__ void knn_search_codes(const QNode<D> *__restrict__ no
     KnnGapUneven<D> gap{qc, CodeMetric<D, false>(hdr)};
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        qc[d] = code_query(q[d], hdr.lo[d], hdr.hi[d], gap.metric.inv(hdr, d), e[d]);
+        qc[d] = code_query(q[d], hdr.lo[d], gap.metric.inv(hdr, d), e[d]);
         e[d] *= gap.metric.weight(d) * (1.0 - 0x1p-22);
         gap.e2[d] = (float)(2.0 * e[d] * (1.0 - 0x1p-23));
         past += e[d] * e[d];
