@@ -567,7 +567,8 @@ def main():
     del q_alt, qs
     # walk statistics (the debug entry point, outside the step): node fetches per query of the
     # one-query-per-thread radius walk and of the seeded kNN walk, and the node bytes those fetches
-    # touch in float nodes (16*dim + 16 B) and in quantized nodes (8*dim + 8 B, 16-byte aligned)
+    # touch in float nodes (16*dim + 16 B) and in quantized nodes (8*dim + 8 B, 16-byte aligned); the
+    # counted walk is over float nodes, so the quantized figures are estimates (boxes rounded outward)
     vr = ax.arborx_debug_node_visits(tree, q, radius=radius).cpu().numpy().astype(np.float64)
     vk = ax.arborx_debug_node_visits(tree, q, k=k).cpu().numpy().astype(np.float64)
     fb, qb = 16 * dim + 16, (8 * dim + 8 + 15) // 16 * 16
@@ -592,8 +593,9 @@ def main():
                 "valu_busy": profiled(dom, cfg["workload"], "valu_busy"),
                 "algorithmic_bytes_per_launch": alg, "avg_launch_ms": avg_ms,
                 "copy_gbs": copy_gbs, "frac_of_copy": achieved / copy_gbs}
-    # node bytes the dominant walk touches (served mostly by L1/L2): node fetches per query from the
-    # walk statistics times the node size of the format the library's defaults walk (quantized nodes)
+    # estimate of the node bytes the dominant walk touches (served mostly by L1/L2): node fetches per
+    # query of the float walk (walk statistics) times the node size of the format the library's
+    # defaults walk (quantized nodes)
     ws = comps["walk_statistics"]
     visits = ws[f"knn{k}_visits_mean"] if dom == "knn" else (ws["radius_visits_mean"] if dom in (
         "spatial_count", "reduce_count", "reduce_sumdist") else None)

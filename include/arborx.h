@@ -570,8 +570,10 @@ arborx_status arborx_debug_morton64(const float *points, int64_t n, int32_t dim,
 
 /* Walk statistics for the touched-bytes measurement: visits[i] = node fetches
  * of query i in the one-query-per-thread depth-first radius walk over binary
- * nodes (op 0, radius) or in the kNN walk after its seeding (op 1, k 1..64).
- * Touched bytes = fetches x the node size (64 B in 3D).  Asynchronous. */
+ * nodes (op 0, radius) or in the kNN walk after its seeding (op 1, k 1..64),
+ * both over float nodes.  Touched bytes = fetches x the node size (64 B in 3D;
+ * an estimate for walks over quantized nodes, whose boxes are rounded outward).
+ * Asynchronous. */
 arborx_status arborx_debug_node_visits(arborx_tree tree, const float *queries, int64_t m, float radius, int32_t op,
                                        int32_t k, int32_t *visits, void *stream);
 

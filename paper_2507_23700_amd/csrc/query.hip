@@ -1011,8 +1011,9 @@ __global__ void k_count_up_to(const Node<D> *__restrict__ nodes, const QNode<D> 
 }
 
 // Walk statistics: node fetches per query of the one-query-per-thread radius
-// walk (op 0) or kNN walk (op 1, after its seeding), for the touched-bytes
-// figure (fetches x node bytes).
+// walk (op 0) or kNN walk (op 1, after its seeding) over float nodes, for the
+// touched-bytes estimate (fetches x node bytes; a walk over codes visits a few
+// nodes more, by its outward rounding).
 template <int D, int K>
 __global__ void k_debug_visits(const Node<D> *__restrict__ nodes, const uint64_t *__restrict__ codes, int n_nodes,
                                const float *__restrict__ leaves, int kind, const TreeHeader *__restrict__ hdr,
