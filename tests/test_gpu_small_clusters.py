@@ -47,6 +47,6 @@ def test_single_points_cost_no_turn_each():
             best = min(best, a.elapsed_time(b) / 1e3)
         return best
 
-    # without a core point nothing but the smallest indices is left out, which take one read and one atomic a point
+    # without a core point the smallest indices are left out: one read and one atomic a point, not 64 turns (twice the time)
     clusters, noise = seconds(1), seconds(9)
-    assert clusters < 1.25 * noise, (clusters, noise)
+    assert clusters < 1.5 * noise, (clusters, noise)
